@@ -99,23 +99,31 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
   pl.G = std::max<int64_t>(
       1, std::min<int64_t>(pl.G, ((int64_t)4 << 30) / std::max<int64_t>(pl.c * pl.Vp * pl.eb, 1)));
   if (g_max > 0) pl.G = std::min<int64_t>(pl.G, g_max);
-  // Chunks of whole 256-token tiles that share a dW group are processed as one
-  // chunk of the group's rows when a chunk's projection leaves its last round
-  // of tiles partly filled (its tiles are not a multiple of the 256 compute
-  // units) and dH runs per group anyway: the same transient (the group's dZ
-  // rows) and the same arithmetic per token and per grad_W contraction, with
-  // one projection launch (and one teacher bucketing) per group, so the
-  // partly filled round comes once per group. When a chunk's tiles fill whole
-  // rounds, each chunk's dH right after its own projection measured faster
-  // than one dH over the group.
+  // The chunks of a dW group are processed as one chunk of the group's rows
+  // when that saves work: the same transient (the group's dZ rows), the same
+  // arithmetic per token and per grad_W contraction.
+  //  * A chunk of few tiles (dH does not fill the compute units with it and
+  //    runs per group anyway): one projection per group instead of one per
+  //    chunk, unless the chunk's projection fills whole rounds of the 256
+  //    compute units with 2048 rows or more. Measured at D = 4096,
+  //    V = 131072 (whole rounds), unmerged and merged: chunk 256, 4096 tokens
+  //    10.80 and 9.55 ms; 512, 8192 tokens 19.26 and 18.59 ms; 1024, 16384
+  //    tokens 37.99 and 37.88 ms; 2048, 16384 tokens 37.61 and 37.84 ms. fp32,
+  //    256 tokens in chunks of 64: 488 and 250 us.
+  //  * A chunk whose tiles fill the chip is merged only when padding its last
+  //    256-token tile costs more than merging (above 5% of its rows): each
+  //    chunk's dH right after its own projection is faster than one dH over
+  //    the group (chunk 4000, 2.4% padding: 36.72 unmerged, 37.42 ms merged).
   pl.merged = 1;
-  const int64_t proj_tiles = cdiv(pl.c, kTile) * (pl.Vp / kTile);
-  const bool dh_grouped =
-      choose_dh_split(cdiv(pl.c, kTile) * cdiv(pl.D, kTile), pl.Vp * pl.eb / 128) > 1;
-  if (pl.G > 1 && pl.c % kTile == 0 && proj_tiles % 256 != 0 && dh_grouped) {
+  const int64_t dh_tiles = cdiv(pl.c, kTile) * cdiv(pl.D, kTile);
+  const bool dh_grouped = dh_tiles < 256 || choose_dh_split(dh_tiles, pl.Vp * pl.eb / 128) > 1;
+  const bool full_rounds =
+      pl.c % kTile == 0 && cdiv(pl.c, kTile) * (pl.Vp / kTile) % 256 == 0 && pl.c >= 2048;
+  const bool padded = (rup(pl.c, kTile) - pl.c) * 20 > pl.c;
+  if (pl.G > 1 && (padded || (dh_grouped && !full_rounds))) {
     pl.merged = pl.G;
-    pl.c *= pl.G;
-    pl.cp = pl.c;
+    pl.c = std::min<int64_t>(pl.c * pl.G, pl.N);
+    pl.cp = rup(pl.c, kTile);
     pl.nchunks = cdiv(pl.N, pl.c);
     pl.nblk = cdiv(pl.c, kLossRows);
     pl.G = 1;

@@ -137,3 +137,39 @@ def test_merged_chunks_with_short_last_group(gpu_lib):
     lt, lo = out["loss_per_token"], other["loss_per_token"]
     assert rel_max(to64(lt), to64(lo)) <= 1e-6
     assert torch.equal(lt[ignore.bool()], torch.zeros_like(lt[ignore.bool()]))
+
+
+@pytest.mark.parametrize("N,D,V,chunk", [
+    (2525, 16384, 300, 1024),   # 256 dH tiles per chunk: chunks kept apart, whole tiles
+    (2525, 16384, 300, 1010),   # the same with 1.4% padding: kept apart, rows prepared per chunk
+    (2525, 16384, 300, 900),    # 13.8% padding: merged, the last rows a partial tile
+    (1100, 64, 500, 256),       # few vocabulary K steps (no dH split): merged
+    (700, 128, 1000, 1),        # one-token chunks
+    (513, 64, 1000, 64),        # merged rows one past a tile edge
+])
+@pytest.mark.parametrize("masked", [False, True])
+def test_chunk_plans(gpu_lib, N, D, V, chunk, masked):
+    """Chunks merged into one per dW group or kept apart, on both sides of
+    the plan's rule: every output of the fused call against the oracle."""
+    K, tau, dev = 8, 1.0, "cuda"
+    # hidden scaled so that the logits' spread does not grow with D
+    hidden = ki.make_hidden(N, D, torch.bfloat16, dev, seed=ki.SEED_HIDDEN + 21,
+                            std=min(1.0, (4096 / D) ** 0.5))
+    W = ki.make_weight(V, D, torch.bfloat16, dev, seed=ki.SEED_W + 21)
+    idx, logit = ki.make_teacher(N, K, V, dev, seed=ki.SEED_TEACHER + 21)
+    ignore = None
+    if masked:
+        g = torch.Generator(device="cpu")
+        g.manual_seed(ki.SEED_MASK + 21)
+        ignore = (torch.rand(N, generator=g) < 0.3).to(torch.uint8).to(dev)
+    print(f"[plans] N={N} D={D} V={V} chunk={chunk} masked={masked}", flush=True)
+    out = gpu_lib.fwd_bwd(hidden, W, idx, logit, tau=tau, ignore=ignore, chunk=chunk,
+                          loss_per_token=True)
+    torch.cuda.synchronize()
+    ref = oracle_by_row_blocks(kd_topk_kl, to64(hidden), to64(W), to64(idx), to64(logit), tau,
+                               ignore=to64(ignore), block=256)
+    tol = TOL["bf16"]
+    assert abs(float(out["loss"]) - ref["loss"]) <= tol["loss"] * abs(ref["loss"])
+    assert rel_max(to64(out["loss_per_token"]), ref["loss_per_token"]) <= tol["loss"]
+    assert rel_max(to64(out["grad_hidden"]), ref["grad_hidden"]) <= tol["grad"]
+    assert rel_max(to64(out["grad_W"]), ref["grad_W"]) <= tol["grad"]
