@@ -56,7 +56,10 @@ typedef enum kd_status {
 } kd_status;
 
 typedef enum kd_dtype {
-  KD_F32 = 0,                    /* fp32 inputs, fp32 arithmetic throughout */
+  KD_F32 = 0,                    /* fp32 inputs; contractions at fp32 accuracy (each
+                                    operand as the exact sum of three bf16 terms,
+                                    bf16 MFMA, fp32 accumulate) and fp32 elsewhere.
+                                    Operands below 1e-33 keep fewer than 24 bits */
   KD_BF16 = 1                    /* bf16 inputs, bf16 MFMA, fp32 accumulate */
 } kd_dtype;
 

@@ -34,7 +34,9 @@ struct Plan {
   int64_t c;           // rows per chunk
   int64_t cp;          // c rounded up to the 256-row tile
   int64_t Vp;          // V rounded up to the 256-column tile
-  int64_t nVT;         // vocabulary tiles
+  int64_t nVT;         // 256-column vocabulary tiles
+  int64_t ts;          // the contractions' tile edge (256 bf16, 128 fp32)
+  int64_t units;       // their workgroups on the chip at once
   int64_t nchunks;
   int64_t nblk;        // loss partials of a full chunk (one per kLossRows rows)
   int64_t G;           // chunks whose dZ rows are gathered before one dH and one dW GEMM
@@ -63,13 +65,13 @@ kd_status check_problem(const kd_problem* p) {
 }
 
 // Split of the dH GEMM's K range (the vocabulary) so that the number of
-// workgroups fills whole waves of the 256 compute units.
-int choose_dh_split(int64_t tiles, int64_t ksteps) {
+// workgroups fills whole rounds of the `units` the chip runs at once.
+int choose_dh_split(int64_t tiles, int64_t ksteps, int64_t units) {
   int best = 1;
-  double best_eff = (double)tiles / (double)(cdiv(tiles, 256) * 256);
+  double best_eff = (double)tiles / (double)(cdiv(tiles, units) * units);
   for (int s = 2; s <= 16; ++s) {
     if (ksteps / s < 8) break;
-    const double eff = (double)(tiles * s) / (double)(cdiv(tiles * s, 256) * 256);
+    const double eff = (double)(tiles * s) / (double)(cdiv(tiles * s, units) * units);
     if (eff > best_eff + 0.05) {
       best = s;
       best_eff = eff;
@@ -90,6 +92,10 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
   pl.cp = rup(pl.c, kTile);
   pl.Vp = rup(pl.V, kTile);
   pl.nVT = pl.Vp / kTile;
+  pl.ts = kd_tile(pl.eb);
+  pl.units = kd_units(pl.eb);
+  pl.td = cdiv(pl.D, pl.ts);
+  pl.ksteps = pl.Vp * pl.eb / 128;
   pl.nchunks = cdiv(pl.N, pl.c);
   pl.nblk = cdiv(pl.c, kLossRows);
   // dW is accumulated in fp32 in place: each dW GEMM reads and writes all of
@@ -115,10 +121,11 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
   //    chunk's dH right after its own projection is faster than one dH over
   //    the group (chunk 4000, 2.4% padding: 36.72 unmerged, 37.42 ms merged).
   pl.merged = 1;
-  const int64_t dh_tiles = cdiv(pl.c, kTile) * cdiv(pl.D, kTile);
-  const bool dh_grouped = dh_tiles < 256 || choose_dh_split(dh_tiles, pl.Vp * pl.eb / 128) > 1;
-  const bool full_rounds =
-      pl.c % kTile == 0 && cdiv(pl.c, kTile) * (pl.Vp / kTile) % 256 == 0 && pl.c >= 2048;
+  const int64_t dh_tiles = cdiv(pl.c, pl.ts) * pl.td;
+  const bool dh_grouped =
+      dh_tiles < pl.units || choose_dh_split(dh_tiles, pl.ksteps, pl.units) > 1;
+  const bool full_rounds = pl.c % kTile == 0 &&
+                           cdiv(pl.c, pl.ts) * (pl.Vp / pl.ts) % pl.units == 0 && pl.c >= 2048;
   const bool padded = (rup(pl.c, kTile) - pl.c) * 20 > pl.c;
   if (pl.G > 1 && (padded || (dh_grouped && !full_rounds))) {
     pl.merged = pl.G;
@@ -137,9 +144,7 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
   // per tile), else once per chunk
   pl.prep_per_group = pl.G > 1 && pl.c % kTile == 0;
   pl.ng = pl.prep_per_group ? pl.G * pl.c : pl.cp;
-  pl.td = cdiv(pl.D, kTile);
-  pl.ksteps = pl.Vp * pl.eb / 128;
-  pl.dh_per_group = choose_dh_split(cdiv(pl.c, kTile) * pl.td, pl.ksteps) > 1;
+  pl.dh_per_group = choose_dh_split(cdiv(pl.c, pl.ts) * pl.td, pl.ksteps, pl.units) > 1;
   int64_t dh_rows[2];  // the row counts dH runs on: full and last chunk or group
   if (pl.dh_per_group) {
     dh_rows[0] = std::min<int64_t>(pl.G * pl.c, pl.N);
@@ -158,8 +163,8 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
   pl.off_p = take((size_t)pl.ng * pl.K * 4);
   pl.off_tidx = take((size_t)pl.ng * pl.K * 4);
   pl.off_rows = take((size_t)7 * pl.ng * 4);
-  pl.off_pm = take((size_t)pl.cp * pl.nVT * 4);
-  pl.off_ps = take((size_t)pl.cp * pl.nVT * 4);
+  pl.off_pm = take((size_t)pl.cp * (pl.Vp / pl.ts) * 4);
+  pl.off_ps = take((size_t)pl.cp * (pl.Vp / pl.ts) * 4);
   pl.off_hits = take((size_t)pl.ng * pl.K * 4);
   pl.off_hitp = take((size_t)pl.ng * pl.K * 4);
   pl.off_hoff = take((size_t)(pl.ng / kTile) * (pl.nVT + 1) * 4);
@@ -177,7 +182,7 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
     int64_t part = 0;
     for (int64_t r : dh_rows) {
       if (r <= 0) continue;
-      const int sp = choose_dh_split(cdiv(r, kTile) * pl.td, pl.ksteps);
+      const int sp = choose_dh_split(cdiv(r, pl.ts) * pl.td, pl.ksteps, pl.units);
       if (sp > 1) part = std::max<int64_t>(part, sp * r);
     }
     pl.off_dhs = part > 0 ? take((size_t)part * pl.D * 4) : 0;
@@ -185,9 +190,9 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
   // partial tiles of the dW contraction's split last round (when its tiles
   // leave the last round of the compute units partly filled)
   {
-    const int64_t tiles = cdiv(pl.D, kTile) * pl.nVT;
-    pl.off_dwp = (tiles > kDwUnits && tiles % kDwUnits != 0)
-                     ? take((size_t)kDwUnits * kTile * kTile * 4)
+    const int64_t tiles = pl.td * cdiv(pl.V, pl.ts);
+    pl.off_dwp = (tiles > pl.units && tiles % pl.units != 0)
+                     ? take((size_t)(pl.units * pl.ts * pl.ts) * 4)
                      : 0;
   }
   pl.total = align256(t);
@@ -416,7 +421,7 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
       h.ldz = pl.Vp;
       h.W = c.W;
       h.tokens = n;
-      h.split = choose_dh_split(cdiv(n, kTile) * pl.td, pl.ksteps);
+      h.split = choose_dh_split(cdiv(n, pl.ts) * pl.td, pl.ksteps, pl.units);
       h.partial = h.split > 1 ? reinterpret_cast<float*>(ws + pl.off_dhs) : nullptr;
       h.gh_f32 = (p->flags & KD_FLAG_GRAD_HIDDEN_F32) ? 1 : 0;
       h.gH = compact ? c.grad_hidden

@@ -21,10 +21,8 @@ typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4_t;
 typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2_t;
 typedef __attribute__((ext_vector_type(4))) int i32x4_t;  // buffer resource in 4 SGPRs
 
-constexpr int kTile = 256;                       // BM = BN
-constexpr int kThreads = 512;                    // 8 waves of 64: 2 (M) x 4 (N)
+constexpr int kTile = 256;                       // token and vocabulary tiles of the buckets
 constexpr int kRowB = 128;                       // bytes of a tile row per K step
-constexpr int kStages = 2;                       // LDS stages of the main loop
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -94,34 +92,31 @@ __device__ __forceinline__ f32x4_t mfma_slot(u32x4_t a, u32x4_t b, f32x4_t c, fl
   return c;
 }
 
-// A 256x256 tile is computed by NW waves: 8 waves in a 2 (M) x 4 (N) grid,
-// each 128x64, or 4 waves in a 2 x 2 grid, each 128x128 (its accumulators
-// then live in the AGPR half of the register file). Accumulator layout of wave
-// w (wm = w / (NW/2), wn = w % (NW/2)) after gemm_tile: acc.v[i][j][r]
-// (i < 8, j < NJ, r < 4) is C[m][n] with
-//   m = wm*128 + 16*i + 4*(lane>>4) + r
-//   n = wn*16*NJ + 16*j + (lane&15)
+// A tile of TS x TS outputs is computed by a workgroup of waves in a 2 (M) x
+// TS/64 (N) grid: 8 waves of 128x64 outputs each for TS = 256, 4 waves of
+// 64x64 for TS = 128. Accumulator layout: acc.v[i][j][r] (i < NI, j < 4, r < 4)
+// of wave (wm, wn) is C[m][n] with
+//   m = wm*16*NI + 16*i + 4*(lane>>4) + r
+//   n = wn*64 + 16*j + (lane&15)
 // (the 16x16 MFMA output layout: lane holds column lane&15 of 4 rows).
-template <int NW>
-struct WaveGrid {
-  static_assert(NW == 8 || NW == 4, "8 or 4 waves per 256x256 tile");
-  static constexpr int NJ = 32 / NW;         // 16-column blocks per wave
-  static constexpr int NPW = 32 / NW;        // DMA instructions per wave per operand step
-  __device__ static int wm(int wave) { return wave >> (NW == 8 ? 2 : 1); }
-  __device__ static int wn(int wave) { return wave & (NW / 2 - 1); }
+template <int TS>
+struct Geo {
+  static_assert(TS == 256 || TS == 128, "256x256 or 128x128 tiles");
+  static constexpr int NW = TS / 32;         // waves
+  static constexpr int NI = TS / 32;         // 16-row blocks per wave
+  static constexpr int kThreads = 64 * NW;
+  static constexpr int GM = 1024 / TS;       // tiles grouped along M in the tile order
+  __device__ static int wm(int wave) { return wave / (TS / 64); }
+  __device__ static int wn(int wave) { return wave % (TS / 64); }
+  __device__ static int acc_m(int wm, int i, int lane, int r) {
+    return wm * 16 * NI + 16 * i + 4 * (lane >> 4) + r;
+  }
+  __device__ static int acc_n(int wn, int j, int lane) { return wn * 64 + 16 * j + (lane & 15); }
 };
-template <int NJ>
-struct AccTileT {
-  f32x4_t v[8][NJ];
+template <int TS>
+struct AccTile {
+  f32x4_t v[Geo<TS>::NI][4];
 };
-typedef AccTileT<4> AccTile;  // 8-wave tiles
-__device__ __forceinline__ int acc_m(int wm, int i, int lane, int r) {
-  return wm * 128 + 16 * i + 4 * (lane >> 4) + r;
-}
-template <int NJ = 4>
-__device__ __forceinline__ int acc_n(int wn, int j, int lane) {
-  return wn * 16 * NJ + 16 * j + (lane & 15);
-}
 
 // One 256x256 output tile: acc = A[m0:m0+256, k-range] * B[n0:n0+256, k-range]^T.
 //
@@ -140,10 +135,10 @@ __device__ __forceinline__ int acc_n(int wn, int j, int lane) {
 //    gets element i%4 of the 8 bytes addressed by lane 4k + i/4 as its value
 //    k), so W, dZ and the hidden rows are consumed where they are.
 // Operands go straight from memory into LDS (buffer loads with the LDS-DMA
-// bit) through stages of 32 KiB per operand (two per operand, or three for A
-// and two for B); one barrier per K step; the next sub-step's fragments are
-// read while the current sub-step's MFMAs run. The caller's LDS must hold
-// kLdsMain bytes (kLdsA3 with SA = 3); ends with a barrier.
+// bit) through stages of 32 KiB per operand (three for A and two for B); one
+// barrier per K step; the next sub-step's fragments are read while the current
+// sub-step's MFMAs run. The caller's LDS must hold kLdsA3 bytes; ends with a
+// barrier. bf16 only: fp32 operands go through the 128x128 tiles of kd_f32.h.
 //
 // The DMA loads are issued from inline assembly, so the compiler does not
 // track them: it would otherwise make every transposing LDS read wait for all
@@ -153,8 +148,7 @@ __device__ __forceinline__ int acc_n(int wn, int j, int lane) {
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4_t;
 typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
 
-constexpr int kLdsMain = kStages * 2 * kTile * kRowB;  // 128 KiB
-constexpr int kLdsA3 = 5 * kTile * kRowB;              // 160 KiB: 3 A stages + 2 B stages
+constexpr int kLdsA3 = 5 * kTile * kRowB;  // 160 KiB: 3 A stages + 2 B stages
 
 struct KcOp {
   const char* base;
@@ -181,9 +175,6 @@ __device__ __forceinline__ int swz_kc(int row) { return row & 7; }
 __device__ __forceinline__ int swz_km16(int row) {
   return ((row & 3) | (((row >> 3) & 1) << 2)) << 1;
 }
-// K-major fp32 rows (1 KiB, 64 slots): a 32-bit read covers 4 slots of rows
-// r, r+4, r+8, r+12, which get the XOR values 0, 4, 8, 12.
-__device__ __forceinline__ int swz_km32(int row) { return ((row >> 2) & 3) << 2; }
 
 // s_waitcnt vmcnt(n) for a compile-time n; expcnt/lgkmcnt are not waited.
 #define KD_VMCNT(n) __builtin_amdgcn_s_waitcnt((0x0f70 & ~0x000f) | ((n) & 0xf) | (((n) >> 4) << 14))
@@ -267,15 +258,9 @@ struct OpDma<T, KmOp, NPW> {
   __device__ __forceinline__ void init(const KmOp& op, int wave, int lane) {
 #pragma unroll
     for (int i = 0; i < NPW; ++i) {
-      if constexpr (sizeof(T) == 2) {
-        // 2 K rows of 512 bytes per instruction: lane -> row 2q + lane/32, slot lane%32
-        const int row = (wave * NPW + i) * 2 + (lane >> 5);
-        voff[i] = (uint32_t)row * (uint32_t)op.ld + (uint32_t)(((lane & 31) ^ swz_km16(row)) << 4);
-      } else {
-        // 1 K row of 1 KiB per instruction: lane -> slot lane
-        const int row = wave * NPW + i;
-        voff[i] = (uint32_t)row * (uint32_t)op.ld + (uint32_t)((lane ^ swz_km32(row)) << 4);
-      }
+      // 2 K rows of 512 bytes per instruction: lane -> row 2q + lane/32, slot lane%32
+      const int row = (wave * NPW + i) * 2 + (lane >> 5);
+      voff[i] = (uint32_t)row * (uint32_t)op.ld + (uint32_t)(((lane & 31) ^ swz_km16(row)) << 4);
     }
   }
   __device__ __forceinline__ DmaStep<NPW> prep(const KmOp& op, char* stage, int wave, int ks,
@@ -295,7 +280,7 @@ struct OpDma<T, KmOp, NPW> {
 // Fragment reads of NB blocks of 16 rows (M or N) from `base` within the tile.
 // Sub-step s of a K step covers K elements [s*KS/2, (s+1)*KS/2) of the step;
 // lane (g = lane/16, j = lane%16) holds row base + 16b + j with K elements
-// s*KS/2 + 8g + 0..7 (bf16) or s*KS/2 + 4g + 0..3 (fp32), in both layouts.
+// s*KS/2 + 8g + 0..7, in both layouts.
 template <typename T, typename Op, int NB>
 struct OpFrag;
 
@@ -341,56 +326,22 @@ struct OpFrag<__bf16, KmOp, NB> {
   }
 };
 
-template <int NB>
-struct OpFrag<float, KmOp, NB> {
-  static constexpr int kReads = 4 * NB;
-  static constexpr int kRow = kTile * 4;
-  int off[NB];  // byte offset of K row 4g, sub-step 0
-  __device__ __forceinline__ void init(int base, int lane) {
-    const int g = lane >> 4, j = lane & 15;
-    const int row = 4 * g;
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int col = base + 16 * b + j;
-      off[b] = row * kRow + (((col >> 2) ^ swz_km32(row)) << 4) + ((col & 3) << 2);
-    }
-  }
-  __device__ __forceinline__ u32x4_t one(const char* op, int s, int b) const {
-    // K rows 16s + 4g + e share row 4g's swizzle (it depends on (row/4) % 4 only)
-    uint32_t v[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      v[e] = *reinterpret_cast<const uint32_t*>(op + off[b] + (16 * s + e) * kRow);
-    return u32x4_t{v[0], v[1], v[2], v[3]};
-  }
-};
-
-// SPREAD selects the fragment-read placement: false puts sub-step 1's reads
-// under the compiler's MFMA/read interleave (by hand, one per pair, with
-// SA = 3) and sub-step 0's reads on the first pairs of the second half; true
-// places both by hand, fragment f with pair f * NP / (8 + NJ). Which one is
-// faster depends on the operand layouts (measured per kernel). SA is the
-// number of A stages: 2 (all DMA of a step in its second half) or 3 (the DMA
-// split between the halves; 160 KiB of LDS).
-template <typename T, typename OA, typename OB, int NW = 8, bool SPREAD = false, int SA = 2>
+// SPREAD selects the fragment-read placement: false puts one read per MFMA
+// pair in order, true spreads them evenly, fragment f with pair f * NP / 12.
+// Which one is faster depends on the operand layouts (measured per kernel).
+template <typename T, typename OA, typename OB, bool SPREAD>
 __device__ __forceinline__ void gemm_tile(const OA& opa, const OB& opb, int ks_begin, int ks_end,
-                                          char* lds, AccTileT<WaveGrid<NW>::NJ>& acc) {
-  typedef WaveGrid<NW> WG;
-  constexpr int NJ = WG::NJ, NPW = WG::NPW;
-  constexpr int S = kStages;
+                                          char* lds, AccTile<256>& acc) {
+  typedef Geo<256> G;
+  constexpr int NJ = 4, NPW = 4;      // 16-column blocks, DMA instructions per operand step, per wave
   constexpr int OPB = kTile * kRowB;  // one operand's stage (32 KiB)
-  constexpr int STB = 2 * OPB;        // one stage (A and B)
   constexpr int NI = 2 * NPW;         // DMA instructions per K step per wave
   constexpr int NP = 4 * NJ;          // MFMA pairs per sub-step
-  constexpr int RD = OpFrag<T, OA, 8>::kReads + OpFrag<T, OB, NJ>::kReads;
-  constexpr int RQ = (RD + NP - 1) / NP;  // LDS reads per MFMA pair in sub-step 0
-  static_assert((S - 1) * NI <= 63, "vmcnt range of the in-flight DMA steps");
-  static_assert(2 * NI == NP, "one DMA instruction on every other MFMA pair");
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = wave_id();
-  const int wm = WG::wm(wave), wn = WG::wn(wave);
+  const int wm = G::wm(wave), wn = G::wn(wave);
 
 #pragma unroll
   for (int i = 0; i < 8; ++i)
@@ -410,15 +361,8 @@ __device__ __forceinline__ void gemm_tile(const OA& opa, const OB& opb, int ks_b
   OpFrag<T, OA, 8> fra;
   OpFrag<T, OB, NJ> frb;
   fra.init(wm * 128, lane);
-  frb.init(wn * 16 * NJ, lane);
+  frb.init(wn * 64, lane);
 
-  auto frag = [&](int stage, int s, u32x4_t (&fa)[8], u32x4_t (&fb)[NJ]) {
-    const char* a = lds + stage * STB;
-#pragma unroll
-    for (int b = 0; b < 8; ++b) fa[b] = fra.one(a, s, b);
-#pragma unroll
-    for (int b = 0; b < NJ; ++b) fb[b] = frb.one(a + OPB, s, b);
-  };
   // pair q: row block i = q / (NJ/2), two column blocks, in a snake order (odd
   // rows right to left) so that consecutive MFMAs change one operand only
   // (the fewest operand changes; measured ~0.8% faster per step than
@@ -430,7 +374,7 @@ __device__ __forceinline__ void gemm_tile(const OA& opa, const OB& opb, int ks_b
     acc.v[i][j1] = mfma_slot(fa[i], fb[j1], acc.v[i][j1], (T*)nullptr);
   };
 
-  if constexpr (SA == 3) {
+  {
     // Three A stages and two B stages (160 KiB): step k's A operand lives in
     // A stage k % 3 and its B operand in B stage k % 2. Step j+2's A DMA goes
     // out during step j's first half (into the A stage retired at barrier
@@ -514,92 +458,7 @@ __device__ __forceinline__ void gemm_tile(const OA& opa, const OB& opb, int ks_b
     }
     KD_VMCNT(0);
     __syncthreads();
-    return;
   }
-
-  // Step j lives in stage j % S; S steps of DMA are always in flight. Sub-step
-  // 0's MFMAs run interleaved with the reads of sub-step 1's fragments; then
-  // the wave waits for its reads and for step j+1's DMA, the barrier
-  // publishes every wave's DMA and retires stage j % S, and sub-step 1's MFMAs
-  // run in pairs: every other pair is issued with one DMA instruction of step
-  // j+S (into the retired stage; spreading them keeps the LDS writes from
-  // bunching up against the fragment reads), and the fragments of step j+1's
-  // sub-step 0 are read alongside (placement per SPREAD).
-#pragma unroll
-  for (int p = 0; p < S; ++p) {
-    char* a = lds + p * STB;
-    const bool live = ks_begin + p < ks_end;
-    const DmaStep<NPW> sa = da.prep(opa, a, wave, ks_begin + p, live);
-    const DmaStep<NPW> sb = db.prep(opb, a + OPB, wave, ks_begin + p, live);
-#pragma unroll
-    for (int i = 0; i < NPW; ++i) sa.one(i);
-#pragma unroll
-    for (int i = 0; i < NPW; ++i) sb.one(i);
-  }
-  KD_VMCNT((S - 1) * NI);
-  __syncthreads();
-  u32x4_t fa[2][8], fb[2][NJ];
-  frag(0, 0, fa[0], fb[0]);
-  int st = 0;
-  constexpr int NF = 8 + NJ;  // fragments per sub-step
-  auto read_at = [&](int q, const char* a, int s, u32x4_t (&xa)[8], u32x4_t (&xb)[NJ]) {
-#pragma unroll
-    for (int f = 0; f < NF; ++f)
-      if ((SPREAD ? (f * NP) / NF : f) == q) {
-        if (f < 8) xa[f] = fra.one(a, s, f);
-        else xb[f - 8] = frb.one(a + OPB, s, f - 8);
-      }
-  };
-  for (int j = 0; j < nsteps; ++j) {
-    if constexpr (SPREAD) {
-      const char* c = lds + st * STB;
-#pragma unroll
-      for (int q = 0; q < NP; ++q) {
-        mfma2(q, fa[0], fb[0]);
-        read_at(q, c, 1, fa[1], fb[1]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    } else {
-      frag(st, 1, fa[1], fb[1]);
-#pragma unroll
-      for (int q = 0; q < NP; ++q) mfma2(q, fa[0], fb[0]);
-#pragma unroll
-      for (int q = 0; q < NP; ++q) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);   // MFMA
-        __builtin_amdgcn_sched_group_barrier(0x100, RQ, 0);  // LDS read
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    __builtin_amdgcn_s_waitcnt(0xc07f & ~0x0f00);  // lgkmcnt(0)
-    KD_VMCNT((S - 2) * NI);
-    __syncthreads();
-    const int nst = st + 1 == S ? 0 : st + 1;
-    {
-      char* a = lds + st * STB;
-      const char* n = lds + nst * STB;
-      const int ks = ks_begin + j + S;
-      const DmaStep<NPW> sa = da.prep(opa, a, wave, ks, ks < ks_end);
-      const DmaStep<NPW> sb = db.prep(opb, a + OPB, wave, ks, ks < ks_end);
-#pragma unroll
-      for (int q = 0; q < NP; ++q) {
-        if ((q & 1) == 0) {
-          if (q < 2 * NPW) sa.one(q >> 1);
-          else sb.one((q - 2 * NPW) >> 1);
-        }
-        mfma2(q, fa[1], fb[1]);
-        if constexpr (SPREAD) {
-          read_at(q, n, 0, fa[0], fb[0]);
-        } else {
-          if (q < 8) fa[0][q] = fra.one(n, 0, q);
-          else if (q < 8 + NJ) fb[0][q - 8] = frb.one(n + OPB, 0, q - 8);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    st = nst;
-  }
-  KD_VMCNT(0);
-  __syncthreads();
 }
 
 // ---------------------------------------------------------------- wave ops --

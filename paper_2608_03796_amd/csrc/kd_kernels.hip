@@ -21,6 +21,7 @@
 // Per group of chunks: transpose_rows, dw -> grad_W (+)= dZ^T H (fp32 accumulate)
 // Per call:    finalize_loss     -> mean over non-ignored tokens
 #include "kd_device.h"
+#include "kd_f32.h"
 #include <type_traits>
 #include "kd_launch.h"
 
@@ -212,6 +213,54 @@ __global__ __launch_bounds__(64) void k_teacher_prologue(
   }
 }
 
+// ------------------------------------------------------- contraction core --
+// One TS x TS tile of the contraction: bf16 operands in 256x256 tiles
+// (gemm_tile), fp32 operands in 128x128 tiles of split bf16 (gemm_f32). LDS
+// bytes: gemm_lds.
+template <typename T, int TS, bool SPREAD, typename OA, typename OB>
+__device__ __forceinline__ void gemm(const OA& a, const OB& b, int kb, int ke, char* lds,
+                                     AccTile<TS>& acc) {
+  if constexpr (TS == 256) gemm_tile<T, OA, OB, SPREAD>(a, b, kb, ke, lds, acc);
+  else gemm_f32<OA, OB>(a, b, kb, ke, lds, acc);
+}
+template <int TS>
+constexpr int gemm_lds = TS == 256 ? kLdsA3 : kLdsF32;
+
+// Epilogues of the projection kernels stage the fp32 tile in LDS half of its
+// tokens at a time, as [token][vocab] rows of TS floats with a 16-byte-slot
+// swizzle.
+template <int TS>
+constexpr int stage_bytes = TS / 2 * TS * 4;  // 128 KiB or 32 KiB
+__device__ __forceinline__ int hsw16(int n) { return (n ^ (n >> 3)) & 15; }
+template <int TS>
+__device__ __forceinline__ float* stage_cell(float* st, int n, int v) {
+  return st + n * TS + ((((v >> 2) ^ hsw16(n)) << 2) | (v & 3));
+}
+// the waves holding half h's tokens write it
+template <int TS>
+__device__ __forceinline__ void stage_half(float* st, const AccTile<TS>& acc, int h, int wm, int wn,
+                                           int lane) {
+  typedef Geo<TS> G;
+  if (wn / (G::NW / 4) != h) return;
+#pragma unroll
+  for (int i = 0; i < G::NI; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int n = G::acc_n(wn, j, lane) & (TS / 2 - 1);  // token row of the half
+      const int vl = G::acc_m(wm, i, lane, 0);             // 4 consecutive vocab
+      *reinterpret_cast<f32x4_t*>(stage_cell<TS>(st, n, vl)) = acc.v[i][j];
+    }
+}
+// The teacher entries of a tile: the bucket of the 256x256 tile that holds it.
+// An entry's token and column within the TS x TS tile at (m0, n0); false when
+// it lies in another part of the 256x256 tile.
+template <int TS>
+__device__ __forceinline__ bool entry_cell(uint32_t e, int m0, int n0, int& tl, int& v) {
+  tl = (int)(e & 255u) - (n0 & 255);
+  v = (int)((e >> 8) & 255u) - (m0 & 255);
+  return TS == 256 || ((unsigned)tl < (unsigned)TS && (unsigned)v < (unsigned)TS);
+}
+
 // ------------------------------------------------- logits + online LSE -----
 // Tile of z^T = W H_c^T (M = vocabulary, N = chunk tokens). Each lane holds 32
 // vocabulary values of 4 tokens; the per-token max and sum of 2^(y - max) of
@@ -232,10 +281,10 @@ constexpr int kZhBits = 0;                      // LDS: 256 tokens x 8 words
 constexpr int kZhPre = 8192;                    // exclusive prefix per word
 constexpr int kZhWs = 16384;                    // per-wave totals of the scan
 constexpr int kZhVal = 16384 + 64;              // z of the marked cells
-constexpr int kZhCap = (kLdsMain - kZhVal) / 4; // 28656 cells
+constexpr int kZhCap = (kLdsA3 - 32768 - kZhVal) / 4; // 28656 cells
 
-template <typename T>
-__global__ __launch_bounds__(kThreads, 1) void k_logits_lse(const T* __restrict__ W,
+template <typename T, int TS>
+__global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_logits_lse(const T* __restrict__ W,
                                                             const T* __restrict__ Hc, int D,
                                                             int V, int rows, int TM, int TN,
                                                             float k2, float* part_m,
@@ -245,10 +294,11 @@ __global__ __launch_bounds__(kThreads, 1) void k_logits_lse(const T* __restrict_
                                                             float* zhit,
                                                             const int* __restrict__ nrow,
                                                             int nrow_base) {
-  __shared__ __attribute__((aligned(16))) char lds[kLdsA3];
+  typedef Geo<TS> G;
+  __shared__ __attribute__((aligned(16))) char lds[gemm_lds<TS>];
   int mt, nt;
-  tile_coords(blockIdx.x, TM, TN, 4, mt, nt);
-  const int m0 = mt * kTile, n0 = nt * kTile;
+  tile_coords(blockIdx.x, TM, TN, G::GM, mt, nt);
+  const int m0 = mt * TS, n0 = nt * TS;
   const int eb = Elt<T>::bytes;
   const int ld = D * eb;
   // with ignored tokens left out only the first *nrow - nrow_base rows hold
@@ -258,22 +308,38 @@ __global__ __launch_bounds__(kThreads, 1) void k_logits_lse(const T* __restrict_
     trows = min(rows, __builtin_amdgcn_readfirstlane(*nrow) - nrow_base);
     if (n0 >= trows) return;
   }
-  const int mrows = min(kTile, V - m0), nrows = min(kTile, trows - n0);
-  AccTile acc;
-  gemm_tile<T, KcOp, KcOp, 8, false, 3>(
+  const int mrows = max(0, min(TS, V - m0)), nrows = min(TS, trows - n0);
+  AccTile<TS> acc;
+  gemm<T, TS, false>(
       KcOp{reinterpret_cast<const char*>(W + (int64_t)m0 * D), (uint32_t)(mrows * ld), ld},
       KcOp{reinterpret_cast<const char*>(Hc + (int64_t)n0 * D), (uint32_t)(nrows * ld), ld}, 0,
       ld / kRowB, lds, acc);
 
   const int lane = threadIdx.x & 63, wave = wave_id();
-  const int wm = wave >> 2, wn = wave & 3;
-  const bool full = m0 + kTile <= V;
-  if (zhit != nullptr) {
-    const int tid = threadIdx.x;
-    const int64_t seg = (int64_t)nt * kTile * K;
-    const int* ho = hoff + (int64_t)nt * (nVT + 1) + mt;
-    const int hb = ho[0], cnt = ho[1] - hb;
-    const uint32_t* hl = hits + seg + hb;
+  const int wm = G::wm(wave), wn = G::wn(wave);
+  const bool full = m0 + TS <= V;
+  const int tid = threadIdx.x;
+  const int nt256 = n0 / kTile;
+  const int64_t seg = (int64_t)nt256 * kTile * K;
+  const int* ho = hoff + (int64_t)nt256 * (nVT + 1) + m0 / kTile;
+  const int hb = ho[0], cnt = ho[1] - hb;
+  const uint32_t* hl = hits + seg + hb;
+  if constexpr (TS == 128) {
+    // a small tile: staged in LDS, each entry reads its cell
+    float* st = reinterpret_cast<float*>(lds);
+    for (int h = 0; h < 2; ++h) {
+      stage_half<TS>(st, acc, h, wm, wn, lane);
+      __syncthreads();
+      for (int q = tid; q < cnt; q += G::kThreads) {
+        const uint32_t e = hl[q];
+        int tl, v;
+        if (entry_cell<TS>(e, m0, n0, tl, v) && tl / (TS / 2) == h)
+          zhit[(int64_t)(n0 + tl) * K + (e >> 16)] = *stage_cell<TS>(st, tl & (TS / 2 - 1), v);
+      }
+      __syncthreads();
+    }
+  } else {
+    constexpr int kThreads = G::kThreads;
     uint32_t* bits = reinterpret_cast<uint32_t*>(lds + kZhBits);
     int* pre = reinterpret_cast<int*>(lds + kZhPre);
     int* wsum = reinterpret_cast<int*>(lds + kZhWs);
@@ -304,11 +370,11 @@ __global__ __launch_bounds__(kThreads, 1) void k_logits_lse(const T* __restrict_
     const int g = lane >> 4;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int n = acc_n(wn, j, lane);  // token in the tile
+      const int n = G::acc_n(wn, j, lane);  // token in the tile
       const u32x4_t wd = *reinterpret_cast<const u32x4_t*>(bits + n * 8 + wm * 4);
       const i32x4_t wp = *reinterpret_cast<const i32x4_t*>(pre + n * 8 + wm * 4);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
+      for (int i = 0; i < G::NI; ++i) {
         const int sh = 16 * (i & 1) + 4 * g;  // bit of the cell's first column in its word
         const uint32_t nib = (wd[i >> 1] >> sh) & 15u;
         if (nib == 0u) continue;
@@ -319,7 +385,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_logits_lse(const T* __restrict_
           if (rank < kZhCap) {
             zval[rank] = acc.v[i][j][r];
           } else {
-            const uint32_t cell = (uint32_t)n | ((uint32_t)acc_m(wm, i, lane, r) << 8);
+            const uint32_t cell = (uint32_t)n | ((uint32_t)G::acc_m(wm, i, lane, r) << 8);
             for (int q = 0; q < cnt; ++q) {
               const uint32_t e = hl[q];
               if ((e & 0xffffu) == cell) zhit[(int64_t)(n0 + n) * K + (e >> 16)] = acc.v[i][j][r];
@@ -349,10 +415,10 @@ __global__ __launch_bounds__(kThreads, 1) void k_logits_lse(const T* __restrict_
     for (int j = 0; j < 4; ++j) {
       float za = -INFINITY;
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
+      for (int i = 0; i < G::NI; ++i)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          if (kFull || m0 + acc_m(wm, i, lane, r) < V) za = fmaxf(za, acc.v[i][j][r]);
+          if (kFull || m0 + G::acc_m(wm, i, lane, r) < V) za = fmaxf(za, acc.v[i][j][r]);
       // the four lane groups (lane>>4) hold the other rows of the same token
       za = fmaxf(za, __shfl_xor(za, 16));
       za = fmaxf(za, __shfl_xor(za, 32));
@@ -360,11 +426,11 @@ __global__ __launch_bounds__(kThreads, 1) void k_logits_lse(const T* __restrict_
       float s = 0.f;
       if (mx != -INFINITY) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < G::NI; ++i)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const float e = fast_exp2(acc.v[i][j][r] * k2 - mx);
-            if (kFull || m0 + acc_m(wm, i, lane, r) < V) s += e;
+            if (kFull || m0 + G::acc_m(wm, i, lane, r) < V) s += e;
           }
       }
       s += __shfl_xor(s, 16);
@@ -385,7 +451,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_logits_lse(const T* __restrict_
   if (wm == 0 && lane < 16) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int t = n0 + acc_n(wn, j, lane);
+      const int t = n0 + G::acc_n(wn, j, lane);
       const float m1 = rm[j], s1 = rs[j];
       const float m2 = xch[((wn * 4 + j) * 16 + lane) * 2 + 0];
       const float s2 = xch[((wn * 4 + j) * 16 + lane) * 2 + 1];
@@ -393,8 +459,8 @@ __global__ __launch_bounds__(kThreads, 1) void k_logits_lse(const T* __restrict_
       float ss = 0.f;
       if (mm != -INFINITY) ss = s1 * fast_exp2(m1 - mm) + s2 * fast_exp2(m2 - mm);
       if (t < rows) {
-        part_m[(int64_t)t * nVT + mt] = mm;
-        part_s[(int64_t)t * nVT + mt] = ss;
+        part_m[(int64_t)t * TM + mt] = mm;
+        part_s[(int64_t)t * TM + mt] = ss;
       }
     }
   }
@@ -536,8 +602,6 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket(const int32_t* __rest
 // its final value (g/tau)(M q - p), its z is recorded for C, and a bitmap marks
 // it; then one wave per token row forms G = (g/tau) M 2^(y - L2) elsewhere and
 // stores the row of dZ[rows, Vp] (columns V..Vp as zeros).
-__device__ __forceinline__ int hsw16(int n) { return (n ^ (n >> 3)) & 15; }
-
 // largest exponent (base 2) of the sum of a tile row's stored provisional
 // gradients 2^(y - R), and so of each of them
 constexpr float kRefGap = 40.f;
@@ -548,22 +612,27 @@ constexpr float kRefGapScale = 1099511627776.f;  // 2^kRefGap
 // i.e. 2^-102 below the reference logit, flush to zero
 constexpr float kRefShift = 24.f;
 
-// epilogue LDS (the main loop's stages are free by then): staging [0, 128 KiB)
-constexpr int kDzBits = kLdsMain;              // 128 x 256-bit hit map of one half
-constexpr int kDzRows = kDzBits + 4 * 1024;    // 3 x 256 floats: g/tau M, g/tau, log2 Z
-static_assert(kDzRows + 3 * 1024 <= kLdsA3, "dZ epilogue LDS");
+// epilogue LDS (the main loop's stages are free by then), after the staging area
+template <int TS>
+constexpr int kDzBits = stage_bytes<TS>;                // TS/2 x TS-bit hit map of one half
+template <int TS>
+constexpr int kDzRows = kDzBits<TS> + TS / 2 * TS / 8;  // 3 x TS floats: g/tau M, g/tau, log2 Z
+static_assert(kDzRows<256> + 3 * 1024 <= gemm_lds<256>, "dZ epilogue LDS");
+static_assert(kDzRows<128> + 3 * 512 <= gemm_lds<128>, "dZ epilogue LDS");
 
-template <typename T>
-__global__ __launch_bounds__(kThreads, 1) void k_dz(
+template <typename T, int TS>
+__global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dz(
     const T* __restrict__ W, const T* __restrict__ Hc, int D, int V, int rows, int TM, int TN,
     float k2, const float* __restrict__ rowL2, const float* __restrict__ rowCoef,
     const float* __restrict__ rowCoefM, const uint32_t* __restrict__ hits,
     const float* __restrict__ hitp, const int* __restrict__ hoff, int K, int nVT, T* dZ,
     int64_t ldz, float* zhit, const int* __restrict__ nrow, int nrow_base) {
-  __shared__ __attribute__((aligned(16))) char lds[kLdsA3];
+  typedef Geo<TS> G;
+  constexpr int kThreads = G::kThreads, HT = TS / 2;  // HT: tokens staged at a time
+  __shared__ __attribute__((aligned(16))) char lds[gemm_lds<TS>];
   int mt, nt;
-  tile_coords(blockIdx.x, TM, TN, 4, mt, nt);
-  const int m0 = mt * kTile, n0 = nt * kTile;
+  tile_coords(blockIdx.x, TM, TN, G::GM, mt, nt);
+  const int m0 = mt * TS, n0 = nt * TS;
   const int eb = Elt<T>::bytes;
   const int ld = D * eb;
   // with ignored tokens left out only the first *nrow - nrow_base rows hold
@@ -573,13 +642,13 @@ __global__ __launch_bounds__(kThreads, 1) void k_dz(
     trows = min(rows, __builtin_amdgcn_readfirstlane(*nrow) - nrow_base);
     if (n0 >= trows) return;
   }
-  const int mrows = min(kTile, V - m0), nrows = min(kTile, trows - n0);
+  const int mrows = max(0, min(TS, V - m0)), nrows = min(TS, trows - n0);
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
-  const int wm = wave >> 2, wn = wave & 3;
+  const int wm = G::wm(wave), wn = G::wn(wave);
 
   // this tile's bucket of teacher entries
-  const int64_t seg = (int64_t)nt * kTile * K;
-  const int* ho = hoff + (int64_t)nt * (nVT + 1) + mt;
+  const int64_t seg = (int64_t)(n0 / kTile) * kTile * K;
+  const int* ho = hoff + (int64_t)(n0 / kTile) * (nVT + 1) + m0 / kTile;
   const int hb = ho[0], cnt = ho[1] - hb;
   // wave w holds the scalars of tokens [32 w, 32 w + 32): lane l has token
   // 32 w + (l & 31), g/tau M and g/tau (l < 32) or log2 Z (l >= 32, in rv0)
@@ -597,46 +666,38 @@ __global__ __launch_bounds__(kThreads, 1) void k_dz(
     fpk = hitp[seg + hb + tid];
   }
 
-  AccTile acc;
-  gemm_tile<T, KcOp, KcOp, 8, false, 3>(
+  AccTile<TS> acc;
+  gemm<T, TS, false>(
       KcOp{reinterpret_cast<const char*>(W + (int64_t)m0 * D), (uint32_t)(mrows * ld), ld},
       KcOp{reinterpret_cast<const char*>(Hc + (int64_t)n0 * D), (uint32_t)(nrows * ld), ld}, 0,
       ld / kRowB, lds, acc);
   {
-    float* rs = reinterpret_cast<float*>(lds + kDzRows);
+    float* rs = reinterpret_cast<float*>(lds + kDzRows<TS>);
     const int t = 32 * wave + (lane & 31);
     if (lane < 32) {
       rs[t] = rv0;
-      rs[256 + t] = rv1;
+      rs[TS + t] = rv1;
     } else {
-      rs[512 + t] = rv0;
+      rs[2 * TS + t] = rv0;
     }
   }
 
   float* st = reinterpret_cast<float*>(lds);
-  const float* rs_cm = reinterpret_cast<const float*>(lds + kDzRows);
-  const float* rs_cf = rs_cm + 256;
-  const float* rs_l2 = rs_cm + 512;
-  uint32_t* hbits = reinterpret_cast<uint32_t*>(lds + kDzBits);
-  const int vl0 = 4 * lane;  // this lane's 4 vocabulary columns in the row pass
+  const float* rs_cm = reinterpret_cast<const float*>(lds + kDzRows<TS>);
+  const float* rs_cf = rs_cm + TS;
+  const float* rs_l2 = rs_cm + 2 * TS;
+  uint32_t* hbits = reinterpret_cast<uint32_t*>(lds + kDzBits<TS>);
+  // row pass: 4 vocabulary columns per lane, RPI token rows per wave and
+  // iteration (the whole wave on one row of 256 columns, half of it on 128)
+  constexpr int LPR = TS / 4, RPI = 64 / LPR;
+  const int vl0 = 4 * (lane % LPR);
 
   // unrolled: a loop header here would make the compiler wait for the first
   // half's dZ stores before staging the second half
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    if ((wn >> 1) == h) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int n = (wn & 1) * 64 + 16 * j + (lane & 15);  // token row of the half
-          const int vl = acc_m(wm, i, lane, 0);                 // 4 consecutive vocab
-          const int slot = (vl >> 2) ^ hsw16(n);
-          *reinterpret_cast<f32x4_t*>(st + n * 256 + slot * 4) = acc.v[i][j];
-        }
-    }
-    hbits[tid] = 0u;
-    hbits[tid + kThreads] = 0u;
+    stage_half<TS>(st, acc, h, wm, wn, lane);
+    for (int q = tid; q < HT * TS / 32; q += kThreads) hbits[q] = 0u;
     __syncthreads();
 
     // Teacher entries of this half: dZ = (g/tau) M q - (g/tau) p in place,
@@ -644,14 +705,14 @@ __global__ __launch_bounds__(kThreads, 1) void k_dz(
     // bucket in registers; a skewed teacher with more entries in one tile
     // than threads reads the rest from memory.
     auto fold = [&](uint32_t e, float pk) {
-      const int tl = (int)(e & 255u);
-      if ((tl >> 7) != h) return;
-      const int n = tl & 127, v = (int)((e >> 8) & 255u), k = (int)(e >> 16);
-      float* cell = st + n * 256 + ((((v >> 2) ^ hsw16(n)) << 2) | (v & 3));
+      int tl, v;
+      if (!entry_cell<TS>(e, m0, n0, tl, v) || tl / HT != h) return;
+      const int n = tl & (HT - 1);
+      float* cell = stage_cell<TS>(st, n, v);
       const float z = *cell;
-      if (zhit != nullptr) zhit[(int64_t)(n0 + tl) * K + k] = z;
+      if (zhit != nullptr) zhit[(int64_t)(n0 + tl) * K + (e >> 16)] = z;
       *cell = rs_cm[tl] * fast_exp2(z * k2 - rs_l2[tl]) - rs_cf[tl] * pk;
-      atomicOr(&hbits[n * 8 + (v >> 5)], 1u << (v & 31));
+      atomicOr(&hbits[n * (TS / 32) + (v >> 5)], 1u << (v & 31));
     };
     if (tid < cnt) fold(fe, fpk);
     // a bucket with more entries than threads: the rest from memory
@@ -666,45 +727,57 @@ __global__ __launch_bounds__(kThreads, 1) void k_dz(
       // a wave-uniform test, and columns past V get no mask (their z is
       // exactly 0, as W's rows past V read as zeros, so they hold finite
       // values that only ever meet those zero rows).
-      const int rb = wave * 16;                                      // first row in the half
-      const int nrow = max(0, min(16, rows - (n0 + 128 * h + rb)));  // rows that exist
-      {
+      const int rb = wave * 16 + lane / LPR;                        // first row in the half
+      const int nrow = max(0, min(16, rows - (n0 + HT * h + wave * 16)));  // rows that exist
 #pragma unroll
-        for (int b8 = 0; b8 < 16; b8 += 8) {
-          f32x4_t zr[8];
-          uint32_t mk[8];
+      for (int b8 = 0; b8 < 16 / RPI; b8 += 8) {
+        f32x4_t zr[8];
+        uint32_t mk[8];
 #pragma unroll
-          for (int rr = 0; rr < 8; ++rr) {
-            const int n = rb + b8 + rr;
-            zr[rr] = *reinterpret_cast<const f32x4_t*>(st + n * 256 + ((lane ^ hsw16(n)) << 2));
-            mk[rr] = (hbits[n * 8 + (lane >> 3)] >> ((lane & 7) * 4)) & 15u;
-          }
-          f32x4_t cmv[2], l2v[2];  // the rows' g/tau M and log2 Z (16-byte aligned runs)
+        for (int rr = 0; rr < 8; ++rr) {
+          const int n = rb + (b8 + rr) * RPI;
+          zr[rr] = *reinterpret_cast<const f32x4_t*>(stage_cell<TS>(st, n, vl0));
+          mk[rr] = (hbits[n * (TS / 32) + (vl0 >> 5)] >> (vl0 & 31)) & 15u;
+        }
+        float cmv[8], l2v[8];  // the rows' g/tau M and log2 Z
+        if constexpr (RPI == 1) {
 #pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            cmv[u] = *reinterpret_cast<const f32x4_t*>(rs_cm + 128 * h + rb + b8 + 4 * u);
-            l2v[u] = *reinterpret_cast<const f32x4_t*>(rs_l2 + 128 * h + rb + b8 + 4 * u);
-          }
+          for (int u = 0; u < 2; ++u) {  // the same for the wave: 16-byte aligned runs
+            const f32x4_t c4 = *reinterpret_cast<const f32x4_t*>(rs_cm + HT * h + rb + b8 + 4 * u);
+            const f32x4_t l4 = *reinterpret_cast<const f32x4_t*>(rs_l2 + HT * h + rb + b8 + 4 * u);
 #pragma unroll
-          for (int rr = 0; rr < 8; ++rr) {
-            const float cm = cmv[rr >> 2][rr & 3], L2 = l2v[rr >> 2][rr & 3];
-            f32x4_t G;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) G[e] = cm * fast_exp2(zr[rr][e] * k2 - L2);
-            if (__builtin_amdgcn_ballot_w64(mk[rr] != 0u) != 0ull) {
-              // teacher cells hold their final value (patched by the fold)
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if ((mk[rr] >> e) & 1u) G[e] = zr[rr][e];
+            for (int e = 0; e < 4; ++e) {
+              cmv[4 * u + e] = c4[e];
+              l2v[4 * u + e] = l4[e];
             }
-            if (b8 + rr < nrow) {
-              T* dst = dZ + (int64_t)(n0 + 128 * h + rb + b8 + rr) * ldz + m0 + vl0;
-              if constexpr (sizeof(T) == 2) {
-                u32x2_t pk2 = {pack_bf16x2(G[0], G[1]), pack_bf16x2(G[2], G[3])};
-                *reinterpret_cast<u32x2_t*>(dst) = pk2;
-              } else {
-                *reinterpret_cast<f32x4_t*>(dst) = G;
-              }
+          }
+        } else {
+#pragma unroll
+          for (int rr = 0; rr < 8; ++rr) {
+            cmv[rr] = rs_cm[HT * h + rb + (b8 + rr) * RPI];
+            l2v[rr] = rs_l2[HT * h + rb + (b8 + rr) * RPI];
+          }
+        }
+#pragma unroll
+        for (int rr = 0; rr < 8; ++rr) {
+          const float cm = cmv[rr], L2 = l2v[rr];
+          f32x4_t g;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) g[e] = cm * fast_exp2(zr[rr][e] * k2 - L2);
+          if (__builtin_amdgcn_ballot_w64(mk[rr] != 0u) != 0ull) {
+            // teacher cells hold their final value (patched by the fold)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if ((mk[rr] >> e) & 1u) g[e] = zr[rr][e];
+          }
+          const int nr = (b8 + rr) * RPI + lane / LPR;
+          if (nr < nrow) {
+            T* dst = dZ + (int64_t)(n0 + HT * h + wave * 16 + nr) * ldz + m0 + vl0;
+            if constexpr (sizeof(T) == 2) {
+              u32x2_t pk2 = {pack_bf16x2(g[0], g[1]), pack_bf16x2(g[2], g[3])};
+              *reinterpret_cast<u32x2_t*>(dst) = pk2;
+            } else {
+              *reinterpret_cast<f32x4_t*>(dst) = g;
             }
           }
         }
@@ -731,17 +804,19 @@ __global__ __launch_bounds__(kThreads, 1) void k_dz(
 // rescales them).
 // The [c, V] buffer is the same transient chunk the recompute schedule holds;
 // nothing grows with N. Staging and teacher bookkeeping are those of k_dz.
-template <typename T>
-__global__ __launch_bounds__(kThreads, 1) void k_logits_dz(
+template <typename T, int TS>
+__global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_logits_dz(
     const T* __restrict__ W, const T* __restrict__ Hc, int D, int V, int rows, int TM, int TN,
     float k2, float* __restrict__ part_m, float* __restrict__ part_s, int nVT,
     const uint32_t* __restrict__ hits, const int* __restrict__ hoff, int K, T* dZ, int64_t ldz,
     float* zhit, const float* __restrict__ rowR, int* rowFlag, const int* __restrict__ nrow,
     int nrow_base) {
-  __shared__ __attribute__((aligned(16))) char lds[kLdsA3];
+  typedef Geo<TS> G;
+  constexpr int kThreads = G::kThreads, HT = TS / 2;  // HT: tokens staged at a time
+  __shared__ __attribute__((aligned(16))) char lds[gemm_lds<TS>];
   int mt, nt;
-  tile_coords(blockIdx.x, TM, TN, 4, mt, nt);
-  const int m0 = mt * kTile, n0 = nt * kTile;
+  tile_coords(blockIdx.x, TM, TN, G::GM, mt, nt);
+  const int m0 = mt * TS, n0 = nt * TS;
   const int eb = Elt<T>::bytes;
   const int ld = D * eb;
   // with ignored tokens left out only the first *nrow - nrow_base rows hold
@@ -753,57 +828,46 @@ __global__ __launch_bounds__(kThreads, 1) void k_logits_dz(
     trows = min(rows, __builtin_amdgcn_readfirstlane(*nrow) - nrow_base);
     if (n0 >= trows) return;
   }
-  const int mrows = min(kTile, V - m0), nrows = min(kTile, trows - n0);
+  const int mrows = max(0, min(TS, V - m0)), nrows = min(TS, trows - n0);
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
-  const int wm = wave >> 2, wn = wave & 3;
+  const int wm = G::wm(wave), wn = G::wn(wave);
 
-  const int64_t seg = (int64_t)nt * kTile * K;
-  const int* ho = hoff + (int64_t)nt * (nVT + 1) + mt;
+  const int64_t seg = (int64_t)(n0 / kTile) * kTile * K;
+  const int* ho = hoff + (int64_t)(n0 / kTile) * (nVT + 1) + m0 / kTile;
   const int hb = ho[0], cnt = ho[1] - hb;
   const uint32_t fe = tid < cnt ? hits[seg + hb + tid] : 0u;
   // the tile's reference logits, loaded before the main loop: a load issued
   // in the epilogue would wait for every store issued before it (loads and
   // stores complete in order), serialising the row pass on its stores
-  const float rref = (tid < kTile && n0 + tid < rows) ? rowR[n0 + tid] : 0.f;
+  const float rref = (tid < TS && n0 + tid < rows) ? rowR[n0 + tid] : 0.f;
 
-  AccTile acc;
-  gemm_tile<T, KcOp, KcOp, 8, false, 3>(
+  AccTile<TS> acc;
+  gemm<T, TS, false>(
       KcOp{reinterpret_cast<const char*>(W + (int64_t)m0 * D), (uint32_t)(mrows * ld), ld},
       KcOp{reinterpret_cast<const char*>(Hc + (int64_t)n0 * D), (uint32_t)(nrows * ld), ld}, 0,
       ld / kRowB, lds, acc);
-  const bool full = m0 + kTile <= V;
+  const bool full = m0 + TS <= V;
 
   float* st = reinterpret_cast<float*>(lds);
-  // past the staging area: R of the tile's 256 tokens (0 past the chunk)
-  float* rs_r = reinterpret_cast<float*>(lds + kLdsMain);
-  if (tid < kTile) rs_r[tid] = rref;
+  // past the staging area: R of the tile's tokens (0 past the chunk)
+  float* rs_r = reinterpret_cast<float*>(lds + stage_bytes<TS>);
+  if (tid < TS) rs_r[tid] = rref;
+  constexpr int NK = TS / 64;
   const int rho = lane >> 4, lam = lane & 15;  // row pass: 4 token rows per wave, 16 lanes each
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    if ((wn >> 1) == h) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int n = (wn & 1) * 64 + 16 * j + (lane & 15);  // token row of the half
-          const int vl = acc_m(wm, i, lane, 0);                 // 4 consecutive vocab
-          const int slot = (vl >> 2) ^ hsw16(n);
-          *reinterpret_cast<f32x4_t*>(st + n * 256 + slot * 4) = acc.v[i][j];
-        }
-    }
+    stage_half<TS>(st, acc, h, wm, wn, lane);
     __syncthreads();
     // z at the teacher entries of this half, for C = sum_k p z (Eq. 2)
     auto rec = [&](uint32_t e) {
-      const int tl = (int)(e & 255u);
-      if ((tl >> 7) != h) return;
-      const int n = tl & 127, v = (int)((e >> 8) & 255u);
-      zhit[(int64_t)(n0 + tl) * K + (e >> 16)] =
-          st[n * 256 + ((((v >> 2) ^ hsw16(n)) << 2) | (v & 3))];
+      int tl, v;
+      if (!entry_cell<TS>(e, m0, n0, tl, v) || tl / HT != h) return;
+      zhit[(int64_t)(n0 + tl) * K + (e >> 16)] = *stage_cell<TS>(st, tl & (HT - 1), v);
     };
     if (tid < cnt) rec(fe);
     for (int q = kThreads + tid; q < cnt; q += kThreads) rec(hits[seg + hb + q]);
 
-    // 16 lanes per token row, lane lam holding columns 4 lam + 64 k + (0..3).
+    // 16 lanes per token row, lane lam holding columns 4 lam + 64 k + (0..3), k < NK.
     // The row's run of dZ'' is 2^(y - R) against the token's reference R; the
     // partials are (R, sum of 2^(y - R)) with the sum reduced within the 16
     // lanes (DPP). A run whose sum exceeds 2^kRefGap (so its values could
@@ -813,31 +877,31 @@ __global__ __launch_bounds__(kThreads, 1) void k_logits_dz(
 #pragma unroll
     for (int gq = 0; gq < 4; ++gq) {
       const int n = wave * 16 + 4 * gq + rho;  // token row of the half
-      const int t = n0 + 128 * h + n;
-      f32x4_t zr[4];
+      const int t = n0 + HT * h + n;
+      f32x4_t zr[NK];
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        zr[k] = *reinterpret_cast<const f32x4_t*>(st + n * 256 + (((lam + 16 * k) ^ hsw16(n)) << 2));
+      for (int k = 0; k < NK; ++k)
+        zr[k] = *reinterpret_cast<const f32x4_t*>(stage_cell<TS>(st, n, 4 * lam + 64 * k));
       // rows past the chunk use a finite reference (nothing of them is stored)
-      float ref = rs_r[128 * h + n];
-      f32x4_t G[4];
+      float ref = rs_r[HT * h + n];
+      f32x4_t g[NK];
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        G[k] = f32x4_t{fast_exp2(zr[k][0] * k2 - ref), fast_exp2(zr[k][1] * k2 - ref),
+      for (int k = 0; k < NK; ++k)
+        g[k] = f32x4_t{fast_exp2(zr[k][0] * k2 - ref), fast_exp2(zr[k][1] * k2 - ref),
                        fast_exp2(zr[k][2] * k2 - ref), fast_exp2(zr[k][3] * k2 - ref)};
       // the column mask only on the last vocabulary tile (a wave-uniform
       // branch instead of per-element selects on every tile)
       if (!full) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < NK; ++k) {
           const int c = m0 + 4 * lam + 64 * k;
-          G[k] = f32x4_t{c < V ? G[k][0] : 0.f, c + 1 < V ? G[k][1] : 0.f,
-                         c + 2 < V ? G[k][2] : 0.f, c + 3 < V ? G[k][3] : 0.f};
+          g[k] = f32x4_t{c < V ? g[k][0] : 0.f, c + 1 < V ? g[k][1] : 0.f,
+                         c + 2 < V ? g[k][2] : 0.f, c + 3 < V ? g[k][3] : 0.f};
         }
       }
       float sum = 0.f;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) sum += (G[k][0] + G[k][1]) + (G[k][2] + G[k][3]);
+      for (int k = 0; k < NK; ++k) sum += (g[k][0] + g[k][1]) + (g[k][2] + g[k][3]);
       sum = row16_sum(sum);
       const bool own = !(sum <= kRefGapScale);
       if (__builtin_amdgcn_ballot_w64(own) != 0ull) {
@@ -845,20 +909,20 @@ __global__ __launch_bounds__(kThreads, 1) void k_logits_dz(
         // every row so that the 16-lane reductions run on a full wave)
         float mx = -INFINITY;
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+        for (int k = 0; k < NK; ++k)
 #pragma unroll
           for (int e = 0; e < 4; ++e)
             if (full || m0 + 4 * lam + 64 * k + e < V) mx = fmaxf(mx, zr[k][e]);
         const float m = row16_max(mx) * k2;
         float s2 = 0.f;
-        f32x4_t G2[4];
+        f32x4_t g2[NK];
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+        for (int k = 0; k < NK; ++k)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             float ev = fast_exp2(zr[k][e] * k2 - m);
             if (!full && m0 + 4 * lam + 64 * k + e >= V) ev = 0.f;
-            G2[k][e] = ev;
+            g2[k][e] = ev;
             s2 += ev;
           }
         s2 = row16_sum(s2);
@@ -866,23 +930,23 @@ __global__ __launch_bounds__(kThreads, 1) void k_logits_dz(
           ref = m;
           sum = s2;
 #pragma unroll
-          for (int k = 0; k < 4; ++k) G[k] = G2[k];
+          for (int k = 0; k < NK; ++k) g[k] = g2[k];
         }
       }
       if (t < rows) {
         T* dst = dZ + (int64_t)t * ldz + m0 + 4 * lam;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < NK; ++k) {
           if constexpr (sizeof(T) == 2) {
-            const u32x2_t pk2 = {pack_bf16x2(G[k][0], G[k][1]), pack_bf16x2(G[k][2], G[k][3])};
+            const u32x2_t pk2 = {pack_bf16x2(g[k][0], g[k][1]), pack_bf16x2(g[k][2], g[k][3])};
             *reinterpret_cast<u32x2_t*>(dst + 64 * k) = pk2;
           } else {
-            *reinterpret_cast<f32x4_t*>(dst + 64 * k) = G[k];
+            *reinterpret_cast<f32x4_t*>(dst + 64 * k) = g[k];
           }
         }
         if (lam == 0) {
-          part_m[(int64_t)t * nVT + mt] = ref;
-          part_s[(int64_t)t * nVT + mt] = sum;
+          part_m[(int64_t)t * TM + mt] = ref;
+          part_s[(int64_t)t * TM + mt] = sum;
           if (own) rowFlag[t] = 1;
         }
       }
@@ -994,7 +1058,7 @@ __global__ void k_row_loss(const float* zhit, const float* p, int K, const float
 // row without a token (-1) only gets a row factor of 0 and a loss of 0.
 template <typename T>
 __global__ __launch_bounds__(256) void k_row_finish(
-    const float* __restrict__ part_m, const float* __restrict__ part_s, int nVT,
+    const float* __restrict__ part_m, const float* __restrict__ part_s, int nVT, int vt_shift,
     const int* __restrict__ rowFlag, T* dZ, int64_t ldz, const int32_t* __restrict__ tidx,
     const float* __restrict__ p, const float* __restrict__ zhit, int K, int V, float k2,
     const float* __restrict__ rowM, const float* __restrict__ rowH,
@@ -1060,7 +1124,7 @@ __global__ __launch_bounds__(256) void k_row_finish(
       // rare: runs stored against different references
       constexpr int VPT = 16 / (int)sizeof(T);
       for (int64_t c0 = (int64_t)lane * VPT; c0 < ldz; c0 += 64 * VPT) {
-        const float fr = fast_exp2(pm[c0 >> 8] - mx);
+        const float fr = fast_exp2(pm[c0 >> vt_shift] - mx);
         u32x4_t* q = reinterpret_cast<u32x4_t*>(row + c0);
         const u32x4_t v = *q;
         // built as a new vector (in-place element updates were miscompiled)
@@ -1128,8 +1192,8 @@ __global__ __launch_bounds__(kFinThreads) void k_finalize_loss(const float* part
 // split > 1 each split covers a K range and writes fp32 partials. With a
 // rowmap, dZ row t is grad_hidden row rowmap[t] (-1: none), and only the
 // first *nrow - nrow_base rows hold tokens (tiles past them are skipped).
-template <typename T>
-__global__ __launch_bounds__(kThreads, 1) void k_dh(const T* __restrict__ dZ, int64_t ldz,
+template <typename T, int TS>
+__global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dh(const T* __restrict__ dZ, int64_t ldz,
                                                     const T* __restrict__ W, int V, int rows,
                                                     int D, int TM, int TN, int ks_total,
                                                     int split, void* gH, int gh_f32,
@@ -1137,36 +1201,37 @@ __global__ __launch_bounds__(kThreads, 1) void k_dh(const T* __restrict__ dZ, in
                                                     const float* __restrict__ rowscale,
                                                     const int* __restrict__ rowmap,
                                                     const int* __restrict__ nrow, int nrow_base) {
-  __shared__ __attribute__((aligned(16))) char lds[kLdsA3];
+  typedef Geo<TS> G;
+  __shared__ __attribute__((aligned(16))) char lds[gemm_lds<TS>];
   const int tiles = TM * TN;
   const int sidx = blockIdx.x / tiles;
   int mt, nt;
-  tile_coords(blockIdx.x - sidx * tiles, TM, TN, 4, mt, nt);
-  const int m0 = mt * kTile, n0 = nt * kTile;
+  tile_coords(blockIdx.x - sidx * tiles, TM, TN, G::GM, mt, nt);
+  const int m0 = mt * TS, n0 = nt * TS;
   if (rowmap != nullptr && m0 >= __builtin_amdgcn_readfirstlane(*nrow) - nrow_base) return;
   const int eb = Elt<T>::bytes;
   const int lda = (int)(ldz * eb), ldb = D * eb;
   const int per = (ks_total + split - 1) / split;
   const int kb = sidx * per, ke = min(ks_total, kb + per);
-  AccTile acc;
-  const int mrows = min(kTile, rows - m0);
-  // the row factors of the tile's 256 rows, loaded before the main loop and
+  AccTile<TS> acc;
+  const int mrows = min(TS, rows - m0);
+  // the row factors of the tile's rows, loaded before the main loop and
   // kept in LDS for the epilogue: a load there would wait for every store
   // issued before it (loads and stores complete in order)
   const int tid = threadIdx.x;
   const float rsv =
-      (rowscale != nullptr && split == 1 && tid < kTile && m0 + tid < rows) ? rowscale[m0 + tid]
+      (rowscale != nullptr && split == 1 && tid < TS && m0 + tid < rows) ? rowscale[m0 + tid]
                                                                            : 1.f;
-  gemm_tile<T, KcOp, KmOp, 8, true, 3>(
+  gemm<T, TS, true>(
       KcOp{reinterpret_cast<const char*>(dZ + (int64_t)m0 * ldz), (uint32_t)(mrows * lda), lda},
                KmOp{reinterpret_cast<const char*>(W + n0),
                     (int64_t)V * ldb - (int64_t)n0 * eb, ldb},
                kb, ke, lds, acc);
   const int lane = tid & 63, wave = wave_id();
-  const int wm = wave >> 2, wn = wave & 3;
+  const int wm = G::wm(wave), wn = G::wn(wave);
   float* rsl = reinterpret_cast<float*>(lds);
-  int* rml = reinterpret_cast<int*>(lds) + kTile;
-  if (tid < kTile) {
+  int* rml = reinterpret_cast<int*>(lds) + TS;
+  if (tid < TS) {
     rsl[tid] = rsv;
     // the output row of each of the tile's rows (loaded here: nothing of the
     // unmasked call is kept live through the main loop for it)
@@ -1174,16 +1239,16 @@ __global__ __launch_bounds__(kThreads, 1) void k_dh(const T* __restrict__ dZ, in
   }
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const f32x4_t sc = *reinterpret_cast<const f32x4_t*>(rsl + acc_m(wm, i, lane, 0));
-    const i32x4_t om = *reinterpret_cast<const i32x4_t*>(rml + acc_m(wm, i, lane, 0));
+  for (int i = 0; i < G::NI; ++i) {
+    const f32x4_t sc = *reinterpret_cast<const f32x4_t*>(rsl + G::acc_m(wm, i, lane, 0));
+    const i32x4_t om = *reinterpret_cast<const i32x4_t*>(rml + G::acc_m(wm, i, lane, 0));
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int d = n0 + acc_n(wn, j, lane);
+      const int d = n0 + G::acc_n(wn, j, lane);
       if (d >= D) continue;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int t = m0 + acc_m(wm, i, lane, r);
+        const int t = m0 + G::acc_m(wm, i, lane, r);
         if (t < rows) {
           if (split == 1) {
             const float v = acc.v[i][j][r] * sc[r];
@@ -1291,14 +1356,16 @@ __global__ __launch_bounds__(256) void k_transpose_rows(const T* __restrict__ H,
 // With nrow (ignored tokens left out), only the group's first *nrow dZ rows
 // hold tokens: the K range stops there, and the dZ rows past it read as
 // zeros.
-template <typename T, bool SPLIT>
-__global__ __launch_bounds__(kThreads, 1) void k_dw(const T* __restrict__ Ht, int ldt,
+template <typename T, int TS, bool SPLIT>
+__global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dw(const T* __restrict__ Ht, int ldt,
                                                     const T* __restrict__ dZ, int64_t ldz,
                                                     int tokens, int V, int D, int TM, int TN,
                                                     int beta, float* __restrict__ gW, int nfull,
                                                     int split, float* __restrict__ partial,
                                                     const int* __restrict__ nrow) {
-  __shared__ __attribute__((aligned(16))) char lds[kLdsA3];
+  typedef Geo<TS> G;
+  constexpr int NI = G::NI;
+  __shared__ __attribute__((aligned(16))) char lds[gemm_lds<TS>];
   constexpr int KS = kRowB / (int)sizeof(T);
   if (nrow != nullptr) tokens = min(tokens, __builtin_amdgcn_readfirstlane(*nrow));
   const int nks = min(ldt / KS, (tokens + KS - 1) / KS);
@@ -1316,35 +1383,35 @@ __global__ __launch_bounds__(kThreads, 1) void k_dw(const T* __restrict__ Ht, in
     ks1 = (int)((int64_t)nks * (s + 1) / split);
   }
   int mt, nt;
-  tile_at(L, TM, TN, 4, mt, nt);
-  const int m0 = mt * kTile, n0 = nt * kTile;  // m: feature d, n: vocabulary v
+  tile_at(L, TM, TN, G::GM, mt, nt);
+  const int m0 = mt * TS, n0 = nt * TS;  // m: feature d, n: vocabulary v
   const int eb = Elt<T>::bytes;
   const int lda = ldt * eb, ldb = (int)(ldz * eb);
-  const int mrows = min(kTile, D - m0);
-  AccTile acc;
-  gemm_tile<T, KcOp, KmOp, 8, true, 3>(
+  const int mrows = min(TS, D - m0);
+  AccTile<TS> acc;
+  gemm<T, TS, true>(
       KcOp{reinterpret_cast<const char*>(Ht + (int64_t)m0 * ldt), (uint32_t)(mrows * lda), lda},
       KmOp{reinterpret_cast<const char*>(dZ + n0), (int64_t)tokens * ldb - (int64_t)n0 * eb, ldb},
       ks0, ks1, lds, acc);
   const int lane = threadIdx.x & 63, wave = wave_id();
-  const int wm = wave >> 2, wn = wave & 3;
-  // the tile's rows of grad_W (or of its partial slot, pitch 256) as one
+  const int wm = G::wm(wave), wn = G::wn(wave);
+  // the tile's rows of grad_W (or of its partial slot, pitch TS) as one
   // resource: rows past V are out of range (loads give 0, stores are
   // dropped), features past D get an out-of-range offset
   const bool part = SPLIT && slot >= 0;
-  const int pitch = part ? kTile : D;
-  const int vrows = __builtin_amdgcn_readfirstlane(part ? kTile : min(kTile, V - n0));
+  const int pitch = part ? TS : D;
+  const int vrows = __builtin_amdgcn_readfirstlane(part ? TS : min(TS, V - n0));
   const __amdgpu_buffer_rsrc_t ro =
-      part ? make_rsrc(partial + (int64_t)slot * kTile * kTile, (uint32_t)kTile * kTile * 4u)
+      part ? make_rsrc(partial + (int64_t)slot * TS * TS, (uint32_t)TS * TS * 4u)
            : make_rsrc(gW + (int64_t)n0 * D, (uint32_t)vrows * (uint32_t)D * 4u);
   // block (i, j) sits at byte offset obase + 64 i (16 features) + 64 pitch j
   // (16 rows): the per-lane part is one register, 64 i goes into the
   // instruction's immediate offset and 64 pitch j into its scalar offset. D
   // is a multiple of 64, so whether block i's features exist is the same for
   // the whole wave.
-  const int dw0 = (part ? 0 : m0) + wm * 128;
+  const int dw0 = (part ? 0 : m0) + wm * 16 * NI;
   const uint32_t obase =
-      ((uint32_t)acc_n(wn, 0, lane) * (uint32_t)pitch + (uint32_t)(dw0 + 4 * (lane >> 4))) * 4u;
+      ((uint32_t)G::acc_n(wn, 0, lane) * (uint32_t)pitch + (uint32_t)(dw0 + 4 * (lane >> 4))) * 4u;
   const uint32_t jstep = 64u * (uint32_t)pitch;
   auto ld = [&](int i, int j) {
     return __builtin_bit_cast(
@@ -1356,35 +1423,35 @@ __global__ __launch_bounds__(kThreads, 1) void k_dw(const T* __restrict__ Ht, in
   };
   auto live = [&](int i) { return part || dw0 + 16 * i < D; };
   if (beta && !part) {
-    f32x4_t old[4][4];
+    f32x4_t old[NI / 2][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NI / 2; ++i)
       if (live(i))
 #pragma unroll
         for (int j = 0; j < 4; ++j) old[i][j] = ld(i, j);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NI / 2; ++i)
       if (live(i))
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc.v[i][j] += old[i][j];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (live(4 + i))
+    for (int i = 0; i < NI / 2; ++i)
+      if (live(NI / 2 + i))
 #pragma unroll
-        for (int j = 0; j < 4; ++j) old[i][j] = ld(4 + i, j);
+        for (int j = 0; j < 4; ++j) old[i][j] = ld(NI / 2 + i, j);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NI / 2; ++i)
       if (live(i))
 #pragma unroll
         for (int j = 0; j < 4; ++j) st(i, j, acc.v[i][j]);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (live(4 + i))
+    for (int i = 0; i < NI / 2; ++i)
+      if (live(NI / 2 + i))
 #pragma unroll
-        for (int j = 0; j < 4; ++j) st(4 + i, j, acc.v[4 + i][j] + old[i][j]);
+        for (int j = 0; j < 4; ++j) st(NI / 2 + i, j, acc.v[NI / 2 + i][j] + old[i][j]);
   } else {
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < NI; ++i)
       if (live(i))
 #pragma unroll
         for (int j = 0; j < 4; ++j) st(i, j, acc.v[i][j]);
@@ -1393,22 +1460,23 @@ __global__ __launch_bounds__(kThreads, 1) void k_dw(const T* __restrict__ Ht, in
 
 // The split tail tiles of k_dw: grad_W = (beta ? grad_W : 0) + part 0 + part 1
 // + ... in this order. One thread per 4 features of a vocabulary row of a tail
-// tile (grid: tail tiles x 256 rows x 64 threads).
+// tile (grid: tail tiles x blocks of rows).
+template <int TS>
 __global__ __launch_bounds__(256) void k_dw_fixup(const float* __restrict__ partial, int split,
                                                   int nfull, int TM, int TN, int V, int D,
                                                   int beta, float* __restrict__ gW) {
   const int q = blockIdx.x;                      // tail tile
-  const int row = blockIdx.y * 4 + (threadIdx.x >> 6);
-  const int c4 = (threadIdx.x & 63) * 4;         // first of 4 features in the tile
+  constexpr int TPR = TS / 4;                    // threads per row
+  const int row = blockIdx.y * (256 / TPR) + threadIdx.x / TPR;
+  const int c4 = (threadIdx.x % TPR) * 4;        // first of 4 features in the tile
   int mt, nt;
-  tile_at(nfull + q, TM, TN, 4, mt, nt);
-  const int v = nt * kTile + row, d = mt * kTile + c4;
+  tile_at(nfull + q, TM, TN, Geo<TS>::GM, mt, nt);
+  const int v = nt * TS + row, d = mt * TS + c4;
   if (v >= V || d >= D) return;
   f32x4_t sum = beta ? *reinterpret_cast<const f32x4_t*>(gW + (int64_t)v * D + d)
                      : f32x4_t{0.f, 0.f, 0.f, 0.f};
   for (int s = 0; s < split; ++s)
-    sum += *reinterpret_cast<const f32x4_t*>(partial + ((int64_t)(q * split + s) * kTile + row) *
-                                                           kTile + c4);
+    sum += *reinterpret_cast<const f32x4_t*>(partial + ((int64_t)(q * split + s) * TS + row) * TS + c4);
   *reinterpret_cast<f32x4_t*>(gW + (int64_t)v * D + d) = sum;
 }
 
@@ -1640,7 +1708,11 @@ template <typename T>
 static int launch_chunk_impl(const KdChunkArgs& a, hipStream_t s) {
   const T* W = static_cast<const T*>(a.W);
   const T* Hc = static_cast<const T*>(a.Hc);
-  const int TMv = cdiv(a.V, kTile), TNt = cdiv(a.rows, kTile);
+  constexpr int TS = kd_tile(sizeof(T));
+  constexpr int kThreads = Geo<TS>::kThreads;
+  // vocabulary tiles up to the padded width: every column of dZ is written
+  const int TMv = a.nVT * (kTile / TS), TNt = cdiv(a.rows, TS);
+  const int nbt = cdiv(a.rows, kTile);  // 256-token tiles of the buckets
   const float k2 = kLog2e * a.inv_tau;
   const double gemm_flops = 2.0 * (double)a.rows * (double)a.D * (double)a.V;
 
@@ -1658,7 +1730,7 @@ static int launch_chunk_impl(const KdChunkArgs& a, hipStream_t s) {
     }
     {
       ProfScope ps_(P_BUCKET, 0.0, s);
-      hipLaunchKernelGGL(k_bucket, dim3(TNt), dim3(kBucketThreads), 0, s, a.tidx, a.p, a.rows,
+      hipLaunchKernelGGL(k_bucket, dim3(nbt), dim3(kBucketThreads), 0, s, a.tidx, a.p, a.rows,
                          a.K, (int)a.V, a.nVT, a.hits, a.hitp, a.hoff, a.zhit);
     }
     if (a.one_projection) {
@@ -1675,7 +1747,7 @@ static int launch_chunk_impl(const KdChunkArgs& a, hipStream_t s) {
     // factors, the fallback rows, the teacher cells and the row losses
     {
       ProfScope ps_(P_LOGITS_DZ, gemm_flops, s);
-      hipLaunchKernelGGL(k_logits_dz<T>, dim3(TMv * TNt), dim3(kThreads), 0, s, W, Hc, (int)a.D,
+      hipLaunchKernelGGL((k_logits_dz<T, TS>), dim3(TMv * TNt), dim3(kThreads), 0, s, W, Hc, (int)a.D,
                          (int)a.V, a.rows, TMv, TNt, k2, a.part_m, a.part_s, a.nVT, a.hits,
                          a.hoff, a.K, static_cast<T*>(a.dZ), a.ldz, a.zhit, a.rowR, a.rowFlag,
                          a.nrow, a.nrow_base);
@@ -1683,7 +1755,8 @@ static int launch_chunk_impl(const KdChunkArgs& a, hipStream_t s) {
     {
       ProfScope ps_(P_ROW_FINISH, 0.0, s);
       hipLaunchKernelGGL(k_row_finish<T>, dim3(cdiv(a.rows, kLossRows)), dim3(64 * kLossRows), 0,
-                         s, a.part_m, a.part_s, a.nVT, a.rowFlag, static_cast<T*>(a.dZ), a.ldz,
+                         s, a.part_m, a.part_s, TMv, TS == 256 ? 8 : 7, a.rowFlag,
+                         static_cast<T*>(a.dZ), a.ldz,
                          a.tidx, a.p, a.zhit, a.K, (int)a.V, k2, a.rowM, a.rowH, a.rowCoef,
                          a.rowCoefM, a.ignore, a.row0, a.rowmap, a.rows, a.inv_tau, a.rowL2,
                          a.rowFactor, a.loss_per_token, a.block_partial);
@@ -1694,21 +1767,21 @@ static int launch_chunk_impl(const KdChunkArgs& a, hipStream_t s) {
         ProfScope ps_(P_LOGITS, gemm_flops, s);
         // no recompute follows (forward only, or a fused call that wants no
         // gradients): z at the teacher entries comes from this GEMM
-        hipLaunchKernelGGL(k_logits_lse<T>, dim3(TMv * TNt), dim3(kThreads), 0, s, W, Hc,
+        hipLaunchKernelGGL((k_logits_lse<T, TS>), dim3(TMv * TNt), dim3(kThreads), 0, s, W, Hc,
                            (int)a.D, (int)a.V, a.rows, TMv, TNt, k2, a.part_m, a.part_s, a.nVT,
                            a.hits, a.hoff, a.K, a.zhit, a.nrow, a.nrow_base);
       }
       {
         ProfScope ps_(P_MERGE, 0.0, s);
         hipLaunchKernelGGL(k_lse_merge, dim3(cdiv(a.rows, 4)), dim3(256), 0, s, a.part_m,
-                           a.part_s, a.rows, a.nVT, a.rowL2, a.rowmap);
+                           a.part_s, a.rows, TMv, a.rowL2, a.rowmap);
       }
     }
     if (bwd && !fwd) {
       // the backward of the split entry points: the logit recompute from the
       // saved log Z (Algorithm 1's backward)
       ProfScope ps_(P_DZ, gemm_flops, s);
-      hipLaunchKernelGGL(k_dz<T>, dim3(TMv * TNt), dim3(kThreads), 0, s, W, Hc, (int)a.D,
+      hipLaunchKernelGGL((k_dz<T, TS>), dim3(TMv * TNt), dim3(kThreads), 0, s, W, Hc, (int)a.D,
                          (int)a.V, a.rows, TMv, TNt, k2, a.rowL2, a.rowCoef, a.rowCoefM, a.hits,
                          a.hitp, a.hoff, a.K, a.nVT, static_cast<T*>(a.dZ), a.ldz,
                          (float*)nullptr, a.nrow, a.nrow_base);
@@ -1731,11 +1804,12 @@ extern "C" int kd_launch_chunk(const KdChunkArgs* a, void* stream) {
 template <typename T>
 static int launch_dh_impl(const KdDhArgs& a, hipStream_t s) {
   const int rows = (int)a.tokens;
-  const int TM = cdiv(rows, kTile), TN = cdiv(a.D, kTile);
+  constexpr int TS = kd_tile(sizeof(T));
+  const int TM = cdiv(rows, TS), TN = cdiv(a.D, TS);
   const int ks = (int)(a.ldz * sizeof(T) / kRowB);
   {
     ProfScope ps_(P_DH, 2.0 * (double)a.tokens * (double)a.D * (double)a.V, s);
-    hipLaunchKernelGGL(k_dh<T>, dim3(TM * TN * a.split), dim3(kThreads), 0, s,
+    hipLaunchKernelGGL((k_dh<T, TS>), dim3(TM * TN * a.split), dim3(Geo<TS>::kThreads), 0, s,
                        static_cast<const T*>(a.dZ), a.ldz, static_cast<const T*>(a.W), (int)a.V,
                        rows, (int)a.D, TM, TN, ks, a.split, a.gH, a.gh_f32, a.partial,
                        a.rowscale, a.rowmap, a.nrow, a.nrow_base);
@@ -1764,34 +1838,36 @@ static int launch_dw_impl(const KdDwArgs& a, hipStream_t s) {
                        static_cast<const T*>(a.Hg), (int)a.tokens, (int)a.D, Ht, ldt,
                        a.rowscale, a.rowmap);
   }
-  const int TM = cdiv(a.D, kTile), TN = cdiv(a.V, kTile);
+  constexpr int TS = kd_tile(sizeof(T)), units = kd_units(sizeof(T));
+  constexpr int kThreads = Geo<TS>::kThreads;
+  const int TM = cdiv(a.D, TS), TN = cdiv(a.V, TS);
   const int tiles = TM * TN;
   // a partly filled last round of the 256 compute units is split along the
   // tokens when the host provides the partial tiles' workspace
   int nfull = tiles, split = 1;
   const int nks = ldt * (int)sizeof(T) / kRowB;
-  if (a.partial != nullptr && tiles > kDwUnits && tiles % kDwUnits != 0) {
-    const int tail = tiles % kDwUnits;
-    split = std::min(kDwMaxSplit, std::min(kDwUnits / tail, nks));
+  if (a.partial != nullptr && tiles > units && tiles % units != 0) {
+    const int tail = tiles % units;
+    split = std::min(kDwMaxSplit, std::min(units / tail, nks));
     if (split >= 2) nfull = tiles - tail;
     else split = 1;
   }
   {
     ProfScope ps_(P_DW, 2.0 * (double)a.tokens * (double)a.D * (double)a.V, s);
     if (nfull < tiles)
-      hipLaunchKernelGGL((k_dw<T, true>), dim3(nfull + (tiles - nfull) * split), dim3(kThreads),
+      hipLaunchKernelGGL((k_dw<T, TS, true>), dim3(nfull + (tiles - nfull) * split), dim3(kThreads),
                          0, s, static_cast<const T*>(Ht), ldt, static_cast<const T*>(a.dZ), a.ldz,
                          (int)a.tokens, (int)a.V, (int)a.D, TM, TN, a.beta, a.gW, nfull, split,
                          a.partial, a.nrow);
     else
-      hipLaunchKernelGGL((k_dw<T, false>), dim3(tiles), dim3(kThreads), 0, s,
+      hipLaunchKernelGGL((k_dw<T, TS, false>), dim3(tiles), dim3(kThreads), 0, s,
                          static_cast<const T*>(Ht), ldt, static_cast<const T*>(a.dZ), a.ldz,
                          (int)a.tokens, (int)a.V, (int)a.D, TM, TN, a.beta, a.gW, tiles, 1,
                          (float*)nullptr, a.nrow);
   }
   if (nfull < tiles) {
     ProfScope ps_(P_DW_FIXUP, 0.0, s);
-    hipLaunchKernelGGL(k_dw_fixup, dim3(tiles - nfull, kTile / 4), dim3(256), 0, s, a.partial,
+    hipLaunchKernelGGL(k_dw_fixup<TS>, dim3(tiles - nfull, TS * TS / 1024), dim3(256), 0, s, a.partial,
                        split, nfull, TM, TN, (int)a.V, (int)a.D, a.beta, a.gW);
   }
   return (int)hipGetLastError();

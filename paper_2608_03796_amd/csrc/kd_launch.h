@@ -65,7 +65,7 @@ struct KdChunkArgs {
   int* rowFlag;             // [rows] a tile fell back to its own max
   float* rowFactor;         // [rows] factor of the row's stored gradient (this
                             // chunk's rows of the group's factor array)
-  float *part_m, *part_s;                            // [rows, nVT]
+  float *part_m, *part_s;   // [rows, vocabulary tiles of the contraction]
   int nVT;
   uint32_t* hits;           // [cdiv(rows, 256) * 256 * K] teacher entries by vocab tile
   float* hitp;              // their p
@@ -96,10 +96,14 @@ struct KdDhArgs {
   int nrow_base;
 };
 
-// dW tiles per full round (the compute units) and the largest split of the
-// tail tiles' token range; the partial tiles' workspace holds
-// kDwUnits * 256 * 256 floats (64 MiB)
-constexpr int kDwUnits = 256;
+// The contractions' tiles by element size: bf16 runs 256x256 tiles, one
+// workgroup per compute unit; fp32 (as split bf16) 128x128 tiles, two
+// workgroups per compute unit. kd_units = workgroups the chip runs at once.
+constexpr int kd_tile(size_t eb) { return eb == 2 ? 256 : 128; }
+constexpr int kd_units(size_t eb) { return eb == 2 ? 256 : 512; }
+
+// the largest split of the dW tail tiles' token range; the partial tiles'
+// workspace holds one tile per unit
 constexpr int kDwMaxSplit = 4;
 
 // dW GEMM over the chunks of one group: grad_W (+)= dZ[:tokens]^T H[:tokens]
