@@ -35,8 +35,7 @@ struct Plan {
   int64_t cp;          // c rounded up to the 256-row tile
   int64_t Vp;          // V rounded up to the 256-column tile
   int64_t nVT;         // 256-column vocabulary tiles
-  int64_t ts;          // the contractions' tile edge (256 bf16, 128 fp32)
-  int64_t units;       // their workgroups on the chip at once
+  int64_t nP;          // (reference, sum) partials per token: vocabulary tiles of the projection
   int64_t nchunks;
   int64_t nblk;        // loss partials of a full chunk (one per kLossRows rows)
   int64_t G;           // chunks whose dZ rows are gathered before one dH and one dW GEMM
@@ -45,7 +44,7 @@ struct Plan {
   bool dh_per_group;   // dH once per group (a chunk alone has too few tiles) or per chunk
   bool prep_per_group; // rows prepared once per group (chunks of whole 256-token tiles)
   int64_t ng;          // rows of the per-row arrays: the group's, or one chunk's (padded)
-  int64_t td, ksteps;  // dH column tiles and K steps (for its vocabulary split)
+  int64_t ksteps;      // K steps of dH (the vocabulary)
   size_t off_misc, off_p, off_tidx, off_rows, off_pm, off_ps, off_hits, off_hitp, off_hoff, off_zhit,
       off_lossp, off_dz, off_fac, off_ht, off_rowmap, off_dhs, off_dwp, total;
 };
@@ -80,6 +79,27 @@ int choose_dh_split(int64_t tiles, int64_t ksteps, int64_t units) {
   return best;
 }
 
+// Tile edge of each contraction over `n` token rows.
+int proj_tile(const Plan& pl, int64_t) { return pl.eb == 4 ? 128 : 256; }
+int dh_tile(const Plan& pl, int64_t) { return pl.eb == 4 ? 128 : 256; }
+int dw_tile(const Plan& pl, int64_t) { return pl.eb == 4 ? 128 : 256; }
+
+// Tiles and vocabulary split of dH over n rows.
+int64_t dh_tiles(const Plan& pl, int64_t n) {
+  const int ts = dh_tile(pl, n);
+  return cdiv(n, ts) * cdiv(pl.D, ts);
+}
+int dh_split(const Plan& pl, int64_t n) {
+  return choose_dh_split(dh_tiles(pl, n), pl.ksteps, kd_units(dh_tile(pl, n)));
+}
+// Bytes of dW's partial tiles over n tokens: its tiles leave the last round of
+// the compute units partly filled, so that round is split along the tokens.
+size_t dw_partial_bytes(const Plan& pl, int64_t n) {
+  const int ts = dw_tile(pl, n);
+  const int64_t units = kd_units(ts), tiles = cdiv(pl.D, ts) * cdiv(pl.V, ts);
+  return (tiles > units && tiles % units != 0) ? (size_t)(units * ts * ts) * 4 : 0;
+}
+
 // g_max > 0 caps the chunks per dW group (see plan_within).
 Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
   Plan pl{};
@@ -92,9 +112,6 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
   pl.cp = rup(pl.c, kTile);
   pl.Vp = rup(pl.V, kTile);
   pl.nVT = pl.Vp / kTile;
-  pl.ts = kd_tile(pl.eb);
-  pl.units = kd_units(pl.eb);
-  pl.td = cdiv(pl.D, pl.ts);
   pl.ksteps = pl.Vp * pl.eb / 128;
   pl.nchunks = cdiv(pl.N, pl.c);
   pl.nblk = cdiv(pl.c, kLossRows);
@@ -115,17 +132,16 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
   //    V = 131072 (whole rounds), unmerged and merged: chunk 256, 4096 tokens
   //    10.80 and 9.55 ms; 512, 8192 tokens 19.26 and 18.59 ms; 1024, 16384
   //    tokens 37.99 and 37.88 ms; 2048, 16384 tokens 37.61 and 37.84 ms. fp32,
-  //    256 tokens in chunks of 64: 488 and 250 us.
+  //    256 tokens in chunks of 64 (fp32 MFMAs in 256x256 tiles): 488 and 250 us.
   //  * A chunk whose tiles fill the chip is merged only when padding its last
   //    256-token tile costs more than merging (above 5% of its rows): each
   //    chunk's dH right after its own projection is faster than one dH over
   //    the group (chunk 4000, 2.4% padding: 36.72 unmerged, 37.42 ms merged).
   pl.merged = 1;
-  const int64_t dh_tiles = cdiv(pl.c, pl.ts) * pl.td;
-  const bool dh_grouped =
-      dh_tiles < pl.units || choose_dh_split(dh_tiles, pl.ksteps, pl.units) > 1;
+  const bool dh_grouped = dh_tiles(pl, pl.c) < kd_units(dh_tile(pl, pl.c)) || dh_split(pl, pl.c) > 1;
+  const int pts = proj_tile(pl, pl.c);
   const bool full_rounds = pl.c % kTile == 0 &&
-                           cdiv(pl.c, pl.ts) * (pl.Vp / pl.ts) % pl.units == 0 && pl.c >= 2048;
+                           cdiv(pl.c, pts) * (pl.Vp / pts) % kd_units(pts) == 0 && pl.c >= 2048;
   const bool padded = (rup(pl.c, kTile) - pl.c) * 20 > pl.c;
   if (pl.G > 1 && (padded || (dh_grouped && !full_rounds))) {
     pl.merged = pl.G;
@@ -144,7 +160,7 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
   // per tile), else once per chunk
   pl.prep_per_group = pl.G > 1 && pl.c % kTile == 0;
   pl.ng = pl.prep_per_group ? pl.G * pl.c : pl.cp;
-  pl.dh_per_group = choose_dh_split(cdiv(pl.c, pl.ts) * pl.td, pl.ksteps, pl.units) > 1;
+  pl.dh_per_group = dh_split(pl, pl.c) > 1;
   int64_t dh_rows[2];  // the row counts dH runs on: full and last chunk or group
   if (pl.dh_per_group) {
     dh_rows[0] = std::min<int64_t>(pl.G * pl.c, pl.N);
@@ -153,6 +169,11 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
     dh_rows[0] = pl.c;
     dh_rows[1] = pl.N - (pl.nchunks - 1) * pl.c;
   }
+  // rows of the last chunk and group, whose tiles may differ from the others'
+  const int64_t c_last = pl.N - (std::max<int64_t>(pl.nchunks, 1) - 1) * pl.c;
+  const int64_t g_full = std::min<int64_t>(pl.G * pl.c, pl.N);
+  const int64_t g_last = pl.N - (std::max<int64_t>(pl.ngroups, 1) - 1) * pl.G * pl.c;
+  pl.nP = pl.Vp / std::min(proj_tile(pl, pl.c), proj_tile(pl, c_last));
   size_t t = 0;
   auto take = [&](size_t bytes) {
     const size_t o = align256(t);
@@ -163,8 +184,8 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
   pl.off_p = take((size_t)pl.ng * pl.K * 4);
   pl.off_tidx = take((size_t)pl.ng * pl.K * 4);
   pl.off_rows = take((size_t)7 * pl.ng * 4);
-  pl.off_pm = take((size_t)pl.cp * (pl.Vp / pl.ts) * 4);
-  pl.off_ps = take((size_t)pl.cp * (pl.Vp / pl.ts) * 4);
+  pl.off_pm = take((size_t)pl.cp * pl.nP * 4);
+  pl.off_ps = take((size_t)pl.cp * pl.nP * 4);
   pl.off_hits = take((size_t)pl.ng * pl.K * 4);
   pl.off_hitp = take((size_t)pl.ng * pl.K * 4);
   pl.off_hoff = take((size_t)(pl.ng / kTile) * (pl.nVT + 1) * 4);
@@ -182,19 +203,14 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
     int64_t part = 0;
     for (int64_t r : dh_rows) {
       if (r <= 0) continue;
-      const int sp = choose_dh_split(cdiv(r, pl.ts) * pl.td, pl.ksteps, pl.units);
+      const int sp = dh_split(pl, r);
       if (sp > 1) part = std::max<int64_t>(part, sp * r);
     }
     pl.off_dhs = part > 0 ? take((size_t)part * pl.D * 4) : 0;
   }
-  // partial tiles of the dW contraction's split last round (when its tiles
-  // leave the last round of the compute units partly filled)
-  {
-    const int64_t tiles = pl.td * cdiv(pl.V, pl.ts);
-    pl.off_dwp = (tiles > pl.units && tiles % pl.units != 0)
-                     ? take((size_t)(pl.units * pl.ts * pl.ts) * 4)
-                     : 0;
-  }
+  // partial tiles of the dW contraction's split last round
+  const size_t dwp = std::max(dw_partial_bytes(pl, g_full), dw_partial_bytes(pl, g_last));
+  pl.off_dwp = dwp > 0 ? take(dwp) : 0;
   pl.total = align256(t);
   return pl;
 }
@@ -292,22 +308,17 @@ kd_status validate(const kd_problem* p, const Call& c, const Plan& pl, bool own_
 kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
   const bool fwd = c.mode != KD_MODE_BWD, bwd = c.mode != KD_MODE_FWD;
   char* ws = static_cast<char*>(c.ws);
-  int* nvalid = reinterpret_cast<int*>(ws + pl.off_misc);
-  float* inv_nvalid = reinterpret_cast<float*>(ws + pl.off_misc + 4);
+  // 1/N_valid: counted on the device with a mask, known here without
+  const bool compact = c.ignore != nullptr && pl.N > 0;
+  float* inv_nvalid = compact ? reinterpret_cast<float*>(ws + pl.off_misc + 4) : nullptr;
+  const float inv_n = pl.N > 0 ? 1.0f / (float)pl.N : 0.0f;
   float* lossp = reinterpret_cast<float*>(ws + pl.off_lossp);
   const bool want_dh = bwd && c.grad_hidden != nullptr && pl.N > 0;
   const bool want_dw = bwd && c.grad_W != nullptr && pl.N > 0;
 
-  KdPrepareArgs pa{};
-  pa.dtype = p->dtype;
-  pa.N = pl.N;
-  pa.D = pl.D;
-  pa.V = pl.V;
-  pa.ignore = c.ignore;
-  pa.nvalid = nvalid;
-  pa.inv_nvalid = inv_nvalid;
-  pa.zero_gW = (bwd && c.grad_W != nullptr && pl.N == 0 && !c.accumulate) ? c.grad_W : nullptr;
-  if (kd_launch_prepare(&pa, c.stream) != 0) return KD_ERR_DEVICE;
+  if (bwd && c.grad_W != nullptr && pl.N == 0 && !c.accumulate &&
+      kd_launch_fill(c.grad_W, pl.V * pl.D, c.stream) != 0)
+    return KD_ERR_DEVICE;
 
   float* rows = reinterpret_cast<float*>(ws + pl.off_rows);
   float* fac = reinterpret_cast<float*>(ws + pl.off_fac);
@@ -319,7 +330,6 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
   // first, and the group's rows are those tokens in order, then rows without
   // a token, whose tiles the contractions skip (their count is on the
   // device).
-  const bool compact = c.ignore != nullptr && pl.N > 0;
   int* rowmap = reinterpret_cast<int*>(ws + pl.off_rowmap);
   int* gnrow = reinterpret_cast<int*>(ws + pl.off_misc + 16);
   char* hcomp = ws + pl.off_ht;
@@ -354,6 +364,10 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
     a.tlogit = c.tlogit;
     a.ignore = c.ignore;
     a.inv_nvalid = inv_nvalid;
+    a.inv_n = inv_n;
+    a.grad_hidden = want_dh ? c.grad_hidden : nullptr;
+    a.gh_f32 = (p->flags & KD_FLAG_GRAD_HIDDEN_F32) ? 1 : 0;
+    a.lpt_full = c.lpt;
     a.rowmap = compact ? rowmap + g : nullptr;
     a.nrow = compact ? gnrow : nullptr;
     a.nrow_base = (int)g;
@@ -380,19 +394,13 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
     const int64_t slot = ci % pl.G;
     if (compact && slot == 0) {
       KdCompactArgs k{};
-      k.dtype = p->dtype;
-      k.D = pl.D;
       k.ignore = c.ignore;
+      k.N = pl.N;
       k.row0 = row0;
       k.rows = (int)std::min<int64_t>(pl.G * pl.c, pl.N - row0);
-      k.hidden = c.hidden;
-      k.hcomp = hcomp;
       k.rowmap = rowmap;
       k.nrow = gnrow;
-      k.grad_hidden = want_dh ? c.grad_hidden : nullptr;
-      k.gh_f32 = (p->flags & KD_FLAG_GRAD_HIDDEN_F32) ? 1 : 0;
-      k.loss_per_token = c.lpt;
-      k.logz_out = c.logz_out;
+      k.inv_nvalid = ci == 0 ? inv_nvalid : nullptr;
       if (kd_launch_compact(&k, c.stream) != 0) return KD_ERR_DEVICE;
     }
     if (pl.prep_per_group && slot == 0) {
@@ -411,7 +419,12 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
     if (kd_launch_chunk(&a, c.stream) != 0) return KD_ERR_DEVICE;
     n_partials += cdiv(rcount, kLossRows);
     group_tokens += rcount;
+    KdTailArgs tail{};
+    tail.dtype = p->dtype;
+    tail.D = pl.D;
     // dH over rows [r0, r0 + n) of the dZ buffer (from its row `zrow`)
+    // (a split dH's parts are added up by the group's tail: only the last
+    // launch of a group can be split)
     auto dh = [&](int64_t r0, int64_t n, int64_t zrow) -> bool {
       KdDhArgs h{};
       h.dtype = p->dtype;
@@ -421,7 +434,7 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
       h.ldz = pl.Vp;
       h.W = c.W;
       h.tokens = n;
-      h.split = choose_dh_split(cdiv(n, pl.ts) * pl.td, pl.ksteps, pl.units);
+      h.split = dh_split(pl, n);
       h.partial = h.split > 1 ? reinterpret_cast<float*>(ws + pl.off_dhs) : nullptr;
       h.gh_f32 = (p->flags & KD_FLAG_GRAD_HIDDEN_F32) ? 1 : 0;
       h.gH = compact ? c.grad_hidden
@@ -430,13 +443,36 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
       h.rowmap = compact ? rowmap + zrow : nullptr;
       h.nrow = compact ? gnrow : nullptr;
       h.nrow_base = (int)zrow;
+      tail.partial = h.partial;
+      tail.split = h.split;
+      tail.dh_rows = n;
+      tail.dh_rowscale = h.rowscale;
+      tail.dh_rowmap = h.rowmap;
+      tail.gH = h.gH;
+      tail.gh_f32 = h.gh_f32;
       return kd_launch_dh(&h, c.stream) == 0;
     };
     if (want_dh && !pl.dh_per_group && !dh(row0, rcount, slot * pl.c)) return KD_ERR_DEVICE;
-    if (!(want_dh || want_dw) || !(slot == pl.G - 1 || ci == pl.nchunks - 1)) continue;
+    const bool last = ci == pl.nchunks - 1;
+    if (last && fwd) {
+      tail.block_partial = lossp;
+      tail.n_partials = (int)n_partials;
+      tail.inv_nvalid = inv_nvalid;
+      tail.inv_n = inv_n;
+      tail.loss = c.loss;
+    }
+    if (!last && (!(want_dh || want_dw) || slot != pl.G - 1)) continue;
     // the group's dH (when it runs per group) and dW over the G chunks' dZ rows
     const int64_t row_first = row0 + rcount - group_tokens;
     if (want_dh && pl.dh_per_group && !dh(row_first, group_tokens, 0)) return KD_ERR_DEVICE;
+    if (want_dw) {
+      tail.Hg = compact ? c.hidden : static_cast<const char*>(c.hidden) + row_first * pl.D * pl.eb;
+      tail.tokens = group_tokens;
+      tail.Ht = ws + pl.off_ht;
+      tail.rowscale = scaled ? fac : nullptr;
+      tail.rowmap = compact ? rowmap : nullptr;
+    }
+    if (kd_launch_tail(&tail, c.stream) != 0) return KD_ERR_DEVICE;
     if (want_dw) {
       KdDwArgs d{};
       d.dtype = p->dtype;
@@ -444,22 +480,23 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
       d.V = pl.V;
       d.dZ = ws + pl.off_dz;
       d.ldz = pl.Vp;
-      d.Hg = compact ? c.hidden : static_cast<const char*>(c.hidden) + row_first * pl.D * pl.eb;
       d.tokens = group_tokens;
       d.Ht = ws + pl.off_ht;
       d.beta = (dw_done || c.accumulate) ? 1 : 0;
       d.gW = c.grad_W;
-      d.rowscale = scaled ? fac : nullptr;
       d.partial = pl.off_dwp ? reinterpret_cast<float*>(ws + pl.off_dwp) : nullptr;
-      d.rowmap = compact ? rowmap : nullptr;
       d.nrow = compact ? gnrow : nullptr;
       if (kd_launch_dw(&d, c.stream) != 0) return KD_ERR_DEVICE;
       dw_done = true;
     }
     group_tokens = 0;
   }
-  if (fwd && kd_launch_finalize(lossp, (int)n_partials, inv_nvalid, c.loss, c.stream) != 0)
-    return KD_ERR_DEVICE;
+  if (fwd && pl.nchunks == 0) {
+    KdTailArgs tail{};
+    tail.dtype = p->dtype;
+    tail.loss = c.loss;
+    if (kd_launch_tail(&tail, c.stream) != 0) return KD_ERR_DEVICE;
+  }
   return KD_OK;
 }
 

@@ -221,13 +221,13 @@ struct DmaStep {
   __device__ __forceinline__ void one(int i) const { dma_b128(r, la + i * 1024, off[i]); }
 };
 
-// An operand's 32 KiB stage is 32 instructions of 1 KiB; wave w issues
-// instructions w*NPW .. w*NPW + NPW - 1.
-template <typename T, typename Op, int NPW>
+// An operand's stage (TS rows of 128 bytes) is TS/8 instructions of 1 KiB; wave
+// w issues instructions w*NPW .. w*NPW + NPW - 1.
+template <typename T, typename Op, int NPW, int TS>
 struct OpDma;
 
-template <typename T, int NPW>
-struct OpDma<T, KcOp, NPW> {
+template <typename T, int NPW, int TS>
+struct OpDma<T, KcOp, NPW, TS> {
   uint32_t voff[NPW];
   i32x4_t r;
   __device__ __forceinline__ void init(const KcOp& op, int wave, int lane) {
@@ -251,16 +251,18 @@ struct OpDma<T, KcOp, NPW> {
   }
 };
 
-template <typename T, int NPW>
-struct OpDma<T, KmOp, NPW> {
+template <typename T, int NPW, int TS>
+struct OpDma<T, KmOp, NPW, TS> {
   static constexpr int KS = kRowB / (int)sizeof(T);  // K rows per step
   uint32_t voff[NPW];
   __device__ __forceinline__ void init(const KmOp& op, int wave, int lane) {
 #pragma unroll
     for (int i = 0; i < NPW; ++i) {
-      // 2 K rows of 512 bytes per instruction: lane -> row 2q + lane/32, slot lane%32
-      const int row = (wave * NPW + i) * 2 + (lane >> 5);
-      voff[i] = (uint32_t)row * (uint32_t)op.ld + (uint32_t)(((lane & 31) ^ swz_km16(row)) << 4);
+      // 512 / TS K rows of 2 TS bytes (TS / 8 slots) per instruction; TS = 256:
+      // lane -> row 2q + lane/32, slot lane%32
+      constexpr int SL = TS / 8;
+      const int row = (wave * NPW + i) * (64 / SL) + lane / SL;
+      voff[i] = (uint32_t)row * (uint32_t)op.ld + (uint32_t)(((lane % SL) ^ swz_km16(row)) << 4);
     }
   }
   __device__ __forceinline__ DmaStep<NPW> prep(const KmOp& op, char* stage, int wave, int ks,
@@ -281,11 +283,11 @@ struct OpDma<T, KmOp, NPW> {
 // Sub-step s of a K step covers K elements [s*KS/2, (s+1)*KS/2) of the step;
 // lane (g = lane/16, j = lane%16) holds row base + 16b + j with K elements
 // s*KS/2 + 8g + 0..7, in both layouts.
-template <typename T, typename Op, int NB>
+template <typename T, typename Op, int NB, int TS>
 struct OpFrag;
 
-template <typename T, int NB>
-struct OpFrag<T, KcOp, NB> {
+template <typename T, int NB, int TS>
+struct OpFrag<T, KcOp, NB, TS> {
   static constexpr int kReads = NB;
   int rd[NB], fx[NB];
   __device__ __forceinline__ void init(int base, int lane) {
@@ -301,10 +303,10 @@ struct OpFrag<T, KcOp, NB> {
   }
 };
 
-template <int NB>
-struct OpFrag<__bf16, KmOp, NB> {
+template <int NB, int TS>
+struct OpFrag<__bf16, KmOp, NB, TS> {
   static constexpr int kReads = 2 * NB;
-  static constexpr int kRow = kTile * 2;  // bytes of a K row in LDS
+  static constexpr int kRow = TS * 2;     // bytes of a K row in LDS
   int off[NB];                            // byte offset at sub-step 0, h = 0
   __device__ __forceinline__ void init(int base, int lane) {
     // lane j of group g points at K row 8g + j/4 (+ 32s + 4h), columns
@@ -354,12 +356,12 @@ __device__ __forceinline__ void gemm_tile(const OA& opa, const OB& opb, int ks_b
     return;
   }
 
-  OpDma<T, OA, NPW> da;
-  OpDma<T, OB, NPW> db;
+  OpDma<T, OA, NPW, 256> da;
+  OpDma<T, OB, NPW, 256> db;
   da.init(opa, wave, lane);
   db.init(opb, wave, lane);
-  OpFrag<T, OA, 8> fra;
-  OpFrag<T, OB, NJ> frb;
+  OpFrag<T, OA, 8, 256> fra;
+  OpFrag<T, OB, NJ, 256> frb;
   fra.init(wm * 128, lane);
   frb.init(wn * 64, lane);
 

@@ -1,14 +1,14 @@
 // HIP kernels (gfx950) of the fused chunked top-K KL loss and their launchers.
 //
-// Per call:    count_valid
 // Per group of chunks, with a mask:
-//              compact_scan, compact_rows -> the group's tokens that are not
-//                                   ignored (row map, count, their hidden rows);
-//                                   the kernels below then skip the rows past them
-// Per chunk:   teacher_prologue  -> p, M, H, g/tau                 (§3.2, Eq. 2 terms)
+//              compact_scan      -> the group's tokens that are not ignored (row map,
+//                                   count); the kernels below skip the rows past
+//                                   them. The first one also counts N_valid.
+// Per chunk:   prologue          -> p, M, H, g/tau                 (§3.2, Eq. 2 terms),
+//                                   the row's hidden row copied next to the others'
+//                                   (with a mask), the reference logit R
 //              bucket            -> teacher entries grouped by vocabulary tile
 //   loss and gradients together (one projection per chunk):
-//              ref_logit         -> per-token reference logit R
 //              logits_dz         -> (reference, sum-exp) partials per (token, vocab
 //                                   tile), z at the teacher entries, dZ'' = 2^(y - R)
 //              row_finish        -> log Z, the row factor (g/tau) M 2^(R - log2 Z),
@@ -16,10 +16,16 @@
 //                                   l_t = H - C/tau + M log Z       (Eq. 2)
 //   forward only:  logits_lse (with z at the teacher entries), lse_merge, row_loss
 //   backward only: dz            -> recomputed logits, dZ = g/tau (M q - p)
-//              dh (+ split reduce): dH = dZ W (per chunk or per group; rows scaled
+//              dh                -> dH = dZ W (per chunk or per group; rows scaled
 //                                   by the factor in the one-projection schedule)
-// Per group of chunks: transpose_rows, dw -> grad_W (+)= dZ^T H (fp32 accumulate)
-// Per call:    finalize_loss     -> mean over non-ignored tokens
+// Per group of chunks: tail      -> dH's split parts added up, the hidden rows
+//                                   transposed, the loss (mean over non-ignored
+//                                   tokens) after the last chunk
+//              dw                -> grad_W (+)= dZ^T H (fp32 accumulate)
+//
+// A kernel of a few microseconds of work occupies the stream for about 4.7 us,
+// so the small passes share launches where nothing orders them: a step of one
+// group is 7 launches (8 with a mask), which were 11 (14).
 #include "kd_device.h"
 #include "kd_f32.h"
 #include <type_traits>
@@ -30,57 +36,25 @@
 namespace kd {
 
 // ------------------------------------------------------------------ small --
-// N_valid = tokens not ignored, and 1/N_valid (0 if none). One workgroup:
-// 4 mask bytes per load when the mask is 4-byte aligned.
-constexpr int kCountThreads = 1024;
-__global__ __launch_bounds__(kCountThreads) void k_count_valid(const uint8_t* ignore, int64_t N,
-                                                               int* nvalid, float* inv_nvalid) {
-  __shared__ int red[kCountThreads / 64];
-  const int tid = threadIdx.x;
-  int c = 0;
-  if (ignore == nullptr) {
-    c = tid == 0 ? (int)N : 0;
-  } else {
-    int64_t i0 = 0;
-    if (((uintptr_t)ignore & 3u) == 0u) {
-      const uint32_t* w = reinterpret_cast<const uint32_t*>(ignore);
-      const int64_t nw = N >> 2;
-      for (int64_t i = tid; i < nw; i += kCountThreads) {
-        const uint32_t v = w[i];
-        c += ((v & 0xffu) == 0u) + (((v >> 8) & 0xffu) == 0u) + (((v >> 16) & 0xffu) == 0u) +
-             ((v >> 24) == 0u);
-      }
-      i0 = nw << 2;
-    }
-    for (int64_t i = i0 + tid; i < N; i += kCountThreads) c += ignore[i] == 0 ? 1 : 0;
-  }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) c += __shfl_xor(c, o);
-  if ((tid & 63) == 0) red[tid >> 6] = c;
-  __syncthreads();
-  if (tid == 0) {
-    int n = 0;
-    for (int w = 0; w < kCountThreads / 64; ++w) n += red[w];
-    nvalid[0] = n;
-    inv_nvalid[0] = n > 0 ? 1.0f / (float)n : 0.0f;
-  }
-}
-
 __global__ void k_fill_f32(float* p, int64_t n, float v) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (; i < n; i += stride) p[i] = v;
 }
 
-// Teacher distribution over the K cached entries of each chunk row (§3.2):
+// Prepares each row, one wave per row.
+//
+// Teacher distribution over the K cached entries (§3.2):
 // p = softmax(teacher_logit / tau), or p = exp(value) as given for cached
 // log-probabilities (partial mass); M = sum p, H = sum p log p (0 log 0 = 0).
 // Row weight coef = g/tau, g = 1/N_valid times the upstream gradient of the
 // mean (gscale, default 1), or the upstream gradient of the token's own loss
 // (gtok); 0 for ignored rows. With a saved log-normaliser (backward only) the
-// row's log2 Z is set from it. One wave per row. With a rowmap, row r is
-// token rowmap[r], and a row without a token (-1) gets p = 0, index -1 and
-// weight 0.
+// row's log2 Z is set from it. With a rowmap, row r is token rowmap[r], whose
+// hidden row is copied to hcomp's row r; a row without a token (-1) gets
+// p = 0, index -1 and weight 0; and if token row0 + r is ignored, its
+// grad_hidden row, per-token loss and saved log Z are set to 0 (the rest of
+// the call never writes them).
 //
 // The support is a set; a row that repeats an index is read as the dense
 // teacher row that sums the repeated entries (scatter-add): the first
@@ -91,6 +65,15 @@ __global__ void k_fill_f32(float* p, int64_t n, float v) {
 // unchanged. Repeats are found with a hash set of the row's indices in LDS
 // (an insertion that meets its own index); only a wave in which some row
 // repeats an index compares the row's entries pairwise, in entry order.
+//
+// With rowR (one-projection schedule), the row's reference logit for
+// k_logits_dz: R = z log2(e)/tau at the teacher entry with the largest
+// teacher logit (a valid index), plus kRefShift; -inf when the row has no
+// valid index. The logit part never exceeds the row's max y beyond rounding,
+// so 2^(y - R) keeps every term that matters; a tile whose sum of 2^(y - R)
+// exceeds 2^kRefGap falls back to its own max. The row's fallback flag is
+// cleared.
+//
 // LDS hash set of the row's valid indices (power-of-two slots, at least K):
 // size in ints for K entries
 __host__ __device__ constexpr int prologue_hash_slots(int K) {
@@ -99,48 +82,108 @@ __host__ __device__ constexpr int prologue_hash_slots(int K) {
   return t;
 }
 
-__global__ __launch_bounds__(64) void k_teacher_prologue(
-    const int32_t* __restrict__ tidx, int32_t* __restrict__ tidx_out, const float* tlogit,
-    const uint8_t* ignore, int64_t row0, const int* __restrict__ rowmap, int rows, int K, int V,
-    float inv_tau, int logprobs, const float* inv_nvalid, const float* gscale, const float* gtok,
-    const float* logz_in, float* p_out, float* rowM, float* rowH, float* rowCoef,
-    float* rowCoefM, float* rowL2) {
+// largest exponent (base 2) of the sum of a tile row's stored provisional
+// gradients 2^(y - R), and so of each of them
+constexpr float kRefGap = 40.f;
+constexpr float kRefGapScale = 1099511627776.f;  // 2^kRefGap
+// R is the reference logit plus this many (base 2): stored values are then
+// smaller, which the dH and dW contractions run about 1% faster on (MFMA power
+// depends on the operands); terms below 2^-126 relative to R + kRefShift,
+// i.e. 2^-102 below the reference logit, flush to zero
+constexpr float kRefShift = 24.f;
+
+struct PrologueArgs {
+  const int32_t* tidx;
+  int32_t* tidx_out;
+  const float* tlogit;
+  const uint8_t* ignore;
+  int64_t row0;
+  const int* rowmap;
+  int rows, K, V, D;
+  float inv_tau;
+  int logprobs;
+  const float* inv_nvalid;  // device 1/N_valid, or null: inv_n
+  float inv_n;
+  const float *gscale, *gtok, *logz_in;
+  float *p_out, *rowM, *rowH, *rowCoef, *rowCoefM, *rowL2;
+  // one-projection schedule (rowR not null)
+  const void *hidden, *W;
+  float k2;
+  float* rowR;
+  int* rowFlag;
+  // with a rowmap
+  char* hcomp;
+  char* gH;
+  int64_t gh_row_bytes;
+  float *lpt, *logz_out;
+};
+
+template <typename T>
+__global__ __launch_bounds__(64) void k_prologue(PrologueArgs a) {
   extern __shared__ __attribute__((aligned(16))) char psm[];
-  const int T = prologue_hash_slots(K);
+  const int K = a.K, V = a.V;
+  const int S = prologue_hash_slots(K);
   int* hset = reinterpret_cast<int*>(psm);
-  int* sidx = hset + T;
+  int* sidx = hset + S;
   float* sp = reinterpret_cast<float*>(sidx + K);
   const int lane = threadIdx.x & 63;
   const int r = blockIdx.x;
-  if (r >= rows) return;
-  const int64_t t = rowmap != nullptr ? (int64_t)rowmap[r] : row0 + r;
+  if (r >= a.rows) return;
+  int64_t t = a.row0 + r;
+  if (a.rowmap != nullptr) {
+    if (a.ignore[t] != 0) {
+      if (a.gH != nullptr) {
+        u32x4_t* z = reinterpret_cast<u32x4_t*>(a.gH + t * a.gh_row_bytes);
+        for (int64_t q = lane; q < a.gh_row_bytes / 16; q += 64) z[q] = u32x4_t{0u, 0u, 0u, 0u};
+      }
+      if (lane == 0) {
+        if (a.lpt != nullptr) a.lpt[t] = 0.f;
+        if (a.logz_out != nullptr) a.logz_out[t] = 0.f;
+      }
+    }
+    t = a.rowmap[r];
+  }
+  float* p_out = a.p_out + (int64_t)r * K;
+  int32_t* tidx_out = a.tidx_out + (int64_t)r * K;
   if (t < 0) {
     for (int k = lane; k < K; k += 64) {
-      p_out[(int64_t)r * K + k] = 0.f;
-      tidx_out[(int64_t)r * K + k] = -1;
+      p_out[k] = 0.f;
+      tidx_out[k] = -1;
     }
     if (lane == 0) {
-      rowM[r] = 0.f;
-      rowH[r] = 0.f;
-      rowCoef[r] = 0.f;
-      rowCoefM[r] = 0.f;
-      if (logz_in != nullptr) rowL2[r] = 0.f;
+      a.rowM[r] = 0.f;
+      a.rowH[r] = 0.f;
+      a.rowCoef[r] = 0.f;
+      a.rowCoefM[r] = 0.f;
+      if (a.logz_in != nullptr) a.rowL2[r] = 0.f;
+      if (a.rowR != nullptr) {
+        a.rowR[r] = -INFINITY;
+        a.rowFlag[r] = 0;
+      }
     }
     return;
   }
-  const float* u = tlogit + t * (int64_t)K;
-  const int32_t* ix = tidx + t * (int64_t)K;
-  for (int i = lane; i < T; i += 64) hset[i] = -1;
+  constexpr int VPT = 16 / (int)sizeof(T);  // elements per 16-byte piece
+  const T* hrow = static_cast<const T*>(a.hidden) + t * a.D;
+  if (a.rowmap != nullptr) {
+    const u32x4_t* src = reinterpret_cast<const u32x4_t*>(hrow);
+    u32x4_t* dst = reinterpret_cast<u32x4_t*>(a.hcomp + (int64_t)r * a.D * sizeof(T));
+#pragma unroll 4
+    for (int q = lane; q < a.D / VPT; q += 64) dst[q] = src[q];
+  }
+  const float* u = a.tlogit + t * (int64_t)K;
+  const int32_t* ix = a.tidx + t * (int64_t)K;
+  for (int i = lane; i < S; i += 64) hset[i] = -1;
   float mx = 0.f, logs = 0.f, scale = 1.f;
-  if (!logprobs) {
+  if (!a.logprobs) {
     mx = -INFINITY;
-    for (int k = lane; k < K; k += 64) mx = fmaxf(mx, u[k] * inv_tau);
+    for (int k = lane; k < K; k += 64) mx = fmaxf(mx, u[k] * a.inv_tau);
     mx = wave_max(mx);
     float s = 0.f;
-    for (int k = lane; k < K; k += 64) s += expf(u[k] * inv_tau - mx);
+    for (int k = lane; k < K; k += 64) s += expf(u[k] * a.inv_tau - mx);
     s = wave_sum(s);
     logs = logf(s);
-    scale = inv_tau;
+    scale = a.inv_tau;
   }
   __syncthreads();  // the cleared hash set
   // p, and the row's indices into the hash set: an insertion that finds its
@@ -156,8 +199,8 @@ __global__ __launch_bounds__(64) void k_teacher_prologue(
     m += pk;
     if ((unsigned)v < (unsigned)V) {
       uint32_t h = ((uint32_t)v * 2654435761u) >> 7;
-      for (int probe = 0; probe < T; ++probe, ++h) {
-        const int prev = atomicCAS(&hset[h & (T - 1)], -1, v);
+      for (int probe = 0; probe < S; ++probe, ++h) {
+        const int prev = atomicCAS(&hset[h & (S - 1)], -1, v);
         if (prev == -1) break;
         if (prev == v) {
           seen = true;
@@ -169,6 +212,8 @@ __global__ __launch_bounds__(64) void k_teacher_prologue(
   const bool any_repeat = __builtin_amdgcn_ballot_w64(seen) != 0ull;
   __syncthreads();  // sidx and sp of the whole row
   float h = 0.f;
+  float best = -INFINITY;  // the valid entry with the largest teacher logit, the first of equals
+  int bk = K;
   for (int k = lane; k < K; k += 64) {
     const int v = sidx[k];
     const float pk = sp[k];
@@ -186,7 +231,8 @@ __global__ __launch_bounds__(64) void k_teacher_prologue(
         }
       }
     }
-    const float lp = u[k] * scale - mx - logs;
+    const float uk = u[k];
+    const float lp = uk * scale - mx - logs;
     float pe = pk, term = pk > 0.f ? pk * lp : 0.f;
     if (dup) {
       pe = 0.f;
@@ -195,21 +241,57 @@ __global__ __launch_bounds__(64) void k_teacher_prologue(
       pe = acc;
       term = acc > 0.f ? acc * logf(acc) : 0.f;
     }
-    p_out[(int64_t)r * K + k] = pe;
-    tidx_out[(int64_t)r * K + k] = dup ? -1 : v;
+    p_out[k] = pe;
+    tidx_out[k] = dup ? -1 : v;
     h += term;
+    if (!dup && (unsigned)v < (unsigned)V && (uk > best || (uk == best && k < bk))) {
+      best = uk;
+      bk = k;
+    }
   }
   m = wave_sum(m);
   h = wave_sum(h);
   if (lane == 0) {
-    const bool valid = ignore == nullptr || ignore[t] == 0;
-    const float g = gtok != nullptr ? gtok[t] : inv_nvalid[0] * (gscale != nullptr ? gscale[0] : 1.f);
-    const float coef = valid ? inv_tau * g : 0.f;
-    rowM[r] = m;
-    rowH[r] = h;
-    rowCoef[r] = coef;
-    rowCoefM[r] = coef * m;
-    if (logz_in != nullptr) rowL2[r] = logz_in[t] * kLog2e;
+    const bool valid = a.ignore == nullptr || a.ignore[t] == 0;
+    const float inv_n = a.inv_nvalid != nullptr ? a.inv_nvalid[0] : a.inv_n;
+    const float g =
+        a.gtok != nullptr ? a.gtok[t] : inv_n * (a.gscale != nullptr ? a.gscale[0] : 1.f);
+    const float coef = valid ? a.inv_tau * g : 0.f;
+    a.rowM[r] = m;
+    a.rowH[r] = h;
+    a.rowCoef[r] = coef;
+    a.rowCoefM[r] = coef * m;
+    if (a.logz_in != nullptr) a.rowL2[r] = a.logz_in[t] * kLog2e;
+  }
+  if (a.rowR == nullptr) return;
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const float ob = __shfl_xor(best, o);
+    const int ok = __shfl_xor(bk, o);
+    if (ob > best || (ob == best && ok < bk)) {
+      best = ob;
+      bk = ok;
+    }
+  }
+  float z = 0.f;
+  if (bk < K) {
+    // 16-byte pieces of both rows (D is a multiple of 64, rows 16-byte aligned)
+    const T* w = static_cast<const T*>(a.W) + (int64_t)sidx[bk] * a.D;
+#pragma unroll 4
+    for (int d = lane * VPT; d < a.D; d += 64 * VPT) {
+      const u32x4_t hv = *reinterpret_cast<const u32x4_t*>(hrow + d);
+      const u32x4_t wv = *reinterpret_cast<const u32x4_t*>(w + d);
+      T he[VPT], we[VPT];
+      __builtin_memcpy(he, &hv, 16);
+      __builtin_memcpy(we, &wv, 16);
+#pragma unroll
+      for (int x = 0; x < VPT; ++x) z += (float)he[x] * (float)we[x];
+    }
+    z = wave_sum(z);
+  }
+  if (lane == 0) {
+    a.rowR[r] = bk < K ? z * a.k2 + kRefShift : -INFINITY;
+    a.rowFlag[r] = 0;
   }
 }
 
@@ -223,7 +305,7 @@ __device__ __forceinline__ void gemm(const OA& a, const OB& b, int kb, int ke, c
   if constexpr (TS == 256) gemm_tile<T, OA, OB, SPREAD>(a, b, kb, ke, lds, acc);
   else gemm_f32<OA, OB>(a, b, kb, ke, lds, acc);
 }
-template <int TS>
+template <typename T, int TS>
 constexpr int gemm_lds = TS == 256 ? kLdsA3 : kLdsF32;
 
 // Epilogues of the projection kernels stage the fp32 tile in LDS half of its
@@ -295,7 +377,7 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_logits
                                                             const int* __restrict__ nrow,
                                                             int nrow_base) {
   typedef Geo<TS> G;
-  __shared__ __attribute__((aligned(16))) char lds[gemm_lds<TS>];
+  __shared__ __attribute__((aligned(16))) char lds[gemm_lds<T, TS>];
   int mt, nt;
   tile_coords(blockIdx.x, TM, TN, G::GM, mt, nt);
   const int m0 = mt * TS, n0 = nt * TS;
@@ -499,9 +581,18 @@ __global__ void k_lse_merge(const float* part_m, const float* part_s, int rows, 
 // tile's entries by vocabulary tile with a counting sort in LDS: segment nt of
 // `hits` (capacity 256 K) lists, for vocabulary tile b, the entries
 // [hoff[nt][b], hoff[nt][b+1]) as (token in tile | column in tile << 8 | k << 16)
-// with their teacher probability in `hitp`. An index outside [0, V) gets no
-// slot and a zero z (it contributes nothing to C or dZ).
+// with their teacher probability in `hitp` (when asked for: only the separate
+// backward reads it). An index outside [0, V) gets no slot and a zero z (it
+// contributes nothing to C or dZ).
+//
+// Latency-bound (one workgroup per 256 tokens). Up to kBucketRegs entries per
+// thread (K <= 128) stay in registers: all of a thread's loads are in flight
+// together, and the atomic that counts an entry also returns its place among
+// the entries of its vocabulary tile, so each entry is read once and takes one
+// atomic (512 tokens, K = 64, V = 32000: 22.5 us, now 12.2 us). More entries are
+// read twice, counted and then placed.
 constexpr int kBucketThreads = 1024;
+constexpr int kBucketRegs = 32;
 constexpr int kBucketBatch = 8;  // entries per thread whose loads are in flight together
 constexpr int kMaxVT = 4096;     // vocabulary tiles (V <= 2^20)
 
@@ -518,24 +609,56 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket(const int32_t* __rest
   const int64_t seg = (int64_t)blockIdx.x * kTile * K;
   // entry e of the tile is element t0 K + e of the row-major [rows, K] arrays
   const int32_t* ti = tidx + (int64_t)t0 * K;
+  const float* pt = p + (int64_t)t0 * K;
+  float* zt = zhit + (int64_t)t0 * K;
   const float invK = 1.0f / (float)K;
+  auto put = [&](int e, int v, int pos) {
+    // token = e / K (exact: e < 2^20, and (e + 0.5) / K stays >= 1/(2K)
+    // away from an integer while the float product errs by < 2^-12)
+    const int tl = (int)(((float)e + 0.5f) * invK);
+    const int k = e - tl * K;
+    hits[seg + pos] = (uint32_t)tl | ((uint32_t)(v & 255) << 8) | ((uint32_t)k << 16);
+    if (hitp != nullptr) hitp[seg + pos] = pt[e];
+  };
+  const bool in_regs = total <= kBucketThreads * kBucketRegs;
+  int v[kBucketRegs], rank[kBucketRegs];
+  if (in_regs) {
+#pragma unroll
+    for (int u = 0; u < kBucketRegs; ++u) {
+      const int e = u * kBucketThreads + tid;
+      v[u] = e < total ? ti[e] : -1;
+    }
+  }
   for (int b = tid; b < nVT; b += kBucketThreads) cnt[b] = 0;
   __syncthreads();
-  for (int base = 0; base < total; base += kBucketThreads * kBucketBatch) {
-    int v[kBucketBatch];
+  if (in_regs) {
 #pragma unroll
-    for (int u = 0; u < kBucketBatch; ++u) {
-      const int e = base + u * kBucketThreads + tid;
-      v[u] = e < total ? ti[e] : 0;
-    }
-#pragma unroll
-    for (int u = 0; u < kBucketBatch; ++u) {
-      const int e = base + u * kBucketThreads + tid;
-      if (e >= total) continue;
+    for (int u = 0; u < kBucketRegs; ++u) {
+      const int e = u * kBucketThreads + tid;
+      if (u * kBucketThreads >= total) break;
+      rank[u] = 0;
       if ((unsigned)v[u] < (unsigned)V)
-        atomicAdd(&cnt[v[u] >> 8], 1);
-      else
-        zhit[(int64_t)t0 * K + e] = 0.f;
+        rank[u] = atomicAdd(&cnt[v[u] >> 8], 1);
+      else if (e < total)
+        zt[e] = 0.f;
+    }
+  } else {
+    for (int base = 0; base < total; base += kBucketThreads * kBucketBatch) {
+      int w[kBucketBatch];
+#pragma unroll
+      for (int u = 0; u < kBucketBatch; ++u) {
+        const int e = base + u * kBucketThreads + tid;
+        w[u] = e < total ? ti[e] : 0;
+      }
+#pragma unroll
+      for (int u = 0; u < kBucketBatch; ++u) {
+        const int e = base + u * kBucketThreads + tid;
+        if (e >= total) continue;
+        if ((unsigned)w[u] < (unsigned)V)
+          atomicAdd(&cnt[w[u] >> 8], 1);
+        else
+          zt[e] = 0.f;
+      }
     }
   }
   __syncthreads();
@@ -567,26 +690,27 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket(const int32_t* __rest
   }
   if (tid == kBucketThreads - 1) ho[nVT] = off;
   __syncthreads();
+  if (in_regs) {
+#pragma unroll
+    for (int u = 0; u < kBucketRegs; ++u) {
+      if (u * kBucketThreads >= total) break;
+      if ((unsigned)v[u] < (unsigned)V)
+        put(u * kBucketThreads + tid, v[u], cur[v[u] >> 8] + rank[u]);
+    }
+    return;
+  }
   for (int base = 0; base < total; base += kBucketThreads * kBucketBatch) {
-    int v[kBucketBatch];
-    float pv[kBucketBatch];
+    int w[kBucketBatch];
 #pragma unroll
     for (int u = 0; u < kBucketBatch; ++u) {
       const int e = base + u * kBucketThreads + tid;
-      v[u] = e < total ? ti[e] : -1;
-      pv[u] = e < total ? p[(int64_t)t0 * K + e] : 0.f;
+      w[u] = e < total ? ti[e] : -1;
     }
 #pragma unroll
     for (int u = 0; u < kBucketBatch; ++u) {
       const int e = base + u * kBucketThreads + tid;
-      if (e >= total || (unsigned)v[u] >= (unsigned)V) continue;
-      // token = e / K (exact: e < 2^20, and (e + 0.5) / K stays >= 1/(2K)
-      // away from an integer while the float product errs by < 2^-12)
-      const int tl = (int)(((float)e + 0.5f) * invK);
-      const int k = e - tl * K;
-      const int pos = atomicAdd(&cur[v[u] >> 8], 1);
-      hits[seg + pos] = (uint32_t)tl | ((uint32_t)(v[u] & 255) << 8) | ((uint32_t)k << 16);
-      hitp[seg + pos] = pv[u];
+      if (e >= total || (unsigned)w[u] >= (unsigned)V) continue;
+      put(e, w[u], atomicAdd(&cur[w[u] >> 8], 1));
     }
   }
 }
@@ -602,23 +726,13 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket(const int32_t* __rest
 // its final value (g/tau)(M q - p), its z is recorded for C, and a bitmap marks
 // it; then one wave per token row forms G = (g/tau) M 2^(y - L2) elsewhere and
 // stores the row of dZ[rows, Vp] (columns V..Vp as zeros).
-// largest exponent (base 2) of the sum of a tile row's stored provisional
-// gradients 2^(y - R), and so of each of them
-constexpr float kRefGap = 40.f;
-constexpr float kRefGapScale = 1099511627776.f;  // 2^kRefGap
-// R is the reference logit plus this many (base 2): stored values are then
-// smaller, which the dH and dW contractions run about 1% faster on (MFMA power
-// depends on the operands); terms below 2^-126 relative to R + kRefShift,
-// i.e. 2^-102 below the reference logit, flush to zero
-constexpr float kRefShift = 24.f;
-
 // epilogue LDS (the main loop's stages are free by then), after the staging area
 template <int TS>
 constexpr int kDzBits = stage_bytes<TS>;                // TS/2 x TS-bit hit map of one half
 template <int TS>
 constexpr int kDzRows = kDzBits<TS> + TS / 2 * TS / 8;  // 3 x TS floats: g/tau M, g/tau, log2 Z
-static_assert(kDzRows<256> + 3 * 1024 <= gemm_lds<256>, "dZ epilogue LDS");
-static_assert(kDzRows<128> + 3 * 512 <= gemm_lds<128>, "dZ epilogue LDS");
+static_assert(kDzRows<256> + 3 * 1024 <= kLdsA3, "dZ epilogue LDS");
+static_assert(kDzRows<128> + 3 * 512 <= kLdsF32, "dZ epilogue LDS");
 
 template <typename T, int TS>
 __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dz(
@@ -629,7 +743,7 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dz(
     int64_t ldz, float* zhit, const int* __restrict__ nrow, int nrow_base) {
   typedef Geo<TS> G;
   constexpr int kThreads = G::kThreads, HT = TS / 2;  // HT: tokens staged at a time
-  __shared__ __attribute__((aligned(16))) char lds[gemm_lds<TS>];
+  __shared__ __attribute__((aligned(16))) char lds[gemm_lds<T, TS>];
   int mt, nt;
   tile_coords(blockIdx.x, TM, TN, G::GM, mt, nt);
   const int m0 = mt * TS, n0 = nt * TS;
@@ -793,7 +907,7 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dz(
 // chunk is projected once instead of once for log Z and again for dZ: the
 // tile records per token z at its teacher entries, the provisional gradient
 // dZ'' = 2^(y - R) with y = z log2(e) / tau in the dZ buffer (0 past V), R
-// being the token's reference logit from k_ref_logit, and the partials (R,
+// being the token's reference logit from k_prologue, and the partials (R,
 // sum of 2^(y - R)) of log Z (a reference and a sum relative to it, like
 // the (max, sum) partials of k_logits_lse).
 // Once log Z is merged, the row factor (g/tau) M 2^(R - log2 Z) turns dZ''
@@ -813,7 +927,7 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_logits
     int nrow_base) {
   typedef Geo<TS> G;
   constexpr int kThreads = G::kThreads, HT = TS / 2;  // HT: tokens staged at a time
-  __shared__ __attribute__((aligned(16))) char lds[gemm_lds<TS>];
+  __shared__ __attribute__((aligned(16))) char lds[gemm_lds<T, TS>];
   int mt, nt;
   tile_coords(blockIdx.x, TM, TN, G::GM, mt, nt);
   const int m0 = mt * TS, n0 = nt * TS;
@@ -952,66 +1066,6 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_logits
       }
     }
     __syncthreads();
-  }
-}
-
-// The reference logit of each token for k_logits_dz: R = z log2(e)/tau at the
-// teacher entry with the largest teacher logit (a valid index), plus
-// kRefShift, one wave per token; -inf when the row has no valid index. The
-// logit part never exceeds the row's max y beyond rounding, so 2^(y - R)
-// keeps every term that matters; a tile whose sum of 2^(y - R) exceeds
-// 2^kRefGap falls back to its own max. Also clears the row's fallback flag.
-// Row r is token row0 + r, or rowmap[r] (a row without a token has no valid
-// index after the prologue).
-template <typename T>
-__global__ void k_ref_logit(const T* __restrict__ H, const T* __restrict__ W, int D,
-                            const int32_t* __restrict__ tidx, const float* __restrict__ tlogit,
-                            int64_t row0, const int* __restrict__ rowmap, int rows, int K, int V,
-                            float k2, float* rowR, int* rowFlag) {
-  const int lane = threadIdx.x & 63;
-  const int r = blockIdx.x * 4 + wave_id();
-  if (r >= rows) return;
-  const int64_t t = rowmap != nullptr ? (int64_t)rowmap[r] : row0 + r;
-  const int32_t* ix = tidx + (int64_t)r * K;
-  const float* tl = tlogit + (t < 0 ? 0 : t) * (int64_t)K;
-  float best = -INFINITY;
-  int bk = K;
-  for (int k = lane; k < K; k += 64) {
-    const int v = ix[k];
-    if ((unsigned)v < (unsigned)V && (tl[k] > best || (tl[k] == best && k < bk))) {
-      best = tl[k];
-      bk = k;
-    }
-  }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const float ob = __shfl_xor(best, o);
-    const int ok = __shfl_xor(bk, o);
-    if (ob > best || (ob == best && ok < bk)) {
-      best = ob;
-      bk = ok;
-    }
-  }
-  float z = 0.f;
-  if (bk < K) {
-    // 16-byte pieces of both rows (D is a multiple of 64, rows 16-byte aligned)
-    constexpr int VPT = 16 / (int)sizeof(T);
-    const T* h = H + t * D;
-    const T* w = W + (int64_t)ix[bk] * D;
-    for (int d = lane * VPT; d < D; d += 64 * VPT) {
-      const u32x4_t hv = *reinterpret_cast<const u32x4_t*>(h + d);
-      const u32x4_t wv = *reinterpret_cast<const u32x4_t*>(w + d);
-      T he[VPT], we[VPT];
-      __builtin_memcpy(he, &hv, 16);
-      __builtin_memcpy(we, &wv, 16);
-#pragma unroll
-      for (int x = 0; x < VPT; ++x) z += (float)he[x] * (float)we[x];
-    }
-    z = wave_sum(z);
-  }
-  if (lane == 0) {
-    rowR[r] = bk < K ? z * k2 + kRefShift : -INFINITY;
-    rowFlag[r] = 0;
   }
 }
 
@@ -1168,22 +1222,26 @@ __global__ __launch_bounds__(256) void k_row_finish(
   if (threadIdx.x == 0) block_partial[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// loss = (sum of the loss partials) / N_valid, in a fixed order: thread i sums
-// partials i, i + 1024, ..., then a tree over the threads.
-constexpr int kFinThreads = 1024;
-__global__ __launch_bounds__(kFinThreads) void k_finalize_loss(const float* partials, int n,
-                                                               const float* inv_nvalid,
-                                                               float* loss) {
+// loss = (sum of the loss partials) / N_valid, in a fixed order: thread i of
+// 256 sums pieces i, i + 256, ... of four partials, then a tree over the
+// threads. partials is 16-byte aligned.
+constexpr int kFinThreads = 256;
+__device__ __forceinline__ void finalize_loss(const float* partials, int n, float inv_n,
+                                              float* loss) {
   __shared__ float red[kFinThreads];
-  float s = 0.f;
-  for (int i = threadIdx.x; i < n; i += kFinThreads) s += partials[i];
-  red[threadIdx.x] = s;
+  const int tid = threadIdx.x;
+  f32x4_t s = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+  for (int i = tid; i < n / 4; i += kFinThreads) s += reinterpret_cast<const f32x4_t*>(partials)[i];
+  float t = (s[0] + s[1]) + (s[2] + s[3]);
+  if (tid < (n & 3)) t += partials[(n & ~3) + tid];
+  red[tid] = t;
   __syncthreads();
   for (int o = kFinThreads / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    if (tid < o) red[tid] += red[tid + o];
     __syncthreads();
   }
-  if (threadIdx.x == 0) loss[0] = red[0] * inv_nvalid[0];
+  if (tid == 0) loss[0] = red[0] * inv_n;
 }
 
 // -------------------------------------------------------------------- dH ----
@@ -1202,7 +1260,7 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dh(con
                                                     const int* __restrict__ rowmap,
                                                     const int* __restrict__ nrow, int nrow_base) {
   typedef Geo<TS> G;
-  __shared__ __attribute__((aligned(16))) char lds[gemm_lds<TS>];
+  __shared__ __attribute__((aligned(16))) char lds[gemm_lds<T, TS>];
   const int tiles = TM * TN;
   const int sidx = blockIdx.x / tiles;
   int mt, nt;
@@ -1266,25 +1324,28 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dh(con
   }
 }
 
+// dH of a split launch: the parts added in order, four features per thread.
 template <typename T>
-__global__ void k_dh_reduce(const float* partial, int split, int64_t n, int D,
-                            const float* __restrict__ rowscale, void* gH, int gh_f32,
-                            const int* __restrict__ rowmap) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (; i < n; i += stride) {
+__device__ __forceinline__ void dh_reduce(int64_t i0, int64_t stride, const float* partial,
+                                          int split, int64_t n, int D, const float* rowscale,
+                                          void* gH, int gh_f32, const int* rowmap) {
+  for (int64_t i = i0; i < n; i += stride) {
     const int64_t t = i / D;
     // with a rowmap: the grad_hidden row of dZ row t (rows without a token,
     // whose partials were never written, are skipped)
     const int64_t o = rowmap != nullptr ? (int64_t)rowmap[t] * D + (i - t * D) : i;
     if (o < 0) continue;
-    float s = 0.f;
-    for (int k = 0; k < split; ++k) s += partial[(int64_t)k * n + i];
-    const float v = rowscale ? s * rowscale[t] : s;
-    if (gh_f32)
-      static_cast<float*>(gH)[o] = v;
-    else
-      static_cast<T*>(gH)[o] = (T)v;
+    f32x4_t v = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int k = 0; k < split; ++k)
+      v += *reinterpret_cast<const f32x4_t*>(partial + (int64_t)k * n + i);
+    if (rowscale != nullptr) v *= rowscale[t];
+    if (gh_f32 || sizeof(T) == 4) {
+      *reinterpret_cast<f32x4_t*>(static_cast<float*>(gH) + o) = v;
+    } else {
+      *reinterpret_cast<u32x2_t*>(static_cast<uint16_t*>(gH) + o) =
+          u32x2_t{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+    }
   }
 }
 
@@ -1295,14 +1356,14 @@ __global__ void k_dh_reduce(const float* partial, int split, int64_t n, int D,
 // per workgroup, 16-byte loads and stores on both sides. With a rowmap,
 // column t is hidden row rowmap[t] (-1: zeros).
 template <typename T>
-__global__ __launch_bounds__(256) void k_transpose_rows(const T* __restrict__ H, int tokens,
-                                                         int D, T* __restrict__ Ht, int ldt,
-                                                         const float* __restrict__ rowscale,
-                                                         const int* __restrict__ rowmap) {
+__device__ __forceinline__ void transpose_rows(int bt, int bd, const T* __restrict__ H, int tokens,
+                                               int D, T* __restrict__ Ht, int ldt,
+                                               const float* __restrict__ rowscale,
+                                               const int* __restrict__ rowmap) {
   constexpr int VPT = 16 / (int)sizeof(T);      // elements per 16-byte piece
   constexpr int PAD = 4 / (int)sizeof(T);       // one dword of padding per LDS row
   __shared__ T tile[64][64 + PAD];              // [token][feature]
-  const int t0 = blockIdx.x * 64, d0 = blockIdx.y * 64;
+  const int t0 = bt * 64, d0 = bd * 64;
   const int tid = threadIdx.x;
 #pragma unroll
   for (int u = 0; u < 64 * 64 / VPT / 256; ++u) {
@@ -1330,6 +1391,48 @@ __global__ __launch_bounds__(256) void k_transpose_rows(const T* __restrict__ H,
     u32x4_t v;
     __builtin_memcpy(&v, e, 16);
     *reinterpret_cast<u32x4_t*>(Ht + (int64_t)(d0 + d) * ldt + t0 + c) = v;
+  }
+}
+
+// What is left between a group's dH and its dW, in one launch: blocks
+// [0, nt) transpose the hidden rows for dW, the next nr add up the parts of a
+// split dH, and one more forms the loss after the last chunk.
+struct TailArgs {
+  int nt, nr;
+  // transpose
+  const void* H;
+  int tokens, D;
+  void* Ht;
+  int ldt;
+  const float* rowscale;
+  const int* rowmap;
+  // dH parts
+  const float* partial;
+  int split;
+  int64_t n;
+  const float* dh_rowscale;
+  const int* dh_rowmap;
+  void* gH;
+  int gh_f32;
+  // loss
+  const float* block_partial;
+  int n_partials;
+  const float* inv_nvalid;  // null: inv_n
+  float inv_n;
+  float* loss;
+};
+template <typename T>
+__global__ __launch_bounds__(256) void k_tail(TailArgs a) {
+  const int b = blockIdx.x;
+  if (b < a.nt) {
+    const int td = a.D / 64;
+    transpose_rows<T>(b / td, b % td, static_cast<const T*>(a.H), a.tokens, a.D,
+                      static_cast<T*>(a.Ht), a.ldt, a.rowscale, a.rowmap);
+  } else if (b < a.nt + a.nr) {
+    dh_reduce<T>(((int64_t)(b - a.nt) * 256 + threadIdx.x) * 4, (int64_t)a.nr * 1024, a.partial,
+                 a.split, a.n, a.D, a.dh_rowscale, a.gH, a.gh_f32, a.dh_rowmap);
+  } else {
+    finalize_loss(a.block_partial, a.n_partials, a.inv_nvalid ? a.inv_nvalid[0] : a.inv_n, a.loss);
   }
 }
 
@@ -1365,7 +1468,7 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dw(con
                                                     const int* __restrict__ nrow) {
   typedef Geo<TS> G;
   constexpr int NI = G::NI;
-  __shared__ __attribute__((aligned(16))) char lds[gemm_lds<TS>];
+  __shared__ __attribute__((aligned(16))) char lds[gemm_lds<T, TS>];
   constexpr int KS = kRowB / (int)sizeof(T);
   if (nrow != nullptr) tokens = min(tokens, __builtin_amdgcn_readfirstlane(*nrow));
   const int nks = min(ldt / KS, (tokens + KS - 1) / KS);
@@ -1483,66 +1586,66 @@ __global__ __launch_bounds__(256) void k_dw_fixup(const float* __restrict__ part
 // ------------------------------------------------- ignored tokens left out --
 // The tokens of a dW group [row0, row0 + rows) that are not ignored, in
 // order: rowmap[j] = the j-th of them, -1 for j >= their count, *nrow = the
-// count. One workgroup: thread i counts a contiguous run of the mask, an
-// exclusive scan of the counts over the threads gives each run its first
-// slot.
+// count. One workgroup: thread i counts a contiguous run of the mask (16 bytes
+// at a time where they are aligned), an exclusive scan of the counts over the
+// threads gives each run its first slot. With inv_nvalid (the call's first
+// group), N_valid of the whole mask [0, N) is counted as well and 1/N_valid
+// (0 if none) written.
 constexpr int kScanThreads = 1024;
-__global__ __launch_bounds__(kScanThreads) void k_compact_scan(const uint8_t* __restrict__ ignore,
-                                                               int64_t row0, int rows,
-                                                               int* __restrict__ rowmap,
-                                                               int* __restrict__ nrow) {
-  __shared__ int sc[kScanThreads];
-  const int tid = threadIdx.x;
-  const int per = (rows + kScanThreads - 1) / kScanThreads;
-  const int b = min(rows, tid * per), e = min(rows, b + per);
-  const uint8_t* m = ignore + row0;
+__device__ __forceinline__ int zero_bytes(uint32_t v) {
+  return ((v & 0xffu) == 0u) + ((v & 0xff00u) == 0u) + ((v & 0xff0000u) == 0u) +
+         ((v & 0xff000000u) == 0u);
+}
+// zero bytes of [b, e)
+__device__ __forceinline__ int count_zero(const uint8_t* m, int64_t b, int64_t e) {
   int c = 0;
-  for (int i = b; i < e; ++i) c += m[i] == 0 ? 1 : 0;
-  sc[tid] = c;
-  __syncthreads();
-  // inclusive scan (Hillis-Steele) of the counts
-  for (int o = 1; o < kScanThreads; o <<= 1) {
-    const int add = tid >= o ? sc[tid - o] : 0;
-    __syncthreads();
-    sc[tid] += add;
-    __syncthreads();
+  while (b < e && ((uintptr_t)(m + b) & 15u) != 0u) c += m[b++] == 0 ? 1 : 0;
+#pragma unroll 4
+  for (; b + 16 <= e; b += 16) {
+    const u32x4_t w = *reinterpret_cast<const u32x4_t*>(m + b);
+    c += (zero_bytes(w[0]) + zero_bytes(w[1])) + (zero_bytes(w[2]) + zero_bytes(w[3]));
   }
-  int pos = sc[tid] - c;
-  const int total = sc[kScanThreads - 1];
+  while (b < e) c += m[b++] == 0 ? 1 : 0;
+  return c;
+}
+__global__ __launch_bounds__(kScanThreads) void k_compact_scan(const uint8_t* __restrict__ ignore,
+                                                               int64_t N, int64_t row0, int rows,
+                                                               int* __restrict__ rowmap,
+                                                               int* __restrict__ nrow,
+                                                               float* __restrict__ inv_nvalid) {
+  constexpr int NWV = kScanThreads / 64;
+  __shared__ int sc[NWV], all[NWV];
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
+  // runs of a multiple of 16 tokens: aligned when the mask is
+  const int per = ((rows + kScanThreads - 1) / kScanThreads + 15) & ~15;
+  const int b = (int)min((int64_t)rows, (int64_t)tid * per), e = min(rows, b + per);
+  const uint8_t* m = ignore + row0;
+  const int c = count_zero(m, b, e);
+  const int incl = wave_incl_scan(c);
+  if (lane == 63) sc[wave] = incl;
+  if (inv_nvalid != nullptr) {
+    const int64_t per_all = ((N + kScanThreads - 1) / kScanThreads + 15) & ~(int64_t)15;
+    const int64_t b0 = min(N, tid * per_all);
+    int n = count_zero(ignore, b0, min(N, b0 + per_all));
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) n += __shfl_xor(n, o);
+    if (lane == 0) all[wave] = n;
+  }
+  __syncthreads();
+  int pos = incl - c, total = 0;
+  for (int w = 0; w < NWV; ++w) {
+    if (w < wave) pos += sc[w];
+    total += sc[w];
+  }
   for (int i = b; i < e; ++i)
     if (m[i] == 0) rowmap[pos++] = (int)(row0 + i);
   for (int j = total + tid; j < rows; j += kScanThreads) rowmap[j] = -1;
-  if (tid == 0) nrow[0] = total;
-}
-
-// Row j of the group: hidden row rowmap[j] copied to hcomp row j (j < *nrow);
-// if token row0 + j is ignored, its grad_hidden row, per-token loss and saved
-// log Z are set to 0 (the rest of the call never writes them). One workgroup per row,
-// 16 bytes per thread and step.
-__global__ __launch_bounds__(256) void k_compact_rows(const char* __restrict__ hidden,
-                                                      int64_t row_bytes, int64_t row0,
-                                                      const uint8_t* __restrict__ ignore,
-                                                      const int* __restrict__ rowmap,
-                                                      const int* __restrict__ nrow,
-                                                      char* __restrict__ hcomp, char* gH,
-                                                      int64_t gh_row_bytes, float* lpt,
-                                                      float* logz) {
-  const int j = blockIdx.x;
-  const int tid = threadIdx.x;
-  if (j < nrow[0]) {
-    const u32x4_t* src = reinterpret_cast<const u32x4_t*>(hidden + (int64_t)rowmap[j] * row_bytes);
-    u32x4_t* dst = reinterpret_cast<u32x4_t*>(hcomp + (int64_t)j * row_bytes);
-    for (int64_t q = tid; q < row_bytes / 16; q += 256) dst[q] = src[q];
-  }
-  const int64_t t = row0 + j;
-  if (ignore[t] != 0) {
-    if (gH != nullptr) {
-      u32x4_t* z = reinterpret_cast<u32x4_t*>(gH + t * gh_row_bytes);
-      for (int64_t q = tid; q < gh_row_bytes / 16; q += 256) z[q] = u32x4_t{0u, 0u, 0u, 0u};
-    }
-    if (tid == 0) {
-      if (lpt != nullptr) lpt[t] = 0.f;
-      if (logz != nullptr) logz[t] = 0.f;
+  if (tid == 0) {
+    nrow[0] = total;
+    if (inv_nvalid != nullptr) {
+      int n = 0;
+      for (int w = 0; w < NWV; ++w) n += all[w];
+      inv_nvalid[0] = n > 0 ? 1.0f / (float)n : 0.0f;
     }
   }
 }
@@ -1610,14 +1713,12 @@ static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 // ------------------------------------------------- event instrumentation ----
 namespace {
 enum ProfKind {
-  P_COUNT_VALID, P_PROLOGUE, P_BUCKET, P_LOGITS, P_MERGE, P_DZ, P_ROW_LOSS, P_DH, P_DH_REDUCE,
-  P_DW, P_FINALIZE, P_FILL, P_TRANSPOSE, P_LOGITS_DZ, P_REF, P_ROW_FINISH, P_DW_FIXUP,
-  P_COMPACT, P_NKINDS
+  P_PROLOGUE, P_BUCKET, P_LOGITS, P_MERGE, P_DZ, P_ROW_LOSS, P_DH, P_DW, P_TAIL, P_FILL,
+  P_LOGITS_DZ, P_ROW_FINISH, P_DW_FIXUP, P_COMPACT, P_NKINDS
 };
 const char* const kProfNames[P_NKINDS] = {
-    "count_valid", "teacher_prologue", "bucket", "logits_lse", "lse_merge", "dz", "row_loss",
-    "dh", "dh_reduce", "dw", "finalize_loss", "fill", "transpose_rows", "logits_dz", "ref_logit",
-    "row_finish", "dw_fixup", "compact"};
+    "prologue", "bucket", "logits_lse", "lse_merge", "dz", "row_loss", "dh", "dw", "tail", "fill",
+    "logits_dz", "row_finish", "dw_fixup", "compact"};
 struct ProfRec {
   int kind;
   hipEvent_t a, b;
@@ -1704,11 +1805,10 @@ extern "C" int kd_profile_read(kd_kernel_time* out, int max) {
   return w;
 }
 
-template <typename T>
+template <typename T, int TS>
 static int launch_chunk_impl(const KdChunkArgs& a, hipStream_t s) {
   const T* W = static_cast<const T*>(a.W);
   const T* Hc = static_cast<const T*>(a.Hc);
-  constexpr int TS = kd_tile(sizeof(T));
   constexpr int kThreads = Geo<TS>::kThreads;
   // vocabulary tiles up to the padded width: every column of dZ is written
   const int TMv = a.nVT * (kTile / TS), TNt = cdiv(a.rows, TS);
@@ -1720,24 +1820,47 @@ static int launch_chunk_impl(const KdChunkArgs& a, hipStream_t s) {
   if (a.stages & KD_STAGE_PREP) {
     {
       ProfScope ps_(P_PROLOGUE, 0.0, s);
-      hipLaunchKernelGGL(k_teacher_prologue, dim3(a.rows), dim3(64),
-                         (size_t)4 * prologue_hash_slots(a.K) + (size_t)8 * a.K, s, a.tidx_in,
-                         a.tidx, a.tlogit, a.ignore, a.row0, a.rowmap, a.rows, a.K, (int)a.V,
-                         a.inv_tau,
-                         a.teacher_logprobs, a.inv_nvalid, a.gscale, a.gtok,
-                         fwd ? nullptr : a.logz_in, a.p, a.rowM, a.rowH, a.rowCoef, a.rowCoefM,
-                         a.rowL2);
+      PrologueArgs p{};
+      p.tidx = a.tidx_in;
+      p.tidx_out = a.tidx;
+      p.tlogit = a.tlogit;
+      p.ignore = a.ignore;
+      p.row0 = a.row0;
+      p.rowmap = a.rowmap;
+      p.rows = a.rows;
+      p.K = a.K;
+      p.V = (int)a.V;
+      p.D = (int)a.D;
+      p.inv_tau = a.inv_tau;
+      p.logprobs = a.teacher_logprobs;
+      p.inv_nvalid = a.inv_nvalid;
+      p.inv_n = a.inv_n;
+      p.gscale = a.gscale;
+      p.gtok = a.gtok;
+      p.logz_in = fwd ? nullptr : a.logz_in;
+      p.p_out = a.p;
+      p.rowM = a.rowM;
+      p.rowH = a.rowH;
+      p.rowCoef = a.rowCoef;
+      p.rowCoefM = a.rowCoefM;
+      p.rowL2 = a.rowL2;
+      p.hidden = a.hidden;
+      p.W = a.W;
+      p.k2 = k2;
+      p.rowR = a.one_projection ? a.rowR : nullptr;
+      p.rowFlag = a.rowFlag;
+      p.hcomp = static_cast<char*>(const_cast<void*>(a.Hc));
+      p.gH = static_cast<char*>(a.grad_hidden);
+      p.gh_row_bytes = a.D * (a.gh_f32 ? 4 : (int64_t)sizeof(T));
+      p.lpt = a.lpt_full;
+      p.logz_out = a.logz_out;
+      hipLaunchKernelGGL(k_prologue<T>, dim3(a.rows), dim3(64),
+                         (size_t)4 * prologue_hash_slots(a.K) + (size_t)8 * a.K, s, p);
     }
     {
       ProfScope ps_(P_BUCKET, 0.0, s);
       hipLaunchKernelGGL(k_bucket, dim3(nbt), dim3(kBucketThreads), 0, s, a.tidx, a.p, a.rows,
-                         a.K, (int)a.V, a.nVT, a.hits, a.hitp, a.hoff, a.zhit);
-    }
-    if (a.one_projection) {
-      ProfScope ps_(P_REF, 0.0, s);
-      hipLaunchKernelGGL(k_ref_logit<T>, dim3(cdiv(a.rows, 4)), dim3(256), 0, s,
-                         static_cast<const T*>(a.hidden), W, (int)a.D, a.tidx, a.tlogit, a.row0,
-                         a.rowmap, a.rows, a.K, (int)a.V, k2, a.rowR, a.rowFlag);
+                         a.K, (int)a.V, a.nVT, a.hits, fwd ? nullptr : a.hitp, a.hoff, a.zhit);
     }
   }
   if (!(a.stages & KD_STAGE_CHUNK)) return (int)hipGetLastError();
@@ -1798,13 +1921,13 @@ static int launch_chunk_impl(const KdChunkArgs& a, hipStream_t s) {
 
 extern "C" int kd_launch_chunk(const KdChunkArgs* a, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
-  return a->dtype == 1 ? launch_chunk_impl<__bf16>(*a, s) : launch_chunk_impl<float>(*a, s);
+  if (a->dtype != 1) return launch_chunk_impl<float, 128>(*a, s);
+  return launch_chunk_impl<__bf16, 256>(*a, s);
 }
 
-template <typename T>
+template <typename T, int TS>
 static int launch_dh_impl(const KdDhArgs& a, hipStream_t s) {
   const int rows = (int)a.tokens;
-  constexpr int TS = kd_tile(sizeof(T));
   const int TM = cdiv(rows, TS), TN = cdiv(a.D, TS);
   const int ks = (int)(a.ldz * sizeof(T) / kRowB);
   {
@@ -1814,31 +1937,20 @@ static int launch_dh_impl(const KdDhArgs& a, hipStream_t s) {
                        rows, (int)a.D, TM, TN, ks, a.split, a.gH, a.gh_f32, a.partial,
                        a.rowscale, a.rowmap, a.nrow, a.nrow_base);
   }
-  if (a.split > 1) {
-    const int64_t n = (int64_t)rows * a.D;
-    ProfScope ps_(P_DH_REDUCE, 0.0, s);
-    hipLaunchKernelGGL(k_dh_reduce<T>, dim3(std::min<int64_t>(cdiv(n, 256), 8192)), dim3(256), 0,
-                       s, a.partial, a.split, n, (int)a.D, a.rowscale, a.gH, a.gh_f32, a.rowmap);
-  }
   return (int)hipGetLastError();
 }
 
 extern "C" int kd_launch_dh(const KdDhArgs* a, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
-  return a->dtype == 1 ? launch_dh_impl<__bf16>(*a, s) : launch_dh_impl<float>(*a, s);
+  if (a->dtype != 1) return launch_dh_impl<float, 128>(*a, s);
+  return launch_dh_impl<__bf16, 256>(*a, s);
 }
 
-template <typename T>
+template <typename T, int TS>
 static int launch_dw_impl(const KdDwArgs& a, hipStream_t s) {
   const int ldt = (int)(((a.tokens + 63) / 64) * 64);
-  T* Ht = static_cast<T*>(a.Ht);
-  {
-    ProfScope ps_(P_TRANSPOSE, 0.0, s);
-    hipLaunchKernelGGL(k_transpose_rows<T>, dim3(ldt / 64, (int)(a.D / 64)), dim3(256), 0, s,
-                       static_cast<const T*>(a.Hg), (int)a.tokens, (int)a.D, Ht, ldt,
-                       a.rowscale, a.rowmap);
-  }
-  constexpr int TS = kd_tile(sizeof(T)), units = kd_units(sizeof(T));
+  const T* Ht = static_cast<const T*>(a.Ht);
+  constexpr int units = kd_units(TS);
   constexpr int kThreads = Geo<TS>::kThreads;
   const int TM = cdiv(a.D, TS), TN = cdiv(a.V, TS);
   const int tiles = TM * TN;
@@ -1856,12 +1968,12 @@ static int launch_dw_impl(const KdDwArgs& a, hipStream_t s) {
     ProfScope ps_(P_DW, 2.0 * (double)a.tokens * (double)a.D * (double)a.V, s);
     if (nfull < tiles)
       hipLaunchKernelGGL((k_dw<T, TS, true>), dim3(nfull + (tiles - nfull) * split), dim3(kThreads),
-                         0, s, static_cast<const T*>(Ht), ldt, static_cast<const T*>(a.dZ), a.ldz,
+                         0, s, Ht, ldt, static_cast<const T*>(a.dZ), a.ldz,
                          (int)a.tokens, (int)a.V, (int)a.D, TM, TN, a.beta, a.gW, nfull, split,
                          a.partial, a.nrow);
     else
       hipLaunchKernelGGL((k_dw<T, TS, false>), dim3(tiles), dim3(kThreads), 0, s,
-                         static_cast<const T*>(Ht), ldt, static_cast<const T*>(a.dZ), a.ldz,
+                         Ht, ldt, static_cast<const T*>(a.dZ), a.ldz,
                          (int)a.tokens, (int)a.V, (int)a.D, TM, TN, a.beta, a.gW, tiles, 1,
                          (float*)nullptr, a.nrow);
   }
@@ -1875,49 +1987,71 @@ static int launch_dw_impl(const KdDwArgs& a, hipStream_t s) {
 
 extern "C" int kd_launch_dw(const KdDwArgs* a, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
-  return a->dtype == 1 ? launch_dw_impl<__bf16>(*a, s) : launch_dw_impl<float>(*a, s);
+  if (a->dtype != 1) return launch_dw_impl<float, 128>(*a, s);
+  return launch_dw_impl<__bf16, 256>(*a, s);
+}
+
+template <typename T>
+static int launch_tail_impl(const KdTailArgs& a, hipStream_t s) {
+  TailArgs t{};
+  if (a.Ht != nullptr) {
+    t.H = a.Hg;
+    t.tokens = (int)a.tokens;
+    t.Ht = a.Ht;
+    t.ldt = (int)(((a.tokens + 63) / 64) * 64);
+    t.rowscale = a.rowscale;
+    t.rowmap = a.rowmap;
+    t.nt = t.ldt / 64 * (int)(a.D / 64);
+  }
+  t.D = (int)a.D;
+  if (a.split > 1) {
+    t.partial = a.partial;
+    t.split = a.split;
+    t.n = a.dh_rows * a.D;
+    t.dh_rowscale = a.dh_rowscale;
+    t.dh_rowmap = a.dh_rowmap;
+    t.gH = a.gH;
+    t.gh_f32 = a.gh_f32;
+    t.nr = (int)std::min<int64_t>(cdiv(t.n, 1024), 4096);
+  }
+  if (a.loss != nullptr) {
+    t.block_partial = a.block_partial;
+    t.n_partials = a.n_partials;
+    t.inv_nvalid = a.inv_nvalid;
+    t.inv_n = a.inv_n;
+    t.loss = a.loss;
+  }
+  const int blocks = t.nt + t.nr + (a.loss != nullptr ? 1 : 0);
+  if (blocks == 0) return 0;
+  {
+    ProfScope ps_(P_TAIL, 0.0, s);
+    hipLaunchKernelGGL(k_tail<T>, dim3(blocks), dim3(256), 0, s, t);
+  }
+  return (int)hipGetLastError();
+}
+
+extern "C" int kd_launch_tail(const KdTailArgs* a, void* stream) {
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  return a->dtype == 1 ? launch_tail_impl<__bf16>(*a, s) : launch_tail_impl<float>(*a, s);
 }
 
 extern "C" int kd_launch_compact(const KdCompactArgs* a, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (a->rows <= 0) return 0;
-  const int64_t eb = a->dtype == 1 ? 2 : 4;
   {
     ProfScope ps_(P_COMPACT, 0.0, s);
-    hipLaunchKernelGGL(k_compact_scan, dim3(1), dim3(kScanThreads), 0, s, a->ignore, a->row0,
-                       a->rows, a->rowmap, a->nrow);
-    hipLaunchKernelGGL(k_compact_rows, dim3(a->rows), dim3(256), 0, s,
-                       static_cast<const char*>(a->hidden), a->D * eb, a->row0, a->ignore,
-                       a->rowmap, a->nrow, static_cast<char*>(a->hcomp),
-                       static_cast<char*>(a->grad_hidden), a->D * (a->gh_f32 ? 4 : eb),
-                       a->loss_per_token, a->logz_out);
+    hipLaunchKernelGGL(k_compact_scan, dim3(1), dim3(kScanThreads), 0, s, a->ignore, a->N, a->row0,
+                       a->rows, a->rowmap, a->nrow, a->inv_nvalid);
   }
   return (int)hipGetLastError();
 }
 
-extern "C" int kd_launch_prepare(const KdPrepareArgs* a, void* stream) {
+extern "C" int kd_launch_fill(float* p, int64_t n, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   {
-    ProfScope ps_(P_COUNT_VALID, 0.0, s);
-    hipLaunchKernelGGL(k_count_valid, dim3(1), dim3(kCountThreads), 0, s, a->ignore, a->N,
-                       a->nvalid, a->inv_nvalid);
-  }
-  if (a->zero_gW != nullptr) {
-    const int64_t n = a->V * a->D;
     ProfScope ps_(P_FILL, 0.0, s);
-    hipLaunchKernelGGL(k_fill_f32, dim3(std::min<int64_t>(cdiv(n, 256), 16384)), dim3(256), 0, s,
-                       a->zero_gW, n, 0.0f);
-  }
-  return (int)hipGetLastError();
-}
-
-extern "C" int kd_launch_finalize(const float* partials, int n, const float* inv_nvalid,
-                                  float* loss, void* stream) {
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  {
-    ProfScope ps_(P_FINALIZE, 0.0, s);
-    hipLaunchKernelGGL(k_finalize_loss, dim3(1), dim3(kFinThreads), 0, s, partials, n, inv_nvalid,
-                       loss);
+    hipLaunchKernelGGL(k_fill_f32, dim3(std::min<int64_t>(cdiv(n, 256), 16384)), dim3(256), 0, s, p,
+                       n, 0.0f);
   }
   return (int)hipGetLastError();
 }

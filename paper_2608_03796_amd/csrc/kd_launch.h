@@ -5,15 +5,6 @@
 #include <stddef.h>
 #include <stdint.h>
 
-struct KdPrepareArgs {
-  int dtype;                // 0 fp32, 1 bf16
-  int64_t N, D, V;
-  const uint8_t* ignore;    // [N] or null
-  int* nvalid;              // device int
-  float* inv_nvalid;        // device float: 1/N_valid or 0
-  float* zero_gW;           // grad_W to clear, or null
-};
-
 enum { KD_MODE_FWD_BWD = 0, KD_MODE_FWD = 1, KD_MODE_BWD = 2 };
 
 // bytes of the allocation-free entry point's static per-device scratch
@@ -22,9 +13,8 @@ constexpr size_t kd_scratch_bytes_max = (size_t)256 << 20;
 // tokens per loss partial (one block of the row-loss kernels, a wave per token)
 constexpr int kLossRows = 4;
 
-// Stages of kd_launch_chunk: preparing rows (teacher prologue, bucketing,
-// and in the one-projection schedule the reference logits) and the chunk's
-// projection and what follows it. The host prepares the rows of a whole dW
+// Stages of kd_launch_chunk: preparing rows (prologue, bucketing) and the
+// chunk's projection and what follows it. The host prepares the rows of a whole dW
 // group at once when chunks align with 256-token tiles, else each chunk.
 enum { KD_STAGE_PREP = 1, KD_STAGE_CHUNK = 2 };
 
@@ -45,19 +35,27 @@ struct KdChunkArgs {
   int rows;                 // tokens in the chunk (prepared rows)
   float inv_tau;
   const void* W;            // [V, D]
-  const void* Hc;           // hidden + row0 * D (the projection's token rows)
+  const void* Hc;           // the projection's token rows (hidden + row0 * D, or the
+                            // workspace's copy of the rows' hidden rows with a rowmap)
   const void* hidden;       // full [N, D] (the reference logits read rows by token)
   const int32_t* tidx_in;   // full [N, K] (the caller's)
   int32_t* tidx;            // [rows, K] the prologue's copy (repeats -1), read by the rest
   const float* tlogit;      // full [N, K] (prologue indexes with row0)
   const uint8_t* ignore;    // full [N] or null
-  const float* inv_nvalid;
+  const float* inv_nvalid;  // device 1/N_valid, or null: inv_n
+  float inv_n;
   // ignored tokens left out (one-projection schedule): row r of the prepared
   // rows is token rowmap[r] (-1: no token; such rows come after every token),
   // and *nrow - nrow_base of the rows hold tokens. Null: row r is token row0 + r.
   const int* rowmap;
   const int* nrow;
   int nrow_base;
+  // with a rowmap the prologue copies the rows' hidden rows to Hc and sets the
+  // ignored tokens' outputs to 0: grad_hidden (full, or null), the full
+  // loss_per_token (or null) and logz_out
+  void* grad_hidden;
+  int gh_f32;
+  float* lpt_full;
   // per-chunk workspace
   float* p;                 // [rows, K]
   float *rowM, *rowH, *rowCoef, *rowCoefM, *rowL2;   // [rows]
@@ -78,7 +76,8 @@ struct KdChunkArgs {
   float* block_partial;     // this chunk's cdiv(rows, kLossRows) partial sums
 };
 
-// dH GEMM over the chunks of one group: grad_hidden[rows] = dZ[rows] W
+// dH GEMM over the chunks of one group: grad_hidden[rows] = dZ[rows] W (the
+// parts of a split launch are added up by the tail)
 struct KdDhArgs {
   int dtype;
   int64_t D, V;
@@ -96,11 +95,10 @@ struct KdDhArgs {
   int nrow_base;
 };
 
-// The contractions' tiles by element size: bf16 runs 256x256 tiles, one
-// workgroup per compute unit; fp32 (as split bf16) 128x128 tiles, two
-// workgroups per compute unit. kd_units = workgroups the chip runs at once.
-constexpr int kd_tile(size_t eb) { return eb == 2 ? 256 : 128; }
-constexpr int kd_units(size_t eb) { return eb == 2 ? 256 : 512; }
+// The contractions run in square tiles of 256 (bf16; one workgroup per compute
+// unit) or 128 (fp32; two workgroups per compute unit): the workgroups the chip
+// runs at once.
+constexpr int kd_units(int64_t tile) { return tile == 256 ? 256 : 512; }
 
 // the largest split of the dW tail tiles' token range; the partial tiles'
 // workspace holds one tile per unit
@@ -112,46 +110,60 @@ struct KdDwArgs {
   int64_t D, V;
   const void* dZ;           // the group's dZ rows [tokens, ldz]
   int64_t ldz;
-  const void* Hg;           // the group's hidden rows [tokens, D] (full with a rowmap)
   int64_t tokens;           // tokens in the group
-  void* Ht;                 // workspace for Hg transposed: [D, tokens rounded up to 64]
+  const void* Ht;           // the tail's transposed hidden rows: [D, tokens rounded up to 64]
   int beta;                 // 0 overwrite, 1 accumulate
   float* gW;
+  float* partial;           // workspace of the split tail tiles, or null (no split)
+  const int* nrow;          // ignored tokens left out: the dZ rows [0, *nrow) hold tokens;
+                            // or null
+};
+
+// Between a group's dH and dW: hidden rows transposed (Ht not null), the parts
+// of a split dH added up (split > 1), the loss (loss not null)
+struct KdTailArgs {
+  int dtype;
+  int64_t D;
+  const void* Hg;           // the group's hidden rows [tokens, D] (full with a rowmap)
+  int64_t tokens;
+  void* Ht;                 // [D, tokens rounded up to 64], or null
   const float* rowscale;    // [tokens] factor of each dZ row (applied to the
                             // hidden rows), or null (= 1)
-  float* partial;           // workspace of the split tail tiles, or null (no split)
   const int* rowmap;        // [tokens] hidden row of each dZ row (-1: none), or null
-  const int* nrow;          // with rowmap: the dZ rows [0, *nrow) hold tokens
+  const float* partial;     // as in KdDhArgs
+  int split;
+  int64_t dh_rows;
+  const float* dh_rowscale;
+  const int* dh_rowmap;
+  void* gH;
+  int gh_f32;
+  const float* block_partial;
+  int n_partials;
+  const float* inv_nvalid;  // device 1/N_valid, or null: inv_n
+  float inv_n;
+  float* loss;
 };
 
 // Ignored tokens of one dW group [row0, row0 + rows) left out: rowmap[j] =
-// the j-th token not ignored (then -1), *nrow = their count, their hidden
-// rows copied to hcomp [rows, D]; the ignored tokens' grad_hidden rows,
-// per-token losses and saved log Z set to 0.
+// the j-th token not ignored (then -1), *nrow = their count; with inv_nvalid
+// also 1/N_valid of the whole mask.
 struct KdCompactArgs {
-  int dtype;
-  int64_t D;
   const uint8_t* ignore;    // full [N]
+  int64_t N;
   int64_t row0;
   int rows;
-  const void* hidden;       // full [N, D]
-  void* hcomp;
   int* rowmap;
   int* nrow;
-  void* grad_hidden;        // full [N, D] or null
-  int gh_f32;
-  float* loss_per_token;    // full [N] or null
-  float* logz_out;          // full [N] or null
+  float* inv_nvalid;        // or null
 };
 
 extern "C" {
-int kd_launch_prepare(const KdPrepareArgs* a, void* stream);
+int kd_launch_fill(float* p, int64_t n, void* stream);  // n zeros
 int kd_launch_chunk(const KdChunkArgs* a, void* stream);
 int kd_launch_dh(const KdDhArgs* a, void* stream);
 int kd_launch_dw(const KdDwArgs* a, void* stream);
 int kd_launch_compact(const KdCompactArgs* a, void* stream);
-int kd_launch_finalize(const float* partials, int n, const float* inv_nvalid, float* loss,
-                       void* stream);
+int kd_launch_tail(const KdTailArgs* a, void* stream);
 int kd_launch_scale(int out_bf16, const float* x, void* y, int64_t n, const float* g,
                     void* stream);
 // the current device's scratch address (hipGetSymbolAddress on first use)
