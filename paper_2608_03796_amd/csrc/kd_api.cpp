@@ -11,7 +11,8 @@
 #include "../../include/kdtopk.h"
 #include "kd_launch.h"
 
-static_assert(KD_SCRATCH_BYTES == kd_scratch_bytes_max, "scratch size in the header");
+static_assert(KD_SCRATCH_BYTES == kd_scratch_bytes_max - kd_scratch_slack,
+              "scratch size in the header");
 
 namespace {
 
@@ -45,6 +46,7 @@ struct Plan {
   bool prep_per_group; // rows prepared once per group (chunks of whole 256-token tiles)
   int64_t ng;          // rows of the per-row arrays: the group's, or one chunk's (padded)
   int64_t ksteps;      // K steps of dH (the vocabulary)
+  int dh_max_parts;    // partial tiles of dH's split last round the workspace holds
   size_t off_misc, off_p, off_tidx, off_rows, off_pm, off_ps, off_hits, off_hitp, off_hoff, off_zhit,
       off_lossp, off_dz, off_fac, off_ht, off_rowmap, off_dhs, off_dwp, total;
 };
@@ -63,34 +65,32 @@ kd_status check_problem(const kd_problem* p) {
   return KD_OK;
 }
 
-// Split of the dH GEMM's K range (the vocabulary) so that the number of
-// workgroups fills whole rounds of the `units` the chip runs at once.
-int choose_dh_split(int64_t tiles, int64_t ksteps, int64_t units) {
-  int best = 1;
-  double best_eff = (double)tiles / (double)(cdiv(tiles, units) * units);
-  for (int s = 2; s <= 16; ++s) {
-    if (ksteps / s < 8) break;
-    const double eff = (double)(tiles * s) / (double)(cdiv(tiles * s, units) * units);
-    if (eff > best_eff + 0.05) {
-      best = s;
-      best_eff = eff;
-    }
-  }
-  return best;
-}
-
 // Tile edge of each contraction over `n` token rows.
 int proj_tile(const Plan& pl, int64_t) { return pl.eb == 4 ? 128 : 256; }
 int dh_tile(const Plan& pl, int64_t) { return pl.eb == 4 ? 128 : 256; }
 int dw_tile(const Plan& pl, int64_t) { return pl.eb == 4 ? 128 : 256; }
 
-// Tiles and vocabulary split of dH over n rows.
-int64_t dh_tiles(const Plan& pl, int64_t n) {
+// Tiles of dH over n rows, and how they run (see kd_dh_split).
+int dh_tiles(const Plan& pl, int64_t n) {
   const int ts = dh_tile(pl, n);
-  return cdiv(n, ts) * cdiv(pl.D, ts);
+  return (int)(cdiv(n, ts) * cdiv(pl.D, ts));
 }
-int dh_split(const Plan& pl, int64_t n) {
-  return choose_dh_split(dh_tiles(pl, n), pl.ksteps, kd_units(dh_tile(pl, n)));
+KdDhSplit dh_split(const Plan& pl, int64_t n, int max_parts = 1 << 20) {
+  const int ts = dh_tile(pl, n);
+  return kd_dh_split(dh_tiles(pl, n), (int)pl.ksteps, kd_units(ts), kd_part_cost(ts, pl.eb == 4),
+                     max_parts);
+}
+// The most partial tiles dH over 1..n rows of the tile of n rows needs (fewer
+// rows hold tokens when ignored ones are left out).
+int dh_parts(const Plan& pl, int64_t n) {
+  const int ts = dh_tile(pl, n);
+  int parts = 0;
+  for (int64_t tm = cdiv(n, ts); tm > 0; --tm) {
+    const KdDhSplit s = kd_dh_split((int)(tm * cdiv(pl.D, ts)), (int)pl.ksteps, kd_units(ts),
+                                    kd_part_cost(ts, pl.eb == 4), 1 << 20);
+    if (s.split > 1) parts = std::max(parts, s.rem * s.split);
+  }
+  return parts;
 }
 // Bytes of dW's partial tiles over n tokens: its tiles leave the last round of
 // the compute units partly filled, so that round is split along the tokens.
@@ -100,8 +100,9 @@ size_t dw_partial_bytes(const Plan& pl, int64_t n) {
   return (tiles > units && tiles % units != 0) ? (size_t)(units * ts * ts) * 4 : 0;
 }
 
-// g_max > 0 caps the chunks per dW group (see plan_within).
-Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
+// g_max > 0 caps the chunks per dW group, parts_ok = false leaves the last rounds of dH
+// and dW unsplit (see plan_within).
+Plan make_plan(const kd_problem* p, int64_t g_max = 0, bool parts_ok = true) {
   Plan pl{};
   pl.N = p->N;
   pl.D = p->D;
@@ -138,7 +139,7 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
   //    chunk's dH right after its own projection is faster than one dH over
   //    the group (chunk 4000, 2.4% padding: 36.72 unmerged, 37.42 ms merged).
   pl.merged = 1;
-  const bool dh_grouped = dh_tiles(pl, pl.c) < kd_units(dh_tile(pl, pl.c)) || dh_split(pl, pl.c) > 1;
+  const bool dh_grouped = dh_tiles(pl, pl.c) < kd_units(dh_tile(pl, pl.c)) || dh_split(pl, pl.c).split > 1;
   const int pts = proj_tile(pl, pl.c);
   const bool full_rounds = pl.c % kTile == 0 &&
                            cdiv(pl.c, pts) * (pl.Vp / pts) % kd_units(pts) == 0 && pl.c >= 2048;
@@ -160,7 +161,7 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
   // per tile), else once per chunk
   pl.prep_per_group = pl.G > 1 && pl.c % kTile == 0;
   pl.ng = pl.prep_per_group ? pl.G * pl.c : pl.cp;
-  pl.dh_per_group = dh_split(pl, pl.c) > 1;
+  pl.dh_per_group = dh_split(pl, pl.c).split > 1;
   int64_t dh_rows[2];  // the row counts dH runs on: full and last chunk or group
   if (pl.dh_per_group) {
     dh_rows[0] = std::min<int64_t>(pl.G * pl.c, pl.N);
@@ -199,30 +200,36 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
   pl.off_ht = take((size_t)pl.D * rup(pl.G * pl.c, 64) * pl.eb);
   // the token of each of those rows
   pl.off_rowmap = take((size_t)pl.G * pl.c * 4);
-  {
-    int64_t part = 0;
+  if (parts_ok) {
+    size_t bytes = 0;
     for (int64_t r : dh_rows) {
       if (r <= 0) continue;
-      const int sp = dh_split(pl, r);
-      if (sp > 1) part = std::max<int64_t>(part, sp * r);
+      const int parts = dh_parts(pl, r), ts = dh_tile(pl, r);
+      pl.dh_max_parts = std::max(pl.dh_max_parts, parts);
+      bytes = std::max(bytes, (size_t)parts * ts * ts * 4);
     }
-    pl.off_dhs = part > 0 ? take((size_t)part * pl.D * 4) : 0;
+    pl.off_dhs = bytes > 0 ? take(bytes) : 0;
   }
   // partial tiles of the dW contraction's split last round
-  const size_t dwp = std::max(dw_partial_bytes(pl, g_full), dw_partial_bytes(pl, g_last));
+  const size_t dwp =
+      parts_ok ? std::max(dw_partial_bytes(pl, g_full), dw_partial_bytes(pl, g_last)) : 0;
   pl.off_dwp = dwp > 0 ? take(dwp) : 0;
   pl.total = align256(t);
   return pl;
 }
 
 // The plan of make_plan, with fewer chunks per dW group if its workspace
-// exceeds `cap` bytes (the same plan when it fits); false if the workspace of
-// one chunk per group does not fit.
+// exceeds `cap` bytes (the same plan when it fits), and at last without partial
+// tiles; false if the workspace of one chunk per group does not fit.
+// The partials of 128-column vocabulary tiles above those of 256-column ones
+// are not counted: kd_scratch_slack holds them.
 bool plan_within(const kd_problem* p, size_t cap, Plan* out) {
+  auto counted = [](const Plan& q) { return q.total - (size_t)q.cp * (q.nP - q.nVT) * 8; };
   Plan pl = make_plan(p);
-  int64_t g = pl.G * pl.merged;  // the caller's chunks per dW group
-  while (pl.total > cap && g > 1) pl = make_plan(p, --g);
-  if (pl.total > cap) return false;
+  const int64_t g0 = pl.G * pl.merged;  // the caller's chunks per dW group
+  for (int64_t g = g0; counted(pl) > cap && g > 1;) pl = make_plan(p, --g);
+  if (counted(pl) > cap) pl = make_plan(p, 1, false);
+  if (counted(pl) > cap || pl.total > kd_scratch_bytes_max) return false;
   *out = pl;
   return true;
 }
@@ -419,14 +426,15 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
     if (kd_launch_chunk(&a, c.stream) != 0) return KD_ERR_DEVICE;
     n_partials += cdiv(rcount, kLossRows);
     group_tokens += rcount;
+    const bool last = ci == pl.nchunks - 1, group_end = last || slot == pl.G - 1;
     KdTailArgs tail{};
     tail.dtype = p->dtype;
     tail.D = pl.D;
     // dH over rows [r0, r0 + n) of the dZ buffer (from its row `zrow`)
-    // (a split dH's parts are added up by the group's tail: only the last
-    // launch of a group can be split)
+    // (the parts of a split dH are added up by the group's tail: only the last
+    // launch of a group is split)
+    KdDhArgs h{};
     auto dh = [&](int64_t r0, int64_t n, int64_t zrow) -> bool {
-      KdDhArgs h{};
       h.dtype = p->dtype;
       h.D = pl.D;
       h.V = pl.V;
@@ -434,8 +442,8 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
       h.ldz = pl.Vp;
       h.W = c.W;
       h.tokens = n;
-      h.split = dh_split(pl, n);
-      h.partial = h.split > 1 ? reinterpret_cast<float*>(ws + pl.off_dhs) : nullptr;
+      h.max_parts = group_end ? pl.dh_max_parts : 0;
+      h.partial = h.max_parts > 0 ? reinterpret_cast<float*>(ws + pl.off_dhs) : nullptr;
       h.gh_f32 = (p->flags & KD_FLAG_GRAD_HIDDEN_F32) ? 1 : 0;
       h.gH = compact ? c.grad_hidden
                      : static_cast<char*>(c.grad_hidden) + r0 * pl.D * (h.gh_f32 ? 4 : pl.eb);
@@ -443,17 +451,10 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
       h.rowmap = compact ? rowmap + zrow : nullptr;
       h.nrow = compact ? gnrow : nullptr;
       h.nrow_base = (int)zrow;
-      tail.partial = h.partial;
-      tail.split = h.split;
-      tail.dh_rows = n;
-      tail.dh_rowscale = h.rowscale;
-      tail.dh_rowmap = h.rowmap;
-      tail.gH = h.gH;
-      tail.gh_f32 = h.gh_f32;
+      tail.dh = &h;
       return kd_launch_dh(&h, c.stream) == 0;
     };
     if (want_dh && !pl.dh_per_group && !dh(row0, rcount, slot * pl.c)) return KD_ERR_DEVICE;
-    const bool last = ci == pl.nchunks - 1;
     if (last && fwd) {
       tail.block_partial = lossp;
       tail.n_partials = (int)n_partials;
@@ -461,7 +462,7 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
       tail.inv_n = inv_n;
       tail.loss = c.loss;
     }
-    if (!last && (!(want_dh || want_dw) || slot != pl.G - 1)) continue;
+    if (!last && (!(want_dh || want_dw) || !group_end)) continue;
     // the group's dH (when it runs per group) and dW over the G chunks' dZ rows
     const int64_t row_first = row0 + rcount - group_tokens;
     if (want_dh && pl.dh_per_group && !dh(row_first, group_tokens, 0)) return KD_ERR_DEVICE;
@@ -630,7 +631,7 @@ kd_status kd_topk_kl_fwd_bwd_noalloc(const kd_problem* p, const void* hidden, co
          loss_per_token, nullptr, nullptr, nullptr, nullptr, grad_hidden, grad_W,
          accumulate_grad_W, nullptr, 0, hip_stream};
   Plan pl;
-  if (!plan_within(p, kd_scratch_bytes_max, &pl)) return KD_ERR_WORKSPACE_TOO_SMALL;
+  if (!plan_within(p, KD_SCRATCH_BYTES, &pl)) return KD_ERR_WORKSPACE_TOO_SMALL;
   st = validate(p, c, pl, true);
   if (st != KD_OK) return st;
   // the device's scratch array (its address is looked up once per device)

@@ -1246,54 +1246,104 @@ __device__ __forceinline__ void finalize_loss(const float* partials, int n, floa
 
 // -------------------------------------------------------------------- dH ----
 // dH_c[t, d] = sum_v dZ[t, v] W[v, d]: A = dZ (K = vocabulary contiguous),
-// B = W read K-major (rows v, columns d); rows of W past V read as zeros. With
-// split > 1 each split covers a K range and writes fp32 partials. With a
-// rowmap, dZ row t is grad_hidden row rowmap[t] (-1: none), and only the
-// first *nrow - nrow_base rows hold tokens (tiles past them are skipped).
+// B = W read K-major (rows v, columns d); rows of W past V read as zeros. The
+// tiles left over for the last round of workgroups are split along the
+// vocabulary into fp32 partial tiles (see kd_dh_split). With a rowmap, dZ row
+// t is grad_hidden row rowmap[t] (-1: none), and only the first
+// *nrow - nrow_base rows hold tokens: the tiles are those of these rows.
+struct DhArgs {
+  const void* dZ;
+  int64_t ldz;
+  const void* W;
+  int V, rows, D, TN, ks_total;
+  void* gH;
+  int gh_f32;
+  float* partial;
+  int max_parts;
+  const float* rowscale;
+  const int* rowmap;
+  const int* nrow;
+  int nrow_base;
+  KdDhSplit sp;  // without nrow
+};
+// the tile rows that hold tokens and the launch's split
 template <typename T, int TS>
-__global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dh(const T* __restrict__ dZ, int64_t ldz,
-                                                    const T* __restrict__ W, int V, int rows,
-                                                    int D, int TM, int TN, int ks_total,
-                                                    int split, void* gH, int gh_f32,
-                                                    float* partial,
-                                                    const float* __restrict__ rowscale,
-                                                    const int* __restrict__ rowmap,
-                                                    const int* __restrict__ nrow, int nrow_base) {
+__device__ __forceinline__ KdDhSplit dh_split(const DhArgs& a, int& n, int& TM) {
+  n = a.nrow != nullptr ? min(a.rows, __builtin_amdgcn_readfirstlane(*a.nrow) - a.nrow_base) : a.rows;
+  n = max(n, 0);
+  TM = (n + TS - 1) / TS;
+  if (a.nrow == nullptr) return a.sp;
+  return kd_dh_split(TM * a.TN, a.ks_total, kd_units(TS), kd_part_cost(TS, sizeof(T) == 4),
+                     a.max_parts);
+}
+
+template <typename T, int TS>
+__global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dh(DhArgs a) {
   typedef Geo<TS> G;
   __shared__ __attribute__((aligned(16))) char lds[gemm_lds<T, TS>];
-  const int tiles = TM * TN;
-  const int sidx = blockIdx.x / tiles;
+  int n, TM;
+  const KdDhSplit sp = dh_split<T, TS>(a, n, TM);
+  const int pid = blockIdx.x;
+  int L, slot = -1, kb = 0, ke = a.ks_total;
+  if (pid < sp.dp) {
+    L = tile_order_xcd(pid, sp.dp);
+  } else {
+    // the last round: neighbours in the order take the same range of
+    // neighbouring tiles, which share operand rows
+    const int parts = sp.rem * sp.split;
+    if (pid - sp.dp >= parts) return;
+    const int q = tile_order_xcd(pid - sp.dp, parts);
+    const int s = q / sp.rem;
+    L = sp.dp + q - s * sp.rem;
+    if (sp.split > 1) {
+      slot = (L - sp.dp) * sp.split + s;
+      kb = (int)((int64_t)a.ks_total * s / sp.split);
+      ke = (int)((int64_t)a.ks_total * (s + 1) / sp.split);
+    }
+  }
   int mt, nt;
-  tile_coords(blockIdx.x - sidx * tiles, TM, TN, G::GM, mt, nt);
+  tile_at(L, TM, a.TN, G::GM, mt, nt);
   const int m0 = mt * TS, n0 = nt * TS;
-  if (rowmap != nullptr && m0 >= __builtin_amdgcn_readfirstlane(*nrow) - nrow_base) return;
+  const int D = a.D, rows = a.rows;
   const int eb = Elt<T>::bytes;
-  const int lda = (int)(ldz * eb), ldb = D * eb;
-  const int per = (ks_total + split - 1) / split;
-  const int kb = sidx * per, ke = min(ks_total, kb + per);
+  const int lda = (int)(a.ldz * eb), ldb = D * eb;
+  const T* dZ = static_cast<const T*>(a.dZ);
   AccTile<TS> acc;
   const int mrows = min(TS, rows - m0);
   // the row factors of the tile's rows, loaded before the main loop and
   // kept in LDS for the epilogue: a load there would wait for every store
   // issued before it (loads and stores complete in order)
   const int tid = threadIdx.x;
-  const float rsv =
-      (rowscale != nullptr && split == 1 && tid < TS && m0 + tid < rows) ? rowscale[m0 + tid]
-                                                                           : 1.f;
+  const float rsv = (a.rowscale != nullptr && slot < 0 && tid < TS && m0 + tid < rows)
+                        ? a.rowscale[m0 + tid]
+                        : 1.f;
   gemm<T, TS, true>(
-      KcOp{reinterpret_cast<const char*>(dZ + (int64_t)m0 * ldz), (uint32_t)(mrows * lda), lda},
-               KmOp{reinterpret_cast<const char*>(W + n0),
-                    (int64_t)V * ldb - (int64_t)n0 * eb, ldb},
-               kb, ke, lds, acc);
+      KcOp{reinterpret_cast<const char*>(dZ + (int64_t)m0 * a.ldz), (uint32_t)(mrows * lda), lda},
+      KmOp{reinterpret_cast<const char*>(static_cast<const T*>(a.W) + n0),
+           (int64_t)a.V * ldb - (int64_t)n0 * eb, ldb},
+      kb, ke, lds, acc);
   const int lane = tid & 63, wave = wave_id();
   const int wm = G::wm(wave), wn = G::wn(wave);
+  if (slot >= 0) {
+    float* part = a.partial + (int64_t)slot * TS * TS;
+#pragma unroll
+    for (int i = 0; i < G::NI; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = G::acc_m(wm, i, lane, r);
+        if (m0 + m >= n) continue;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) part[m * TS + G::acc_n(wn, j, lane)] = acc.v[i][j][r];
+      }
+    return;
+  }
   float* rsl = reinterpret_cast<float*>(lds);
   int* rml = reinterpret_cast<int*>(lds) + TS;
   if (tid < TS) {
     rsl[tid] = rsv;
     // the output row of each of the tile's rows (loaded here: nothing of the
     // unmasked call is kept live through the main loop for it)
-    rml[tid] = (rowmap != nullptr && split == 1 && m0 + tid < rows) ? rowmap[m0 + tid] : m0 + tid;
+    rml[tid] = (a.rowmap != nullptr && m0 + tid < rows) ? a.rowmap[m0 + tid] : m0 + tid;
   }
   __syncthreads();
 #pragma unroll
@@ -1306,44 +1356,45 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dh(con
       if (d >= D) continue;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int t = m0 + G::acc_m(wm, i, lane, r);
-        if (t < rows) {
-          if (split == 1) {
-            const float v = acc.v[i][j][r] * sc[r];
-            const int64_t o = om[r];  // the grad_hidden row
-            if (o < 0) continue;
-            if (gh_f32)
-              static_cast<float*>(gH)[o * D + d] = v;
-            else
-              static_cast<T*>(gH)[o * D + d] = (T)v;
-          } else
-            partial[((int64_t)sidx * rows + t) * D + d] = acc.v[i][j][r];
-        }
+        if (m0 + G::acc_m(wm, i, lane, r) >= rows) continue;
+        const float v = acc.v[i][j][r] * sc[r];
+        const int64_t o = om[r];  // the grad_hidden row
+        if (o < 0) continue;
+        if (a.gh_f32)
+          static_cast<float*>(a.gH)[o * D + d] = v;
+        else
+          static_cast<T*>(a.gH)[o * D + d] = (T)v;
       }
     }
   }
 }
 
-// dH of a split launch: the parts added in order, four features per thread.
-template <typename T>
-__device__ __forceinline__ void dh_reduce(int64_t i0, int64_t stride, const float* partial,
-                                          int split, int64_t n, int D, const float* rowscale,
-                                          void* gH, int gh_f32, const int* rowmap) {
-  for (int64_t i = i0; i < n; i += stride) {
-    const int64_t t = i / D;
-    // with a rowmap: the grad_hidden row of dZ row t (rows without a token,
-    // whose partials were never written, are skipped)
-    const int64_t o = rowmap != nullptr ? (int64_t)rowmap[t] * D + (i - t * D) : i;
+// The split tiles of dH: their parts added in order, four features per thread.
+template <typename T, int TS>
+__device__ __forceinline__ void dh_reduce(int block, int blocks, const DhArgs& a) {
+  int n, TM;
+  const KdDhSplit sp = dh_split<T, TS>(a, n, TM);
+  if (sp.split < 2) return;
+  constexpr int Q = TS * TS / 4;  // pieces per tile
+  const int total = sp.rem * Q;
+  for (int i = block * 256 + (int)threadIdx.x; i < total; i += blocks * 256) {
+    const int q = i / Q, row = i % Q / (TS / 4), c = i % (TS / 4) * 4;
+    int mt, nt;
+    tile_at(sp.dp + q, TM, a.TN, Geo<TS>::GM, mt, nt);
+    const int t = mt * TS + row, d = nt * TS + c;
+    if (t >= n || d >= a.D) continue;
+    const int64_t o = a.rowmap != nullptr ? a.rowmap[t] : t;  // the grad_hidden row
     if (o < 0) continue;
+    const float* part = a.partial + (int64_t)q * sp.split * (TS * TS) + row * TS + c;
     f32x4_t v = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
-    for (int k = 0; k < split; ++k)
-      v += *reinterpret_cast<const f32x4_t*>(partial + (int64_t)k * n + i);
-    if (rowscale != nullptr) v *= rowscale[t];
-    if (gh_f32 || sizeof(T) == 4) {
-      *reinterpret_cast<f32x4_t*>(static_cast<float*>(gH) + o) = v;
+    for (int k = 0; k < sp.split; ++k)
+      v += *reinterpret_cast<const f32x4_t*>(part + (int64_t)k * TS * TS);
+    if (a.rowscale != nullptr) v *= a.rowscale[t];
+    if (a.gh_f32 || sizeof(T) == 4) {
+      *reinterpret_cast<f32x4_t*>(static_cast<float*>(a.gH) + o * a.D + d) = v;
     } else {
-      *reinterpret_cast<u32x2_t*>(static_cast<uint16_t*>(gH) + o) =
+      *reinterpret_cast<u32x2_t*>(static_cast<uint16_t*>(a.gH) + o * a.D + d) =
           u32x2_t{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
     }
   }
@@ -1406,14 +1457,7 @@ struct TailArgs {
   int ldt;
   const float* rowscale;
   const int* rowmap;
-  // dH parts
-  const float* partial;
-  int split;
-  int64_t n;
-  const float* dh_rowscale;
-  const int* dh_rowmap;
-  void* gH;
-  int gh_f32;
+  DhArgs dh;  // the dH launch whose parts are added up
   // loss
   const float* block_partial;
   int n_partials;
@@ -1421,7 +1465,7 @@ struct TailArgs {
   float inv_n;
   float* loss;
 };
-template <typename T>
+template <typename T, int DTS>
 __global__ __launch_bounds__(256) void k_tail(TailArgs a) {
   const int b = blockIdx.x;
   if (b < a.nt) {
@@ -1429,8 +1473,7 @@ __global__ __launch_bounds__(256) void k_tail(TailArgs a) {
     transpose_rows<T>(b / td, b % td, static_cast<const T*>(a.H), a.tokens, a.D,
                       static_cast<T*>(a.Ht), a.ldt, a.rowscale, a.rowmap);
   } else if (b < a.nt + a.nr) {
-    dh_reduce<T>(((int64_t)(b - a.nt) * 256 + threadIdx.x) * 4, (int64_t)a.nr * 1024, a.partial,
-                 a.split, a.n, a.D, a.dh_rowscale, a.gH, a.gh_f32, a.dh_rowmap);
+    dh_reduce<T, DTS>(b - a.nt, a.nr, a.dh);
   } else {
     finalize_loss(a.block_partial, a.n_partials, a.inv_nvalid ? a.inv_nvalid[0] : a.inv_n, a.loss);
   }
@@ -1926,16 +1969,43 @@ extern "C" int kd_launch_chunk(const KdChunkArgs* a, void* stream) {
 }
 
 template <typename T, int TS>
+static DhArgs dh_args(const KdDhArgs& a) {
+  DhArgs d{};
+  d.dZ = a.dZ;
+  d.ldz = a.ldz;
+  d.W = a.W;
+  d.V = (int)a.V;
+  d.rows = (int)a.tokens;
+  d.D = (int)a.D;
+  d.TN = cdiv(a.D, TS);
+  d.ks_total = (int)(a.ldz * sizeof(T) / kRowB);
+  d.gH = a.gH;
+  d.gh_f32 = a.gh_f32;
+  d.partial = a.partial;
+  d.max_parts = a.max_parts;
+  d.rowscale = a.rowscale;
+  d.rowmap = a.rowmap;
+  d.nrow = a.nrow;
+  d.nrow_base = a.nrow_base;
+  d.sp = kd_dh_split(cdiv(a.tokens, TS) * d.TN, d.ks_total, kd_units(TS),
+                     kd_part_cost(TS, sizeof(T) == 4), a.max_parts);
+  return d;
+}
+
+template <typename T, int TS>
 static int launch_dh_impl(const KdDhArgs& a, hipStream_t s) {
-  const int rows = (int)a.tokens;
-  const int TM = cdiv(rows, TS), TN = cdiv(a.D, TS);
-  const int ks = (int)(a.ldz * sizeof(T) / kRowB);
+  const DhArgs d = dh_args<T, TS>(a);
+  // with a device-side row count: the most workgroups any count needs
+  int blocks = d.sp.dp + d.sp.rem * d.sp.split;
+  if (a.nrow != nullptr)
+    for (int tm = cdiv(a.tokens, TS) - 1; tm > 0; --tm) {
+      const KdDhSplit q = kd_dh_split(tm * d.TN, d.ks_total, kd_units(TS),
+                                      kd_part_cost(TS, sizeof(T) == 4), a.max_parts);
+      blocks = std::max(blocks, q.dp + q.rem * q.split);
+    }
   {
     ProfScope ps_(P_DH, 2.0 * (double)a.tokens * (double)a.D * (double)a.V, s);
-    hipLaunchKernelGGL((k_dh<T, TS>), dim3(TM * TN * a.split), dim3(Geo<TS>::kThreads), 0, s,
-                       static_cast<const T*>(a.dZ), a.ldz, static_cast<const T*>(a.W), (int)a.V,
-                       rows, (int)a.D, TM, TN, ks, a.split, a.gH, a.gh_f32, a.partial,
-                       a.rowscale, a.rowmap, a.nrow, a.nrow_base);
+    hipLaunchKernelGGL((k_dh<T, TS>), dim3(blocks), dim3(Geo<TS>::kThreads), 0, s, d);
   }
   return (int)hipGetLastError();
 }
@@ -1991,7 +2061,7 @@ extern "C" int kd_launch_dw(const KdDwArgs* a, void* stream) {
   return launch_dw_impl<__bf16, 256>(*a, s);
 }
 
-template <typename T>
+template <typename T, int DTS>
 static int launch_tail_impl(const KdTailArgs& a, hipStream_t s) {
   TailArgs t{};
   if (a.Ht != nullptr) {
@@ -2004,15 +2074,12 @@ static int launch_tail_impl(const KdTailArgs& a, hipStream_t s) {
     t.nt = t.ldt / 64 * (int)(a.D / 64);
   }
   t.D = (int)a.D;
-  if (a.split > 1) {
-    t.partial = a.partial;
-    t.split = a.split;
-    t.n = a.dh_rows * a.D;
-    t.dh_rowscale = a.dh_rowscale;
-    t.dh_rowmap = a.dh_rowmap;
-    t.gH = a.gH;
-    t.gh_f32 = a.gh_f32;
-    t.nr = (int)std::min<int64_t>(cdiv(t.n, 1024), 4096);
+  if (a.dh != nullptr && a.dh->max_parts > 0) {
+    t.dh = dh_args<T, DTS>(*a.dh);
+    const int rem = a.dh->nrow != nullptr ? std::min(cdiv(a.dh->tokens, DTS) * t.dh.TN, kd_units(DTS))
+                    : t.dh.sp.split > 1   ? t.dh.sp.rem
+                                          : 0;
+    t.nr = std::min(rem * (DTS * DTS / 1024), 4096);
   }
   if (a.loss != nullptr) {
     t.block_partial = a.block_partial;
@@ -2025,14 +2092,15 @@ static int launch_tail_impl(const KdTailArgs& a, hipStream_t s) {
   if (blocks == 0) return 0;
   {
     ProfScope ps_(P_TAIL, 0.0, s);
-    hipLaunchKernelGGL(k_tail<T>, dim3(blocks), dim3(256), 0, s, t);
+    hipLaunchKernelGGL((k_tail<T, DTS>), dim3(blocks), dim3(256), 0, s, t);
   }
   return (int)hipGetLastError();
 }
 
 extern "C" int kd_launch_tail(const KdTailArgs* a, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
-  return a->dtype == 1 ? launch_tail_impl<__bf16>(*a, s) : launch_tail_impl<float>(*a, s);
+  if (a->dtype != 1) return launch_tail_impl<float, 128>(*a, s);
+  return launch_tail_impl<__bf16, 256>(*a, s);
 }
 
 extern "C" int kd_launch_compact(const KdCompactArgs* a, void* stream) {

@@ -7,8 +7,13 @@
 
 enum { KD_MODE_FWD_BWD = 0, KD_MODE_FWD = 1, KD_MODE_BWD = 2 };
 
-// bytes of the allocation-free entry point's static per-device scratch
-constexpr size_t kd_scratch_bytes_max = (size_t)256 << 20;
+// bytes of the allocation-free entry point's static per-device scratch: the
+// 256 MiB a plan may count, and a slack for the projection's partials of
+// 128-column vocabulary tiles above those of 256-column ones: 8 bytes per row
+// (padded to 256) and 256 columns, at most 8 MiB (256 rows at V = 2^20; more
+// rows only with fewer columns)
+constexpr size_t kd_scratch_slack = (size_t)8 << 20;
+constexpr size_t kd_scratch_bytes_max = ((size_t)256 << 20) + kd_scratch_slack;
 
 // tokens per loss partial (one block of the row-loss kernels, a wave per token)
 constexpr int kLossRows = 4;
@@ -85,8 +90,8 @@ struct KdDhArgs {
   int64_t ldz;
   const void* W;            // [V, D]
   int64_t tokens;           // tokens in the group
-  int split;                // split of the vocabulary (K) range, >= 1
-  float* partial;           // [split, tokens, D] when split > 1
+  float* partial;           // partial tiles of the split last round
+  int max_parts;            // their number (0: no split)
   void* gH;                 // grad_hidden + the group's first row * D (full with a rowmap)
   int gh_f32;               // grad_hidden is fp32 (else the operands' dtype)
   const float* rowscale;    // [tokens] factor of each dZ row, or null (= 1)
@@ -99,6 +104,51 @@ struct KdDhArgs {
 // unit) or 128 (fp32; two workgroups per compute unit): the workgroups the chip
 // runs at once.
 constexpr int kd_units(int64_t tile) { return tile == 256 ? 256 : 512; }
+
+// How dH's tiles run: the tiles of the full rounds whole (`dp` of them), the
+// `rem` tiles left over for the last round each split into `split` ranges of
+// the vocabulary, whose fp32 partial tiles the tail launch adds up. The split
+// is the one with the least time by a model in K steps of a tile: a round
+// costs its longest range plus kDhRound steps (pipeline fill and epilogue), a
+// partial tile its write and read. Splitting only the last round keeps the
+// partial traffic small. Measured, whole calls: 6001 tokens, D = 2560, V =
+// 40001 (240 tiles): 3.26 -> 2.90 ms; 77 tokens, D = 768, V = 32003 (3 tiles):
+// 126 -> 109 us. Evaluated on the device where the
+// number of rows is only known there (ignored tokens left out). At most
+// max_parts partial tiles, and at most two rounds of them (their traffic).
+constexpr float kDhRound = 4.f;
+constexpr int kDhMaxSplit = 64;
+struct KdDhSplit {
+  int dp, rem, split;
+};
+#ifdef __HIP__
+__host__ __device__
+#endif
+inline KdDhSplit kd_dh_split(int tiles, int ksteps, int units, float part_cost, int max_parts) {
+  KdDhSplit r;
+  r.dp = tiles / units * units;
+  r.rem = tiles - r.dp;
+  r.split = 1;
+  if (r.rem == 0) return r;
+  float best = (float)ksteps + kDhRound;
+  for (int s = 2; s <= kDhMaxSplit; ++s) {
+    const int parts = r.rem * s;
+    if (parts > max_parts || parts > 2 * units || ksteps < 4 * s) break;
+    const float t = (float)((parts + units - 1) / units) *
+                        ((float)((ksteps + s - 1) / s) + kDhRound) +
+                    (float)parts * part_cost + kDhRound;
+    if (t < best) {
+      best = t;
+      r.split = s;
+    }
+  }
+  return r;
+}
+// K steps of a tile that one partial tile's write and read cost (a 256 KB
+// partial tile against 1.44 us, a 64 KB one of fp32 against 2 us)
+constexpr float kd_part_cost(int tile, bool) {
+  return tile == 256 ? 0.08f : 0.015f;
+}
 
 // the largest split of the dW tail tiles' token range; the partial tiles'
 // workspace holds one tile per unit
@@ -120,7 +170,7 @@ struct KdDwArgs {
 };
 
 // Between a group's dH and dW: hidden rows transposed (Ht not null), the parts
-// of a split dH added up (split > 1), the loss (loss not null)
+// of a split dH added up (dh not null), the loss (loss not null)
 struct KdTailArgs {
   int dtype;
   int64_t D;
@@ -130,13 +180,7 @@ struct KdTailArgs {
   const float* rowscale;    // [tokens] factor of each dZ row (applied to the
                             // hidden rows), or null (= 1)
   const int* rowmap;        // [tokens] hidden row of each dZ row (-1: none), or null
-  const float* partial;     // as in KdDhArgs
-  int split;
-  int64_t dh_rows;
-  const float* dh_rowscale;
-  const int* dh_rowmap;
-  void* gH;
-  int gh_f32;
+  const KdDhArgs* dh;       // the dH launch whose parts are to be added up, or null
   const float* block_partial;
   int n_partials;
   const float* inv_nvalid;  // device 1/N_valid, or null: inv_n
