@@ -46,7 +46,7 @@ struct Plan {
   bool prep_per_group; // rows prepared once per group (chunks of whole 256-token tiles)
   int64_t ng;          // rows of the per-row arrays: the group's, or one chunk's (padded)
   int64_t ksteps;      // K steps of dH (the vocabulary)
-  int dh_max_parts;    // partial tiles of dH's split last round the workspace holds
+  int dh_max_parts, dw_max_parts;  // partial tiles of the split last rounds it holds
   size_t off_misc, off_p, off_tidx, off_rows, off_pm, off_ps, off_hits, off_hitp, off_hoff, off_zhit,
       off_lossp, off_dz, off_fac, off_ht, off_rowmap, off_dhs, off_dwp, total;
 };
@@ -65,19 +65,38 @@ kd_status check_problem(const kd_problem* p) {
   return KD_OK;
 }
 
-// Tile edge of each contraction over `n` token rows.
-int proj_tile(const Plan& pl, int64_t) { return pl.eb == 4 ? 128 : 256; }
-int dh_tile(const Plan& pl, int64_t) { return pl.eb == 4 ? 128 : 256; }
-int dw_tile(const Plan& pl, int64_t) { return pl.eb == 4 ? 128 : 256; }
+// Tile edge of each contraction over n token rows: fp32 runs 128x128 tiles; bf16
+// 256x256 tiles, whose main loop is 10 to 25% faster, unless these are so few
+// that most of the chip would idle. The lines are where whole calls crossed
+// (256 and 128 tiles, us; t = 256x256 tiles of the launch):
+//  * projection, t <= 128: 400 x 1024 x 8192 (t = 64) 90.3, 80.6; 600 x 3072 x
+//    10000 (120) 179, 172; 1000 x 512 x 16000 (252) 104, 110;
+//  * dH, t <= 8: 256 x 256 x 8192 (1) 69, 63; 512 x 1024 x 32000 (8) 154, 148;
+//    128 x 4096 x 32000 (16) 322, 326; 1024 x 1024 x 32000 (16) 233, 239;
+//  * dW, t <= 128: 2000 x 512 x 4096 (32) 110, 90; 1000 x 512 x 16000 (126) 104,
+//    97; 2000 x 4096 x 4096 (256) 226, 238. Also up to two K steps (128 tokens)
+//    in up to two rounds, where a tile is all epilogue: 77 x 768 x 32003
+//    (t = 375) 109, 86; 128 x 1024 x 100003 (1564) 265, 285.
+int64_t tiles256(int64_t m, int64_t n) { return cdiv(m, 256) * cdiv(n, 256); }
+int proj_tile(const Plan& pl, int64_t n) {
+  return pl.eb == 4 || tiles256(pl.V, n) <= 128 ? 128 : 256;
+}
+int dh_tile(const Plan& pl, int64_t n) {
+  return pl.eb == 4 || tiles256(pl.D, n) <= 8 ? 128 : 256;
+}
+int dw_tile(const Plan& pl, int64_t n) {
+  const int64_t t = tiles256(pl.D, pl.V);
+  return pl.eb == 4 || t <= 128 || (n <= 128 && t <= 512) ? 128 : 256;
+}
 
-// Tiles of dH over n rows, and how they run (see kd_dh_split).
+// Tiles of dH over n rows, and how they run (see kd_split_rounds).
 int dh_tiles(const Plan& pl, int64_t n) {
   const int ts = dh_tile(pl, n);
   return (int)(cdiv(n, ts) * cdiv(pl.D, ts));
 }
-KdDhSplit dh_split(const Plan& pl, int64_t n, int max_parts = 1 << 20) {
+KdRounds dh_split(const Plan& pl, int64_t n, int max_parts = 1 << 20) {
   const int ts = dh_tile(pl, n);
-  return kd_dh_split(dh_tiles(pl, n), (int)pl.ksteps, kd_units(ts), kd_part_cost(ts, pl.eb == 4),
+  return kd_split_rounds(dh_tiles(pl, n), (int)pl.ksteps, kd_units(ts), kd_part_cost(ts, pl.eb == 4),
                      max_parts);
 }
 // The most partial tiles dH over 1..n rows of the tile of n rows needs (fewer
@@ -86,18 +105,19 @@ int dh_parts(const Plan& pl, int64_t n) {
   const int ts = dh_tile(pl, n);
   int parts = 0;
   for (int64_t tm = cdiv(n, ts); tm > 0; --tm) {
-    const KdDhSplit s = kd_dh_split((int)(tm * cdiv(pl.D, ts)), (int)pl.ksteps, kd_units(ts),
+    const KdRounds s = kd_split_rounds((int)(tm * cdiv(pl.D, ts)), (int)pl.ksteps, kd_units(ts),
                                     kd_part_cost(ts, pl.eb == 4), 1 << 20);
     if (s.split > 1) parts = std::max(parts, s.rem * s.split);
   }
   return parts;
 }
-// Bytes of dW's partial tiles over n tokens: its tiles leave the last round of
-// the compute units partly filled, so that round is split along the tokens.
-size_t dw_partial_bytes(const Plan& pl, int64_t n) {
+// The partial tiles dW over n tokens needs.
+int dw_parts(const Plan& pl, int64_t n) {
   const int ts = dw_tile(pl, n);
-  const int64_t units = kd_units(ts), tiles = cdiv(pl.D, ts) * cdiv(pl.V, ts);
-  return (tiles > units && tiles % units != 0) ? (size_t)(units * ts * ts) * 4 : 0;
+  const KdRounds s =
+      kd_split_rounds((int)(cdiv(pl.D, ts) * cdiv(pl.V, ts)), (int)(rup(n, 64) * pl.eb / 128),
+                      kd_units(ts), kd_part_cost(ts, pl.eb == 4), 1 << 20);
+  return s.split > 1 ? s.rem * s.split : 0;
 }
 
 // g_max > 0 caps the chunks per dW group, parts_ok = false leaves the last rounds of dH
@@ -210,10 +230,17 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0, bool parts_ok = true) {
     }
     pl.off_dhs = bytes > 0 ? take(bytes) : 0;
   }
-  // partial tiles of the dW contraction's split last round
-  const size_t dwp =
-      parts_ok ? std::max(dw_partial_bytes(pl, g_full), dw_partial_bytes(pl, g_last)) : 0;
-  pl.off_dwp = dwp > 0 ? take(dwp) : 0;
+  // partial tiles of dW's split last round
+  if (parts_ok) {
+    size_t bytes = 0;
+    for (int64_t r : {g_full, g_last}) {
+      if (r <= 0) continue;
+      const int parts = dw_parts(pl, r), ts = dw_tile(pl, r);
+      pl.dw_max_parts = std::max(pl.dw_max_parts, parts);
+      bytes = std::max(bytes, (size_t)parts * ts * ts * 4);
+    }
+    pl.off_dwp = bytes > 0 ? take(bytes) : 0;
+  }
   pl.total = align256(t);
   return pl;
 }
@@ -348,6 +375,7 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
   auto chunk_args = [&](int64_t row0, int rcount, int64_t o, int64_t g, int stages) {
     KdChunkArgs a{};
     a.dtype = p->dtype;
+    a.tile = proj_tile(pl, rcount);
     a.mode = c.mode;
     a.stages = stages;
     a.one_projection = scaled ? 1 : 0;
@@ -442,6 +470,7 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
       h.ldz = pl.Vp;
       h.W = c.W;
       h.tokens = n;
+      h.tile = dh_tile(pl, n);
       h.max_parts = group_end ? pl.dh_max_parts : 0;
       h.partial = h.max_parts > 0 ? reinterpret_cast<float*>(ws + pl.off_dhs) : nullptr;
       h.gh_f32 = (p->flags & KD_FLAG_GRAD_HIDDEN_F32) ? 1 : 0;
@@ -477,6 +506,7 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
     if (want_dw) {
       KdDwArgs d{};
       d.dtype = p->dtype;
+      d.tile = dw_tile(pl, group_tokens);
       d.D = pl.D;
       d.V = pl.V;
       d.dZ = ws + pl.off_dz;
@@ -485,7 +515,8 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
       d.Ht = ws + pl.off_ht;
       d.beta = (dw_done || c.accumulate) ? 1 : 0;
       d.gW = c.grad_W;
-      d.partial = pl.off_dwp ? reinterpret_cast<float*>(ws + pl.off_dwp) : nullptr;
+      d.max_parts = pl.dw_max_parts;
+      d.partial = d.max_parts > 0 ? reinterpret_cast<float*>(ws + pl.off_dwp) : nullptr;
       d.nrow = compact ? gnrow : nullptr;
       if (kd_launch_dw(&d, c.stream) != 0) return KD_ERR_DEVICE;
       dw_done = true;

@@ -463,6 +463,84 @@ __device__ __forceinline__ void gemm_tile(const OA& opa, const OB& opb, int ks_b
   }
 }
 
+// The 128x128 tile of bf16 contractions: 4 waves of 64x64, two workgroups per
+// compute unit. Same operands, LDS layouts and K order as gemm_tile, with two
+// stages of 16 KiB per operand; a stage is refilled once every wave has read
+// it, and what hides a workgroup's waits is the other workgroup. A 64x64 wave
+// needs 8 fragment reads per 16 MFMAs instead of 12 per 32, so the LDS (2/3 of
+// the MFMA rate at best) bounds it: for launches of few tiles, where four
+// times the workgroups, shorter epilogues and a finer last round count for
+// more. Ends with a barrier.
+constexpr int kLdsSmall = 2 * 2 * 128 * kRowB;  // 64 KiB
+
+template <typename OA, typename OB>
+__device__ __forceinline__ void gemm_small(const OA& opa, const OB& opb, int ks_begin, int ks_end,
+                                           char* lds, AccTile<128>& acc) {
+  typedef Geo<128> G;
+  constexpr int NPW = 4, OPB = 128 * kRowB, STB = 2 * OPB;
+  const int lane = threadIdx.x & 63, wave = wave_id();
+  const int wm = G::wm(wave), wn = G::wn(wave);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc.v[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int nsteps = ks_end - ks_begin;
+  if (nsteps <= 0) {
+    __syncthreads();
+    return;
+  }
+  OpDma<__bf16, OA, NPW, 128> da;
+  OpDma<__bf16, OB, NPW, 128> db;
+  da.init(opa, wave, lane);
+  db.init(opb, wave, lane);
+  OpFrag<__bf16, OA, 4, 128> fra;
+  OpFrag<__bf16, OB, 4, 128> frb;
+  fra.init(wm * 64, lane);
+  frb.init(wn * 64, lane);
+  auto fill = [&](int stage, int ks) {
+    const bool live = ks < ks_end;
+    const DmaStep<NPW> sa = da.prep(opa, lds + stage * STB, wave, ks, live);
+    const DmaStep<NPW> sb = db.prep(opb, lds + stage * STB + OPB, wave, ks, live);
+#pragma unroll
+    for (int i = 0; i < NPW; ++i) sa.one(i);
+#pragma unroll
+    for (int i = 0; i < NPW; ++i) sb.one(i);
+  };
+  fill(0, ks_begin);
+  fill(1, ks_begin + 1);
+  int st = 0;
+#pragma unroll 1
+  for (int j = 0; j < nsteps; ++j) {
+    KD_VMCNT(2 * NPW);  // step j has landed, step j + 1 may still fly
+    __syncthreads();
+    const char* a = lds + st * STB;
+    const char* b = a + OPB;
+    u32x4_t fa[2][4], fb[2][4];
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        fb[s][q] = frb.one(b, s, q);
+        fa[s][q] = fra.one(a, s, q);
+      }
+    __builtin_amdgcn_s_waitcnt(0xc07f & ~0x0f00);  // lgkmcnt(0)
+    __syncthreads();  // every wave has read the stage
+    fill(st, ks_begin + j + 2);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+          const int c = (i & 1) ? 3 - jj : jj;
+          acc.v[i][c] = mfma_slot(fa[s][i], fb[s][c], acc.v[i][c], (__bf16*)nullptr);
+        }
+    st ^= 1;
+  }
+  KD_VMCNT(0);
+  __syncthreads();
+}
+
 // ---------------------------------------------------------------- wave ops --
 __device__ __forceinline__ float wave_sum(float x) {
 #pragma unroll

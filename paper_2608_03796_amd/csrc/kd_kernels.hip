@@ -297,16 +297,17 @@ __global__ __launch_bounds__(64) void k_prologue(PrologueArgs a) {
 
 // ------------------------------------------------------- contraction core --
 // One TS x TS tile of the contraction: bf16 operands in 256x256 tiles
-// (gemm_tile), fp32 operands in 128x128 tiles of split bf16 (gemm_f32). LDS
-// bytes: gemm_lds.
+// (gemm_tile) or, for launches of few tiles, in 128x128 tiles (gemm_small);
+// fp32 operands in 128x128 tiles of split bf16 (gemm_f32). LDS bytes: gemm_lds.
 template <typename T, int TS, bool SPREAD, typename OA, typename OB>
 __device__ __forceinline__ void gemm(const OA& a, const OB& b, int kb, int ke, char* lds,
                                      AccTile<TS>& acc) {
   if constexpr (TS == 256) gemm_tile<T, OA, OB, SPREAD>(a, b, kb, ke, lds, acc);
+  else if constexpr (sizeof(T) == 2) gemm_small<OA, OB>(a, b, kb, ke, lds, acc);
   else gemm_f32<OA, OB>(a, b, kb, ke, lds, acc);
 }
 template <typename T, int TS>
-constexpr int gemm_lds = TS == 256 ? kLdsA3 : kLdsF32;
+constexpr int gemm_lds = TS == 256 ? kLdsA3 : sizeof(T) == 2 ? kLdsSmall : kLdsF32;
 
 // Epilogues of the projection kernels stage the fp32 tile in LDS half of its
 // tokens at a time, as [token][vocab] rows of TS floats with a 16-byte-slot
@@ -1248,7 +1249,7 @@ __device__ __forceinline__ void finalize_loss(const float* partials, int n, floa
 // dH_c[t, d] = sum_v dZ[t, v] W[v, d]: A = dZ (K = vocabulary contiguous),
 // B = W read K-major (rows v, columns d); rows of W past V read as zeros. The
 // tiles left over for the last round of workgroups are split along the
-// vocabulary into fp32 partial tiles (see kd_dh_split). With a rowmap, dZ row
+// vocabulary into fp32 partial tiles (see kd_split_rounds). With a rowmap, dZ row
 // t is grad_hidden row rowmap[t] (-1: none), and only the first
 // *nrow - nrow_base rows hold tokens: the tiles are those of these rows.
 struct DhArgs {
@@ -1264,16 +1265,16 @@ struct DhArgs {
   const int* rowmap;
   const int* nrow;
   int nrow_base;
-  KdDhSplit sp;  // without nrow
+  KdRounds sp;  // without nrow
 };
 // the tile rows that hold tokens and the launch's split
 template <typename T, int TS>
-__device__ __forceinline__ KdDhSplit dh_split(const DhArgs& a, int& n, int& TM) {
+__device__ __forceinline__ KdRounds dh_split(const DhArgs& a, int& n, int& TM) {
   n = a.nrow != nullptr ? min(a.rows, __builtin_amdgcn_readfirstlane(*a.nrow) - a.nrow_base) : a.rows;
   n = max(n, 0);
   TM = (n + TS - 1) / TS;
   if (a.nrow == nullptr) return a.sp;
-  return kd_dh_split(TM * a.TN, a.ks_total, kd_units(TS), kd_part_cost(TS, sizeof(T) == 4),
+  return kd_split_rounds(TM * a.TN, a.ks_total, kd_units(TS), kd_part_cost(TS, sizeof(T) == 4),
                      a.max_parts);
 }
 
@@ -1282,7 +1283,7 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dh(DhA
   typedef Geo<TS> G;
   __shared__ __attribute__((aligned(16))) char lds[gemm_lds<T, TS>];
   int n, TM;
-  const KdDhSplit sp = dh_split<T, TS>(a, n, TM);
+  const KdRounds sp = dh_split<T, TS>(a, n, TM);
   const int pid = blockIdx.x;
   int L, slot = -1, kb = 0, ke = a.ks_total;
   if (pid < sp.dp) {
@@ -1373,7 +1374,7 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dh(DhA
 template <typename T, int TS>
 __device__ __forceinline__ void dh_reduce(int block, int blocks, const DhArgs& a) {
   int n, TM;
-  const KdDhSplit sp = dh_split<T, TS>(a, n, TM);
+  const KdRounds sp = dh_split<T, TS>(a, n, TM);
   if (sp.split < 2) return;
   constexpr int Q = TS * TS / 4;  // pieces per tile
   const int total = sp.rem * Q;
@@ -1490,14 +1491,14 @@ __global__ __launch_bounds__(256) void k_tail(TailArgs a) {
 // (loads and stores complete in issue order, so waiting for those loads does
 // not wait for the stores).
 //
-// SPLIT (for a tile count that leaves the last round of the 256 compute units
-// partly filled): blocks [0, nfull) compute the whole tiles of the full
-// rounds (in the XCD-aware order over those), and the tail tiles are split
-// into `split` token ranges, block nfull + split q + s taking range s of tail
-// tile nfull + q and storing its fp32 partial tile (pitch 256) at partial
-// slot split q + s; k_dw_fixup then adds the parts to grad_W in a fixed
-// order, so the last round is split times shorter. Without SPLIT every block
-// computes a whole tile (nfull, split and partial unused).
+// SPLIT (for a tile count that leaves the last round of the compute units
+// partly filled, or few tiles): blocks [0, nfull) compute the whole tiles of
+// the full rounds, and the tiles left over are split into `split` token ranges
+// (kd_split_rounds), neighbours in the order taking the same range of
+// neighbouring tiles; range s of tile nfull + q is stored as an fp32 partial
+// tile (pitch TS) at slot split q + s, and k_dw_fixup adds the parts to grad_W
+// in a fixed order. Without SPLIT every block computes a whole tile (nfull,
+// split and partial unused).
 //
 // With nrow (ignored tokens left out), only the group's first *nrow dZ rows
 // hold tokens: the K range stops there, and the dZ rows past it read as
@@ -1522,7 +1523,9 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dw(con
   } else if (pid < nfull) {
     L = tile_order_xcd(pid, nfull);
   } else {
-    const int q = (pid - nfull) / split, s = (pid - nfull) - q * split;
+    const int rem = TM * TN - nfull;
+    const int o = tile_order_xcd(pid - nfull, rem * split);
+    const int s = o / rem, q = o - s * rem;
     L = nfull + q;
     slot = q * split + s;
     ks0 = (int)((int64_t)nks * s / split);
@@ -1604,8 +1607,8 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dw(con
   }
 }
 
-// The split tail tiles of k_dw: grad_W = (beta ? grad_W : 0) + part 0 + part 1
-// + ... in this order. One thread per 4 features of a vocabulary row of a tail
+// The split tail tiles of k_dw: grad_W = (beta ? grad_W : 0) + (part 0 + part 1
+// + ...), the parts in this order. One thread per 4 features of a vocabulary row of a tail
 // tile (grid: tail tiles x blocks of rows).
 template <int TS>
 __global__ __launch_bounds__(256) void k_dw_fixup(const float* __restrict__ partial, int split,
@@ -1619,10 +1622,11 @@ __global__ __launch_bounds__(256) void k_dw_fixup(const float* __restrict__ part
   tile_at(nfull + q, TM, TN, Geo<TS>::GM, mt, nt);
   const int v = nt * TS + row, d = mt * TS + c4;
   if (v >= V || d >= D) return;
-  f32x4_t sum = beta ? *reinterpret_cast<const f32x4_t*>(gW + (int64_t)v * D + d)
-                     : f32x4_t{0.f, 0.f, 0.f, 0.f};
+  f32x4_t sum = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
   for (int s = 0; s < split; ++s)
     sum += *reinterpret_cast<const f32x4_t*>(partial + ((int64_t)(q * split + s) * TS + row) * TS + c4);
+  if (beta) sum += *reinterpret_cast<const f32x4_t*>(gW + (int64_t)v * D + d);
   *reinterpret_cast<f32x4_t*>(gW + (int64_t)v * D + d) = sum;
 }
 
@@ -1965,7 +1969,8 @@ static int launch_chunk_impl(const KdChunkArgs& a, hipStream_t s) {
 extern "C" int kd_launch_chunk(const KdChunkArgs* a, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (a->dtype != 1) return launch_chunk_impl<float, 128>(*a, s);
-  return launch_chunk_impl<__bf16, 256>(*a, s);
+  return a->tile == 128 ? launch_chunk_impl<__bf16, 128>(*a, s)
+                        : launch_chunk_impl<__bf16, 256>(*a, s);
 }
 
 template <typename T, int TS>
@@ -1987,7 +1992,7 @@ static DhArgs dh_args(const KdDhArgs& a) {
   d.rowmap = a.rowmap;
   d.nrow = a.nrow;
   d.nrow_base = a.nrow_base;
-  d.sp = kd_dh_split(cdiv(a.tokens, TS) * d.TN, d.ks_total, kd_units(TS),
+  d.sp = kd_split_rounds(cdiv(a.tokens, TS) * d.TN, d.ks_total, kd_units(TS),
                      kd_part_cost(TS, sizeof(T) == 4), a.max_parts);
   return d;
 }
@@ -1999,7 +2004,7 @@ static int launch_dh_impl(const KdDhArgs& a, hipStream_t s) {
   int blocks = d.sp.dp + d.sp.rem * d.sp.split;
   if (a.nrow != nullptr)
     for (int tm = cdiv(a.tokens, TS) - 1; tm > 0; --tm) {
-      const KdDhSplit q = kd_dh_split(tm * d.TN, d.ks_total, kd_units(TS),
+      const KdRounds q = kd_split_rounds(tm * d.TN, d.ks_total, kd_units(TS),
                                       kd_part_cost(TS, sizeof(T) == 4), a.max_parts);
       blocks = std::max(blocks, q.dp + q.rem * q.split);
     }
@@ -2013,7 +2018,7 @@ static int launch_dh_impl(const KdDhArgs& a, hipStream_t s) {
 extern "C" int kd_launch_dh(const KdDhArgs* a, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (a->dtype != 1) return launch_dh_impl<float, 128>(*a, s);
-  return launch_dh_impl<__bf16, 256>(*a, s);
+  return a->tile == 128 ? launch_dh_impl<__bf16, 128>(*a, s) : launch_dh_impl<__bf16, 256>(*a, s);
 }
 
 template <typename T, int TS>
@@ -2024,16 +2029,12 @@ static int launch_dw_impl(const KdDwArgs& a, hipStream_t s) {
   constexpr int kThreads = Geo<TS>::kThreads;
   const int TM = cdiv(a.D, TS), TN = cdiv(a.V, TS);
   const int tiles = TM * TN;
-  // a partly filled last round of the 256 compute units is split along the
-  // tokens when the host provides the partial tiles' workspace
-  int nfull = tiles, split = 1;
+  // the last round is split along the tokens when the model says so and the
+  // host provides the partial tiles' workspace
   const int nks = ldt * (int)sizeof(T) / kRowB;
-  if (a.partial != nullptr && tiles > units && tiles % units != 0) {
-    const int tail = tiles % units;
-    split = std::min(kDwMaxSplit, std::min(units / tail, nks));
-    if (split >= 2) nfull = tiles - tail;
-    else split = 1;
-  }
+  const KdRounds sp =
+      kd_split_rounds(tiles, nks, units, kd_part_cost(TS, sizeof(T) == 4), a.max_parts);
+  const int split = sp.split, nfull = split > 1 ? sp.dp : tiles;
   {
     ProfScope ps_(P_DW, 2.0 * (double)a.tokens * (double)a.D * (double)a.V, s);
     if (nfull < tiles)
@@ -2058,7 +2059,7 @@ static int launch_dw_impl(const KdDwArgs& a, hipStream_t s) {
 extern "C" int kd_launch_dw(const KdDwArgs* a, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (a->dtype != 1) return launch_dw_impl<float, 128>(*a, s);
-  return launch_dw_impl<__bf16, 256>(*a, s);
+  return a->tile == 128 ? launch_dw_impl<__bf16, 128>(*a, s) : launch_dw_impl<__bf16, 256>(*a, s);
 }
 
 template <typename T, int DTS>
@@ -2100,7 +2101,8 @@ static int launch_tail_impl(const KdTailArgs& a, hipStream_t s) {
 extern "C" int kd_launch_tail(const KdTailArgs* a, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (a->dtype != 1) return launch_tail_impl<float, 128>(*a, s);
-  return launch_tail_impl<__bf16, 256>(*a, s);
+  return a->dh != nullptr && a->dh->tile == 128 ? launch_tail_impl<__bf16, 128>(*a, s)
+                                                : launch_tail_impl<__bf16, 256>(*a, s);
 }
 
 extern "C" int kd_launch_compact(const KdCompactArgs* a, void* stream) {

@@ -25,6 +25,7 @@ enum { KD_STAGE_PREP = 1, KD_STAGE_CHUNK = 2 };
 
 struct KdChunkArgs {
   int dtype;
+  int tile;                 // tile edge of the contraction (256 or 128; fp32: 128)
   int mode;                 // KD_MODE_*: which half of Algorithm 1 runs
   int stages;               // KD_STAGE_* bits
   int one_projection;       // loss and gradients together (k_logits_dz schedule)
@@ -85,6 +86,7 @@ struct KdChunkArgs {
 // parts of a split launch are added up by the tail)
 struct KdDhArgs {
   int dtype;
+  int tile;                 // tile edge of the contraction (256 or 128; fp32: 128)
   int64_t D, V;
   const void* dZ;           // the group's dZ rows [tokens, ldz]
   int64_t ldz;
@@ -101,42 +103,45 @@ struct KdDhArgs {
 };
 
 // The contractions run in square tiles of 256 (bf16; one workgroup per compute
-// unit) or 128 (fp32; two workgroups per compute unit): the workgroups the chip
-// runs at once.
+// unit) or 128 (fp32, and bf16 launches of few tiles; two workgroups per
+// compute unit): the workgroups the chip runs at once.
 constexpr int kd_units(int64_t tile) { return tile == 256 ? 256 : 512; }
 
-// How dH's tiles run: the tiles of the full rounds whole (`dp` of them), the
-// `rem` tiles left over for the last round each split into `split` ranges of
-// the vocabulary, whose fp32 partial tiles the tail launch adds up. The split
-// is the one with the least time by a model in K steps of a tile: a round
-// costs its longest range plus kDhRound steps (pipeline fill and epilogue), a
-// partial tile its write and read. Splitting only the last round keeps the
-// partial traffic small. Measured, whole calls: 6001 tokens, D = 2560, V =
-// 40001 (240 tiles): 3.26 -> 2.90 ms; 77 tokens, D = 768, V = 32003 (3 tiles):
-// 126 -> 109 us. Evaluated on the device where the
-// number of rows is only known there (ignored tokens left out). At most
-// max_parts partial tiles, and at most two rounds of them (their traffic).
-constexpr float kDhRound = 4.f;
-constexpr int kDhMaxSplit = 64;
-struct KdDhSplit {
+// How the tiles of dH and dW run: those of the full rounds whole (`dp` of them),
+// the `rem` tiles left over for the last round each split into `split` ranges
+// of their K (the vocabulary or the tokens), whose fp32 partial tiles are added
+// up afterwards (dH's by the tail launch, dW's by k_dw_fixup). The split is the
+// one with the least time by a model in K steps of a tile: a round costs its
+// longest range plus kSplitRound steps (pipeline fill and epilogue), a partial
+// tile its write and read, and adding the parts up kSplitRound more. Splitting
+// only the last round keeps the partial traffic small. Whole calls, against
+// splitting every dH tile to fill the rounds: 6001 tokens, D = 2560, V = 40001
+// (240 tiles) 3.26 and 2.90 ms; 77 tokens, D = 768, V = 32003 (3 tiles) 126 and
+// 109 us; dW of few tiles unsplit: 4000 tokens, D = 256, V = 4096 105 and 91
+// us. Evaluated on the device where the number of rows is only known there
+// (ignored tokens left out). At most max_parts partial tiles, and at most two
+// rounds of them (their traffic).
+constexpr float kSplitRound = 4.f;
+constexpr int kSplitMax = 64;
+struct KdRounds {
   int dp, rem, split;
 };
 #ifdef __HIP__
 __host__ __device__
 #endif
-inline KdDhSplit kd_dh_split(int tiles, int ksteps, int units, float part_cost, int max_parts) {
-  KdDhSplit r;
+inline KdRounds kd_split_rounds(int tiles, int ksteps, int units, float part_cost, int max_parts) {
+  KdRounds r;
   r.dp = tiles / units * units;
   r.rem = tiles - r.dp;
   r.split = 1;
   if (r.rem == 0) return r;
-  float best = (float)ksteps + kDhRound;
-  for (int s = 2; s <= kDhMaxSplit; ++s) {
+  float best = (float)ksteps + kSplitRound;
+  for (int s = 2; s <= kSplitMax; ++s) {
     const int parts = r.rem * s;
     if (parts > max_parts || parts > 2 * units || ksteps < 4 * s) break;
     const float t = (float)((parts + units - 1) / units) *
-                        ((float)((ksteps + s - 1) / s) + kDhRound) +
-                    (float)parts * part_cost + kDhRound;
+                        ((float)((ksteps + s - 1) / s) + kSplitRound) +
+                    (float)parts * part_cost + kSplitRound;
     if (t < best) {
       best = t;
       r.split = s;
@@ -145,18 +150,15 @@ inline KdDhSplit kd_dh_split(int tiles, int ksteps, int units, float part_cost, 
   return r;
 }
 // K steps of a tile that one partial tile's write and read cost (a 256 KB
-// partial tile against 1.44 us, a 64 KB one of fp32 against 2 us)
-constexpr float kd_part_cost(int tile, bool) {
-  return tile == 256 ? 0.08f : 0.015f;
+// partial tile against 1.44 us, a 64 KB one against 2 us (fp32) or 0.65 us)
+constexpr float kd_part_cost(int tile, bool f32) {
+  return tile == 256 ? 0.08f : f32 ? 0.015f : 0.045f;
 }
-
-// the largest split of the dW tail tiles' token range; the partial tiles'
-// workspace holds one tile per unit
-constexpr int kDwMaxSplit = 4;
 
 // dW GEMM over the chunks of one group: grad_W (+)= dZ[:tokens]^T H[:tokens]
 struct KdDwArgs {
   int dtype;
+  int tile;                 // tile edge of the contraction (256 or 128; fp32: 128)
   int64_t D, V;
   const void* dZ;           // the group's dZ rows [tokens, ldz]
   int64_t ldz;
@@ -164,7 +166,8 @@ struct KdDwArgs {
   const void* Ht;           // the tail's transposed hidden rows: [D, tokens rounded up to 64]
   int beta;                 // 0 overwrite, 1 accumulate
   float* gW;
-  float* partial;           // workspace of the split tail tiles, or null (no split)
+  float* partial;           // partial tiles of the split last round
+  int max_parts;            // their number (0: no split)
   const int* nrow;          // ignored tokens left out: the dZ rows [0, *nrow) hold tokens;
                             // or null
 };
