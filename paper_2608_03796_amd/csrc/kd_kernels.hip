@@ -1623,7 +1623,7 @@ __global__ __launch_bounds__(256) void k_dw_fixup(const float* __restrict__ part
   const int v = nt * TS + row, d = mt * TS + c4;
   if (v >= V || d >= D) return;
   f32x4_t sum = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
+#pragma unroll kDwMaxSplit
   for (int s = 0; s < split; ++s)
     sum += *reinterpret_cast<const f32x4_t*>(partial + ((int64_t)(q * split + s) * TS + row) * TS + c4);
   if (beta) sum += *reinterpret_cast<const f32x4_t*>(gW + (int64_t)v * D + d);

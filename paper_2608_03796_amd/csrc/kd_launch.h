@@ -155,6 +155,9 @@ constexpr float kd_part_cost(int tile, bool f32) {
   return tile == 256 ? 0.08f : f32 ? 0.015f : 0.045f;
 }
 
+// the most parts of a split dW tile that k_dw_fixup has in flight at a time
+constexpr int kDwMaxSplit = 4;
+
 // dW GEMM over the chunks of one group: grad_W (+)= dZ[:tokens]^T H[:tokens]
 struct KdDwArgs {
   int dtype;
