@@ -81,6 +81,18 @@ int64_t tiles256(int64_t m, int64_t n) { return cdiv(m, 256) * cdiv(n, 256); }
 int proj_tile(const Plan& pl, int64_t n) {
   return pl.eb == 4 || tiles256(pl.V, n) <= 128 ? 128 : 256;
 }
+// The projection's 256x256 tiles over n rows that run whole; the others run as
+// 128x128 tiles in a launch of their own: up to 64 tiles behind full rounds,
+// which would occupy a quarter of the chip for a round's time (512 x 2048 x
+// 37000, 290 tiles: 350 and 336 us; forward only 3000 x 2048 x 33000, 1548
+// tiles: 390 and 378 us; 2000 x 2048 x 50021, 1568 tiles: 1163 and 1158 us).
+// With 128 of them it no longer paid (768 x 2048 x 32768: 360 and 364 us).
+int64_t proj_large(const Plan& pl, int64_t n) {
+  if (proj_tile(pl, n) == 128) return 0;
+  const int64_t t = tiles256(pl.V, n), rem = t % 256;
+  if (t < 256 || rem == 0 || rem > 64) return t;
+  return t - rem;
+}
 int dh_tile(const Plan& pl, int64_t n) {
   return pl.eb == 4 || tiles256(pl.D, n) <= 8 ? 128 : 256;
 }
@@ -194,7 +206,9 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0, bool parts_ok = true) {
   const int64_t c_last = pl.N - (std::max<int64_t>(pl.nchunks, 1) - 1) * pl.c;
   const int64_t g_full = std::min<int64_t>(pl.G * pl.c, pl.N);
   const int64_t g_last = pl.N - (std::max<int64_t>(pl.ngroups, 1) - 1) * pl.G * pl.c;
-  pl.nP = pl.Vp / std::min(proj_tile(pl, pl.c), proj_tile(pl, c_last));
+  const bool small = proj_large(pl, pl.c) < tiles256(pl.V, pl.c) ||
+                     proj_large(pl, c_last) < tiles256(pl.V, c_last);
+  pl.nP = small ? 2 * pl.nVT : pl.nVT;
   size_t t = 0;
   auto take = [&](size_t bytes) {
     const size_t o = align256(t);
@@ -375,7 +389,8 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
   auto chunk_args = [&](int64_t row0, int rcount, int64_t o, int64_t g, int stages) {
     KdChunkArgs a{};
     a.dtype = p->dtype;
-    a.tile = proj_tile(pl, rcount);
+    a.large_tiles = (int)proj_large(pl, rcount);
+    a.nP = (int)pl.nP;
     a.mode = c.mode;
     a.stages = stages;
     a.one_projection = scaled ? 1 : 0;

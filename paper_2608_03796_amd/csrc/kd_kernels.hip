@@ -309,6 +309,42 @@ __device__ __forceinline__ void gemm(const OA& a, const OB& b, int kb, int ke, c
 template <typename T, int TS>
 constexpr int gemm_lds = TS == 256 ? kLdsA3 : sizeof(T) == 2 ? kLdsSmall : kLdsF32;
 
+// The tiles of a projection launch: part [first, first + count) of the order of
+// the projection's TM x TN tiles of 256x256, whole (TS = 256) or as four
+// 128x128 tiles each. Every token has nP (reference, sum) partials, one per
+// 256 or per 128 vocabulary columns.
+struct ProjTiles {
+  int TM, TN, first, count, nP;
+};
+template <int TS>
+__device__ __forceinline__ void proj_tile(const ProjTiles& p, int& m0, int& n0) {
+  int mt, nt;
+  if constexpr (TS == 256) {
+    tile_at(p.first + tile_order_xcd(blockIdx.x, p.count), p.TM, p.TN, 4, mt, nt);
+    m0 = mt * 256;
+    n0 = nt * 256;
+  } else {
+    const int q = tile_order_xcd(blockIdx.x, 4 * p.count);
+    tile_at(p.first + (q >> 2), p.TM, p.TN, 4, mt, nt);
+    m0 = mt * 256 + 128 * (q & 1);
+    n0 = nt * 256 + 128 * ((q >> 1) & 1);
+  }
+}
+// token t's partial of the tile at column m0; `none` completes a 256-column
+// tile's two 128-column partials
+template <int TS>
+__device__ __forceinline__ void put_partial(const ProjTiles& p, float* pm, float* ps, int64_t t,
+                                            int m0, float ref, float sum, float none) {
+  const bool fine = p.nP != p.TM;
+  const int64_t o = t * p.nP + (m0 >> (fine ? 7 : 8));
+  pm[o] = ref;
+  ps[o] = sum;
+  if (TS == 256 && fine) {
+    pm[o + 1] = none;
+    ps[o + 1] = 0.f;
+  }
+}
+
 // Epilogues of the projection kernels stage the fp32 tile in LDS half of its
 // tokens at a time, as [token][vocab] rows of TS floats with a 16-byte-slot
 // swizzle.
@@ -369,7 +405,7 @@ constexpr int kZhCap = (kLdsA3 - 32768 - kZhVal) / 4; // 28656 cells
 template <typename T, int TS>
 __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_logits_lse(const T* __restrict__ W,
                                                             const T* __restrict__ Hc, int D,
-                                                            int V, int rows, int TM, int TN,
+                                                            int V, int rows, ProjTiles tiles,
                                                             float k2, float* part_m,
                                                             float* part_s, int nVT,
                                                             const uint32_t* __restrict__ hits,
@@ -379,18 +415,15 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_logits
                                                             int nrow_base) {
   typedef Geo<TS> G;
   __shared__ __attribute__((aligned(16))) char lds[gemm_lds<T, TS>];
-  int mt, nt;
-  tile_coords(blockIdx.x, TM, TN, G::GM, mt, nt);
-  const int m0 = mt * TS, n0 = nt * TS;
+  int m0, n0;
+  proj_tile<TS>(tiles, m0, n0);
   const int eb = Elt<T>::bytes;
   const int ld = D * eb;
   // with ignored tokens left out only the first *nrow - nrow_base rows hold
   // tokens (as in k_logits_dz)
   int trows = rows;
-  if (nrow != nullptr) {
-    trows = min(rows, __builtin_amdgcn_readfirstlane(*nrow) - nrow_base);
-    if (n0 >= trows) return;
-  }
+  if (nrow != nullptr) trows = min(rows, __builtin_amdgcn_readfirstlane(*nrow) - nrow_base);
+  if (n0 >= trows) return;
   const int mrows = max(0, min(TS, V - m0)), nrows = min(TS, trows - n0);
   AccTile<TS> acc;
   gemm<T, TS, false>(
@@ -542,8 +575,7 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_logits
       float ss = 0.f;
       if (mm != -INFINITY) ss = s1 * fast_exp2(m1 - mm) + s2 * fast_exp2(m2 - mm);
       if (t < rows) {
-        part_m[(int64_t)t * TM + mt] = mm;
-        part_s[(int64_t)t * TM + mt] = ss;
+        put_partial<TS>(tiles, part_m, part_s, t, m0, mm, ss, -INFINITY);
       }
     }
   }
@@ -737,7 +769,7 @@ static_assert(kDzRows<128> + 3 * 512 <= kLdsF32, "dZ epilogue LDS");
 
 template <typename T, int TS>
 __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dz(
-    const T* __restrict__ W, const T* __restrict__ Hc, int D, int V, int rows, int TM, int TN,
+    const T* __restrict__ W, const T* __restrict__ Hc, int D, int V, int rows, ProjTiles tiles,
     float k2, const float* __restrict__ rowL2, const float* __restrict__ rowCoef,
     const float* __restrict__ rowCoefM, const uint32_t* __restrict__ hits,
     const float* __restrict__ hitp, const int* __restrict__ hoff, int K, int nVT, T* dZ,
@@ -745,18 +777,15 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dz(
   typedef Geo<TS> G;
   constexpr int kThreads = G::kThreads, HT = TS / 2;  // HT: tokens staged at a time
   __shared__ __attribute__((aligned(16))) char lds[gemm_lds<T, TS>];
-  int mt, nt;
-  tile_coords(blockIdx.x, TM, TN, G::GM, mt, nt);
-  const int m0 = mt * TS, n0 = nt * TS;
+  int m0, n0;
+  proj_tile<TS>(tiles, m0, n0);
   const int eb = Elt<T>::bytes;
   const int ld = D * eb;
   // with ignored tokens left out only the first *nrow - nrow_base rows hold
   // tokens (as in k_logits_dz; the rows past them have weight 0)
   int trows = rows;
-  if (nrow != nullptr) {
-    trows = min(rows, __builtin_amdgcn_readfirstlane(*nrow) - nrow_base);
-    if (n0 >= trows) return;
-  }
+  if (nrow != nullptr) trows = min(rows, __builtin_amdgcn_readfirstlane(*nrow) - nrow_base);
+  if (n0 >= trows) return;
   const int mrows = max(0, min(TS, V - m0)), nrows = min(TS, trows - n0);
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
   const int wm = G::wm(wave), wn = G::wn(wave);
@@ -921,7 +950,7 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dz(
 // nothing grows with N. Staging and teacher bookkeeping are those of k_dz.
 template <typename T, int TS>
 __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_logits_dz(
-    const T* __restrict__ W, const T* __restrict__ Hc, int D, int V, int rows, int TM, int TN,
+    const T* __restrict__ W, const T* __restrict__ Hc, int D, int V, int rows, ProjTiles tiles,
     float k2, float* __restrict__ part_m, float* __restrict__ part_s, int nVT,
     const uint32_t* __restrict__ hits, const int* __restrict__ hoff, int K, T* dZ, int64_t ldz,
     float* zhit, const float* __restrict__ rowR, int* rowFlag, const int* __restrict__ nrow,
@@ -929,9 +958,8 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_logits
   typedef Geo<TS> G;
   constexpr int kThreads = G::kThreads, HT = TS / 2;  // HT: tokens staged at a time
   __shared__ __attribute__((aligned(16))) char lds[gemm_lds<T, TS>];
-  int mt, nt;
-  tile_coords(blockIdx.x, TM, TN, G::GM, mt, nt);
-  const int m0 = mt * TS, n0 = nt * TS;
+  int m0, n0;
+  proj_tile<TS>(tiles, m0, n0);
   const int eb = Elt<T>::bytes;
   const int ld = D * eb;
   // with ignored tokens left out only the first *nrow - nrow_base rows hold
@@ -939,10 +967,8 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_logits
   // them in the last tile read hidden rows of zeros (stored like the others,
   // with a row factor of 0)
   int trows = rows;
-  if (nrow != nullptr) {
-    trows = min(rows, __builtin_amdgcn_readfirstlane(*nrow) - nrow_base);
-    if (n0 >= trows) return;
-  }
+  if (nrow != nullptr) trows = min(rows, __builtin_amdgcn_readfirstlane(*nrow) - nrow_base);
+  if (n0 >= trows) return;
   const int mrows = max(0, min(TS, V - m0)), nrows = min(TS, trows - n0);
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
   const int wm = G::wm(wave), wn = G::wn(wave);
@@ -1060,8 +1086,7 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_logits
           }
         }
         if (lam == 0) {
-          part_m[(int64_t)t * TM + mt] = ref;
-          part_s[(int64_t)t * TM + mt] = sum;
+          put_partial<TS>(tiles, part_m, part_s, t, m0, ref, sum, ref);
           if (own) rowFlag[t] = 1;
         }
       }
@@ -1133,10 +1158,10 @@ __global__ __launch_bounds__(256) void k_row_finish(
   } else if (r < rows) {
     const float* pm = part_m + (int64_t)r * nVT;
     const float* ps = part_s + (int64_t)r * nVT;
-    // up to 512 vocabulary tiles: the row's partials are loaded into registers
+    // up to 1024 partials per row: they are loaded into registers
     // in one batch, with the row scalars, before any arithmetic (one round of
     // memory latency instead of one per pass); the sums keep the same order
-    constexpr int kRF = 8;
+    constexpr int kRF = 16;
     const bool in_regs = nVT <= 64 * kRF;
     float pmv[kRF], psv[kRF];
     if (in_regs) {
@@ -1852,18 +1877,47 @@ extern "C" int kd_profile_read(kd_kernel_time* out, int max) {
   return w;
 }
 
+// One projection launch: `count` 256x256 tiles from `first` on of the order
+// (see ProjTiles). Vocabulary tiles go up to the padded width: every column of
+// dZ is written.
 template <typename T, int TS>
-static int launch_chunk_impl(const KdChunkArgs& a, hipStream_t s) {
+static void launch_projection(const KdChunkArgs& a, int first, int count, hipStream_t s) {
+  if (count <= 0) return;
   const T* W = static_cast<const T*>(a.W);
   const T* Hc = static_cast<const T*>(a.Hc);
-  constexpr int kThreads = Geo<TS>::kThreads;
-  // vocabulary tiles up to the padded width: every column of dZ is written
-  const int TMv = a.nVT * (kTile / TS), TNt = cdiv(a.rows, TS);
-  const int nbt = cdiv(a.rows, kTile);  // 256-token tiles of the buckets
+  const int TN = cdiv(a.rows, kTile);
+  const ProjTiles t{a.nVT, TN, first, count, a.nP};
+  const dim3 grid(count * (kTile / TS) * (kTile / TS)), block(Geo<TS>::kThreads);
   const float k2 = kLog2e * a.inv_tau;
-  const double gemm_flops = 2.0 * (double)a.rows * (double)a.D * (double)a.V;
+  const double flops = 2.0 * (double)a.rows * (double)a.D * (double)a.V * count / (a.nVT * TN);
+  if (a.one_projection) {
+    ProfScope ps_(P_LOGITS_DZ, flops, s);
+    hipLaunchKernelGGL((k_logits_dz<T, TS>), grid, block, 0, s, W, Hc, (int)a.D, (int)a.V, a.rows,
+                       t, k2, a.part_m, a.part_s, a.nVT, a.hits, a.hoff, a.K,
+                       static_cast<T*>(a.dZ), a.ldz, a.zhit, a.rowR, a.rowFlag, a.nrow,
+                       a.nrow_base);
+  } else if (a.mode != KD_MODE_BWD) {
+    // no recompute follows (forward only, or a fused call that wants no
+    // gradients): z at the teacher entries comes from this GEMM
+    ProfScope ps_(P_LOGITS, flops, s);
+    hipLaunchKernelGGL((k_logits_lse<T, TS>), grid, block, 0, s, W, Hc, (int)a.D, (int)a.V, a.rows,
+                       t, k2, a.part_m, a.part_s, a.nVT, a.hits, a.hoff, a.K, a.zhit, a.nrow,
+                       a.nrow_base);
+  } else {
+    // the backward of the split entry points: the logit recompute from the
+    // saved log Z (Algorithm 1's backward)
+    ProfScope ps_(P_DZ, flops, s);
+    hipLaunchKernelGGL((k_dz<T, TS>), grid, block, 0, s, W, Hc, (int)a.D, (int)a.V, a.rows, t, k2,
+                       a.rowL2, a.rowCoef, a.rowCoefM, a.hits, a.hitp, a.hoff, a.K, a.nVT,
+                       static_cast<T*>(a.dZ), a.ldz, (float*)nullptr, a.nrow, a.nrow_base);
+  }
+}
 
-  const bool fwd = a.mode != KD_MODE_BWD, bwd = a.mode != KD_MODE_FWD;
+template <typename T>
+static int launch_chunk_impl(const KdChunkArgs& a, hipStream_t s) {
+  const int nbt = cdiv(a.rows, kTile);  // 256-token tiles (of the buckets too)
+  const float k2 = kLog2e * a.inv_tau;
+  const bool fwd = a.mode != KD_MODE_BWD;
   if (a.stages & KD_STAGE_PREP) {
     {
       ProfScope ps_(P_PROLOGUE, 0.0, s);
@@ -1911,52 +1965,26 @@ static int launch_chunk_impl(const KdChunkArgs& a, hipStream_t s) {
     }
   }
   if (!(a.stages & KD_STAGE_CHUNK)) return (int)hipGetLastError();
+  // bf16: whole 256x256 tiles, and the order's last ones as 128x128 tiles
+  const int large = sizeof(T) == 2 ? a.large_tiles : 0;
+  if constexpr (sizeof(T) == 2) launch_projection<T, 256>(a, 0, large, s);
+  launch_projection<T, 128>(a, large, a.nVT * nbt - large, s);
   if (a.one_projection) {
-    // loss and gradients together: one projection per chunk (k_logits_dz)
-    // against the reference logit, then the merge of log Z with the row
-    // factors, the fallback rows, the teacher cells and the row losses
+    // the merge of log Z with the row factors, the fallback rows, the teacher
+    // cells and the row losses
+    ProfScope ps_(P_ROW_FINISH, 0.0, s);
+    hipLaunchKernelGGL(k_row_finish<T>, dim3(cdiv(a.rows, kLossRows)), dim3(64 * kLossRows), 0, s,
+                       a.part_m, a.part_s, a.nP, a.nP == a.nVT ? 8 : 7, a.rowFlag,
+                       static_cast<T*>(a.dZ), a.ldz, a.tidx, a.p, a.zhit, a.K, (int)a.V, k2,
+                       a.rowM, a.rowH, a.rowCoef, a.rowCoefM, a.ignore, a.row0, a.rowmap, a.rows,
+                       a.inv_tau, a.rowL2, a.rowFactor, a.loss_per_token, a.block_partial);
+  } else if (fwd) {
     {
-      ProfScope ps_(P_LOGITS_DZ, gemm_flops, s);
-      hipLaunchKernelGGL((k_logits_dz<T, TS>), dim3(TMv * TNt), dim3(kThreads), 0, s, W, Hc, (int)a.D,
-                         (int)a.V, a.rows, TMv, TNt, k2, a.part_m, a.part_s, a.nVT, a.hits,
-                         a.hoff, a.K, static_cast<T*>(a.dZ), a.ldz, a.zhit, a.rowR, a.rowFlag,
-                         a.nrow, a.nrow_base);
+      ProfScope ps_(P_MERGE, 0.0, s);
+      hipLaunchKernelGGL(k_lse_merge, dim3(cdiv(a.rows, 4)), dim3(256), 0, s, a.part_m, a.part_s,
+                         a.rows, a.nP, a.rowL2, a.rowmap);
     }
     {
-      ProfScope ps_(P_ROW_FINISH, 0.0, s);
-      hipLaunchKernelGGL(k_row_finish<T>, dim3(cdiv(a.rows, kLossRows)), dim3(64 * kLossRows), 0,
-                         s, a.part_m, a.part_s, TMv, TS == 256 ? 8 : 7, a.rowFlag,
-                         static_cast<T*>(a.dZ), a.ldz,
-                         a.tidx, a.p, a.zhit, a.K, (int)a.V, k2, a.rowM, a.rowH, a.rowCoef,
-                         a.rowCoefM, a.ignore, a.row0, a.rowmap, a.rows, a.inv_tau, a.rowL2,
-                         a.rowFactor, a.loss_per_token, a.block_partial);
-    }
-  } else {
-    if (fwd) {
-      {
-        ProfScope ps_(P_LOGITS, gemm_flops, s);
-        // no recompute follows (forward only, or a fused call that wants no
-        // gradients): z at the teacher entries comes from this GEMM
-        hipLaunchKernelGGL((k_logits_lse<T, TS>), dim3(TMv * TNt), dim3(kThreads), 0, s, W, Hc,
-                           (int)a.D, (int)a.V, a.rows, TMv, TNt, k2, a.part_m, a.part_s, a.nVT,
-                           a.hits, a.hoff, a.K, a.zhit, a.nrow, a.nrow_base);
-      }
-      {
-        ProfScope ps_(P_MERGE, 0.0, s);
-        hipLaunchKernelGGL(k_lse_merge, dim3(cdiv(a.rows, 4)), dim3(256), 0, s, a.part_m,
-                           a.part_s, a.rows, TMv, a.rowL2, a.rowmap);
-      }
-    }
-    if (bwd && !fwd) {
-      // the backward of the split entry points: the logit recompute from the
-      // saved log Z (Algorithm 1's backward)
-      ProfScope ps_(P_DZ, gemm_flops, s);
-      hipLaunchKernelGGL((k_dz<T, TS>), dim3(TMv * TNt), dim3(kThreads), 0, s, W, Hc, (int)a.D,
-                         (int)a.V, a.rows, TMv, TNt, k2, a.rowL2, a.rowCoef, a.rowCoefM, a.hits,
-                         a.hitp, a.hoff, a.K, a.nVT, static_cast<T*>(a.dZ), a.ldz,
-                         (float*)nullptr, a.nrow, a.nrow_base);
-    }
-    if (fwd) {
       ProfScope ps_(P_ROW_LOSS, 0.0, s);
       hipLaunchKernelGGL(k_row_loss, dim3(cdiv(a.rows, kLossRows)), dim3(64 * kLossRows), 0, s,
                          a.zhit, a.p, a.K, a.rowL2, a.rowM, a.rowH, a.ignore, a.row0, a.rowmap,
@@ -1968,9 +1996,7 @@ static int launch_chunk_impl(const KdChunkArgs& a, hipStream_t s) {
 
 extern "C" int kd_launch_chunk(const KdChunkArgs* a, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (a->dtype != 1) return launch_chunk_impl<float, 128>(*a, s);
-  return a->tile == 128 ? launch_chunk_impl<__bf16, 128>(*a, s)
-                        : launch_chunk_impl<__bf16, 256>(*a, s);
+  return a->dtype == 1 ? launch_chunk_impl<__bf16>(*a, s) : launch_chunk_impl<float>(*a, s);
 }
 
 template <typename T, int TS>

@@ -25,7 +25,8 @@ enum { KD_STAGE_PREP = 1, KD_STAGE_CHUNK = 2 };
 
 struct KdChunkArgs {
   int dtype;
-  int tile;                 // tile edge of the contraction (256 or 128; fp32: 128)
+  int large_tiles;          // bf16: the projection's tiles that run as 256x256 (the first
+                            // of the tile order; the rest as 128x128)
   int mode;                 // KD_MODE_*: which half of Algorithm 1 runs
   int stages;               // KD_STAGE_* bits
   int one_projection;       // loss and gradients together (k_logits_dz schedule)
@@ -69,7 +70,8 @@ struct KdChunkArgs {
   int* rowFlag;             // [rows] a tile fell back to its own max
   float* rowFactor;         // [rows] factor of the row's stored gradient (this
                             // chunk's rows of the group's factor array)
-  float *part_m, *part_s;   // [rows, vocabulary tiles of the contraction]
+  float *part_m, *part_s;   // [rows, nP]
+  int nP;                   // partials per token: nVT, or 2 nVT with 128x128 tiles
   int nVT;
   uint32_t* hits;           // [cdiv(rows, 256) * 256 * K] teacher entries by vocab tile
   float* hitp;              // their p
