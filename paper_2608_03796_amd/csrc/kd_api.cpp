@@ -655,13 +655,10 @@ kd_status kd_scale_grads(const float* grad_loss, const float* grad_hidden_f32,
   if (st != KD_OK) return st;
   st = scale_one(grad_loss, grad_W_f32, w_dtype, grad_W_out, n_W, hip_stream);
   if (st != KD_OK) return st;
-  if (grad_hidden_f32 != nullptr && n_hidden > 0 &&
-      kd_launch_scale(hidden_dtype == KD_BF16, grad_hidden_f32, grad_hidden_out, n_hidden,
-                      grad_loss, hip_stream) != 0)
-    return KD_ERR_DEVICE;
-  if (grad_W_f32 != nullptr && n_W > 0 &&
-      kd_launch_scale(w_dtype == KD_BF16, grad_W_f32, grad_W_out, n_W, grad_loss, hip_stream) != 0)
-    return KD_ERR_DEVICE;
+  const KdScaleArg h{grad_hidden_f32, grad_hidden_out, grad_hidden_f32 != nullptr ? n_hidden : 0,
+                     hidden_dtype == KD_BF16};
+  const KdScaleArg w{grad_W_f32, grad_W_out, grad_W_f32 != nullptr ? n_W : 0, w_dtype == KD_BF16};
+  if (kd_launch_scale(&h, &w, grad_loss, hip_stream) != 0) return KD_ERR_DEVICE;
   return KD_OK;
 }
 

@@ -1413,7 +1413,7 @@ __device__ __forceinline__ void dh_reduce(int block, int blocks, const DhArgs& a
     if (o < 0) continue;
     const float* part = a.partial + (int64_t)q * sp.split * (TS * TS) + row * TS + c;
     f32x4_t v = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
+#pragma unroll 8
     for (int k = 0; k < sp.split; ++k)
       v += *reinterpret_cast<const f32x4_t*>(part + (int64_t)k * TS * TS);
     if (a.rowscale != nullptr) v *= a.rowscale[t];
@@ -1688,14 +1688,16 @@ __global__ __launch_bounds__(kScanThreads) void k_compact_scan(const uint8_t* __
   constexpr int NWV = kScanThreads / 64;
   __shared__ int sc[NWV], all[NWV];
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
-  // runs of a multiple of 16 tokens: aligned when the mask is
-  const int per = ((rows + kScanThreads - 1) / kScanThreads + 15) & ~15;
+  // long runs are a multiple of 16 tokens: aligned when the mask is
+  int per = (rows + kScanThreads - 1) / kScanThreads;
+  if (per > 8) per = (per + 15) & ~15;
   const int b = (int)min((int64_t)rows, (int64_t)tid * per), e = min(rows, b + per);
   const uint8_t* m = ignore + row0;
   const int c = count_zero(m, b, e);
   const int incl = wave_incl_scan(c);
   if (lane == 63) sc[wave] = incl;
-  if (inv_nvalid != nullptr) {
+  const bool count = inv_nvalid != nullptr && rows < N;  // else the group is the whole mask
+  if (count) {
     const int64_t per_all = ((N + kScanThreads - 1) / kScanThreads + 15) & ~(int64_t)15;
     const int64_t b0 = min(N, tid * per_all);
     int n = count_zero(ignore, b0, min(N, b0 + per_all));
@@ -1715,8 +1717,8 @@ __global__ __launch_bounds__(kScanThreads) void k_compact_scan(const uint8_t* __
   if (tid == 0) {
     nrow[0] = total;
     if (inv_nvalid != nullptr) {
-      int n = 0;
-      for (int w = 0; w < NWV; ++w) n += all[w];
+      int n = count ? 0 : total;
+      for (int w = 0; w < (count ? NWV : 0); ++w) n += all[w];
       inv_nvalid[0] = n > 0 ? 1.0f / (float)n : 0.0f;
     }
   }
@@ -1745,13 +1747,21 @@ __global__ void k_check_indices(const int32_t* idx, int64_t N, int K, int64_t V,
 // times the upstream gradient of that mean (Algorithm 1's backward scales G
 // by g; the loss is linear in g, so scaling the finished gradients is the
 // same function). fp32 in; out in fp32 or bf16 (one rounding); in place when
-// x and y are the same fp32 buffer. Each thread handles 8 elements, 16-byte
+// x and y are the same fp32 buffer. Bound by memory (2.36 GB of a 128256 x
+// 3072 grad_W to bf16: 0.47 ms); both gradients share a launch, the first
+// `blocks0` blocks taking the first. Each thread handles 8 elements, 16-byte
 // accesses where the 8 are in range (the buffers are 16-byte aligned).
+struct ScaleArg {
+  const float* x;
+  void* y;
+  int64_t n;
+  int bf16;
+};
 template <typename TO>
-__global__ void k_scale_f32(const float* x, TO* y, int64_t n, const float* __restrict__ g) {
-  const float s = g[0];
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x * 8;
-  for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 8; i < n; i += stride) {
+__device__ __forceinline__ void scale_f32(const float* x, TO* y, int64_t n, float s, int block,
+                                          int blocks) {
+  const int64_t stride = (int64_t)blocks * blockDim.x * 8;
+  for (int64_t i = ((int64_t)block * blockDim.x + threadIdx.x) * 8; i < n; i += stride) {
     if (i + 8 <= n) {
       const f32x4_t a = *reinterpret_cast<const f32x4_t*>(x + i) * s;
       const f32x4_t b = *reinterpret_cast<const f32x4_t*>(x + i + 4) * s;
@@ -1767,6 +1777,17 @@ __global__ void k_scale_f32(const float* x, TO* y, int64_t n, const float* __res
       for (int64_t k = i; k < n; ++k) y[k] = (TO)(x[k] * s);
     }
   }
+}
+__global__ void k_scale(ScaleArg a, ScaleArg b, int blocks0, const float* __restrict__ g) {
+  const float s = g[0];
+  const bool first = (int)blockIdx.x < blocks0;
+  const ScaleArg c = first ? a : b;
+  const int block = first ? blockIdx.x : blockIdx.x - blocks0;
+  const int blocks = first ? blocks0 : gridDim.x - blocks0;
+  if (c.bf16)
+    scale_f32(c.x, static_cast<__bf16*>(c.y), c.n, s, block, blocks);
+  else
+    scale_f32(c.x, static_cast<float*>(c.y), c.n, s, block, blocks);
 }
 
 }  // namespace kd
@@ -2166,19 +2187,15 @@ extern "C" int kd_launch_check_indices(const int32_t* idx, int64_t N, int K, int
   return (int)hipStreamSynchronize(s);
 }
 
-// y = g x for the gradients (see k_scale_f32): x fp32, y fp32 (out_bf16 = 0)
-// or bf16 (out_bf16 = 1)
-extern "C" int kd_launch_scale(int out_bf16, const float* x, void* y, int64_t n, const float* g,
+// y = g x for one or two gradients (see k_scale): a count of 0 skips one
+extern "C" int kd_launch_scale(const KdScaleArg* a, const KdScaleArg* b, const float* g,
                                void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (n <= 0) return 0;
-  const int64_t blocks = std::min<int64_t>((n + 2047) / 2048, 8192);
-  if (out_bf16)
-    hipLaunchKernelGGL(k_scale_f32<__bf16>, dim3((int)blocks), dim3(256), 0, s, x,
-                       static_cast<__bf16*>(y), n, g);
-  else
-    hipLaunchKernelGGL(k_scale_f32<float>, dim3((int)blocks), dim3(256), 0, s, x,
-                       static_cast<float*>(y), n, g);
+  auto arg = [](const KdScaleArg* q) { return ScaleArg{q->x, q->y, q->n, q->out_bf16}; };
+  auto blocks = [](int64_t n) { return (int)std::min<int64_t>((n + 2047) / 2048, 8192); };
+  const int ba = blocks(a->n), bb = blocks(b->n);
+  if (ba + bb == 0) return 0;
+  hipLaunchKernelGGL(k_scale, dim3(ba + bb), dim3(256), 0, s, arg(a), arg(b), ba, g);
   return (int)hipGetLastError();
 }
 

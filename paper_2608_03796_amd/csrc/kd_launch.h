@@ -209,6 +209,14 @@ struct KdCompactArgs {
   float* inv_nvalid;        // or null
 };
 
+// out = g x for one gradient: x fp32, out fp32 or bf16, n elements (0: nothing)
+struct KdScaleArg {
+  const float* x;
+  void* y;
+  int64_t n;
+  int out_bf16;
+};
+
 extern "C" {
 int kd_launch_fill(float* p, int64_t n, void* stream);  // n zeros
 int kd_launch_chunk(const KdChunkArgs* a, void* stream);
@@ -216,8 +224,7 @@ int kd_launch_dh(const KdDhArgs* a, void* stream);
 int kd_launch_dw(const KdDwArgs* a, void* stream);
 int kd_launch_compact(const KdCompactArgs* a, void* stream);
 int kd_launch_tail(const KdTailArgs* a, void* stream);
-int kd_launch_scale(int out_bf16, const float* x, void* y, int64_t n, const float* g,
-                    void* stream);
+int kd_launch_scale(const KdScaleArg* a, const KdScaleArg* b, const float* g, void* stream);
 // the current device's scratch address (hipGetSymbolAddress on first use)
 int kd_scratch_get(void** ptr);
 // nonzero: the calling thread's launches record no profiling events
