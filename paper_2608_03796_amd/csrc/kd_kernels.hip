@@ -92,6 +92,8 @@ constexpr float kRefGapScale = 1099511627776.f;  // 2^kRefGap
 // i.e. 2^-102 below the reference logit, flush to zero
 constexpr float kRefShift = 24.f;
 
+constexpr int prologue_lds(int K) { return 4 * prologue_hash_slots(K) + 8 * K; }
+
 struct PrologueArgs {
   const int32_t* tidx;
   int32_t* tidx_out;
@@ -118,16 +120,21 @@ struct PrologueArgs {
   float *lpt, *logz_out;
 };
 
+// LDS accesses of one wave stay in order: only the compiler is held back
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// row r by the calling wave, with prologue_lds(K) bytes of LDS of its own
 template <typename T>
-__global__ __launch_bounds__(64) void k_prologue(PrologueArgs a) {
-  extern __shared__ __attribute__((aligned(16))) char psm[];
+__device__ __forceinline__ void prologue_row(const PrologueArgs& a, int r, char* lds) {
   const int K = a.K, V = a.V;
   const int S = prologue_hash_slots(K);
-  int* hset = reinterpret_cast<int*>(psm);
+  int* hset = reinterpret_cast<int*>(lds);
   int* sidx = hset + S;
   float* sp = reinterpret_cast<float*>(sidx + K);
   const int lane = threadIdx.x & 63;
-  const int r = blockIdx.x;
   if (r >= a.rows) return;
   int64_t t = a.row0 + r;
   if (a.rowmap != nullptr) {
@@ -185,7 +192,7 @@ __global__ __launch_bounds__(64) void k_prologue(PrologueArgs a) {
     logs = logf(s);
     scale = a.inv_tau;
   }
-  __syncthreads();  // the cleared hash set
+  wave_lds_sync();  // the cleared hash set
   // p, and the row's indices into the hash set: an insertion that finds its
   // own index already there has seen a repeat (invalid indices are skipped
   // by every kernel and take no part)
@@ -210,7 +217,7 @@ __global__ __launch_bounds__(64) void k_prologue(PrologueArgs a) {
     }
   }
   const bool any_repeat = __builtin_amdgcn_ballot_w64(seen) != 0ull;
-  __syncthreads();  // sidx and sp of the whole row
+  wave_lds_sync();  // sidx and sp of the whole row
   float h = 0.f;
   float best = -INFINITY;  // the valid entry with the largest teacher logit, the first of equals
   int bk = K;
@@ -629,37 +636,55 @@ constexpr int kBucketRegs = 32;
 constexpr int kBucketBatch = 8;  // entries per thread whose loads are in flight together
 constexpr int kMaxVT = 4096;     // vocabulary tiles (V <= 2^20)
 
-__global__ __launch_bounds__(kBucketThreads) void k_bucket(const int32_t* __restrict__ tidx,
-                                                           const float* __restrict__ p, int rows,
-                                                           int K, int V, int nVT, uint32_t* hits,
-                                                           float* hitp, int* hoff, float* zhit) {
+struct BucketArgs {
+  const int32_t* tidx;  // [rows, K], or with rowmap the full [N, K] indexed by its tokens
+  const int* rowmap;    // or null
+  const float* p;
+  int rows, K, V, nVT;
+  uint32_t* hits;
+  float* hitp;
+  int* hoff;
+  float* zhit;
+};
+
+__device__ __forceinline__ void bucket_tile(const BucketArgs& a, int block) {
+  const int rows = a.rows, K = a.K, V = a.V, nVT = a.nVT;
+  uint32_t* hits = a.hits;
+  float* hitp = a.hitp;
   __shared__ int cnt[kMaxVT];
   __shared__ int cur[kMaxVT];
   __shared__ int wsum[kBucketThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
-  const int t0 = blockIdx.x * kTile;
+  const int t0 = block * kTile;
   const int total = min(kTile, rows - t0) * K;
-  const int64_t seg = (int64_t)blockIdx.x * kTile * K;
+  const int64_t seg = (int64_t)block * kTile * K;
   // entry e of the tile is element t0 K + e of the row-major [rows, K] arrays
-  const int32_t* ti = tidx + (int64_t)t0 * K;
-  const float* pt = p + (int64_t)t0 * K;
-  float* zt = zhit + (int64_t)t0 * K;
+  const float* pt = a.p + (int64_t)t0 * K;
+  float* zt = a.zhit + (int64_t)t0 * K;
   const float invK = 1.0f / (float)K;
-  auto put = [&](int e, int v, int pos) {
-    // token = e / K (exact: e < 2^20, and (e + 0.5) / K stays >= 1/(2K)
-    // away from an integer while the float product errs by < 2^-12)
-    const int tl = (int)(((float)e + 0.5f) * invK);
+  // token = e / K (exact: e < 2^20, and (e + 0.5) / K stays >= 1/(2K)
+  // away from an integer while the float product errs by < 2^-12)
+  auto token = [&](int e) { return (int)(((float)e + 0.5f) * invK); };
+  auto index = [&](int e) -> int {
+    if (a.rowmap == nullptr) return a.tidx[(int64_t)t0 * K + e];
+    const int tl = token(e), tok = a.rowmap[t0 + tl];
+    return tok < 0 ? -1 : a.tidx[(int64_t)tok * K + (e - tl * K)];
+  };
+  auto put = [&](int e, int v, int pos, float pk) {
+    const int tl = token(e);
     const int k = e - tl * K;
     hits[seg + pos] = (uint32_t)tl | ((uint32_t)(v & 255) << 8) | ((uint32_t)k << 16);
-    if (hitp != nullptr) hitp[seg + pos] = pt[e];
+    if (hitp != nullptr) hitp[seg + pos] = pk;
   };
   const bool in_regs = total <= kBucketThreads * kBucketRegs;
   int v[kBucketRegs], rank[kBucketRegs];
+  float pv[kBucketRegs];
   if (in_regs) {
 #pragma unroll
     for (int u = 0; u < kBucketRegs; ++u) {
       const int e = u * kBucketThreads + tid;
-      v[u] = e < total ? ti[e] : -1;
+      v[u] = e < total ? index(e) : -1;
+      pv[u] = hitp != nullptr && e < total ? pt[e] : 0.f;
     }
   }
   for (int b = tid; b < nVT; b += kBucketThreads) cnt[b] = 0;
@@ -681,7 +706,7 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket(const int32_t* __rest
 #pragma unroll
       for (int u = 0; u < kBucketBatch; ++u) {
         const int e = base + u * kBucketThreads + tid;
-        w[u] = e < total ? ti[e] : 0;
+        w[u] = e < total ? index(e) : 0;
       }
 #pragma unroll
       for (int u = 0; u < kBucketBatch; ++u) {
@@ -712,7 +737,7 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket(const int32_t* __rest
   }
   __syncthreads();
   int off = wsum[wave] + incl - run;
-  int* ho = hoff + (int64_t)blockIdx.x * (nVT + 1);
+  int* ho = a.hoff + (int64_t)block * (nVT + 1);
   for (int q = 0; q < R; ++q) {
     const int b = tid * R + q;
     if (b < nVT) {
@@ -728,24 +753,55 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket(const int32_t* __rest
     for (int u = 0; u < kBucketRegs; ++u) {
       if (u * kBucketThreads >= total) break;
       if ((unsigned)v[u] < (unsigned)V)
-        put(u * kBucketThreads + tid, v[u], cur[v[u] >> 8] + rank[u]);
+        put(u * kBucketThreads + tid, v[u], cur[v[u] >> 8] + rank[u], pv[u]);
     }
     return;
   }
   for (int base = 0; base < total; base += kBucketThreads * kBucketBatch) {
     int w[kBucketBatch];
+    float pw[kBucketBatch];
 #pragma unroll
     for (int u = 0; u < kBucketBatch; ++u) {
       const int e = base + u * kBucketThreads + tid;
-      w[u] = e < total ? ti[e] : -1;
+      w[u] = e < total ? index(e) : -1;
+      pw[u] = hitp != nullptr && e < total ? pt[e] : 0.f;
     }
 #pragma unroll
     for (int u = 0; u < kBucketBatch; ++u) {
       const int e = base + u * kBucketThreads + tid;
       if (e >= total || (unsigned)w[u] >= (unsigned)V) continue;
-      put(e, w[u], atomicAdd(&cur[w[u] >> 8], 1));
+      put(e, w[u], atomicAdd(&cur[w[u] >> 8], 1), pw[u]);
     }
   }
+}
+
+__global__ __launch_bounds__(kBucketThreads) void k_bucket(BucketArgs a) {
+  bucket_tile(a, blockIdx.x);
+}
+
+// The prologue of a row per wave and, in the first `nb` workgroups (K <=
+// kPrepMaxK), the buckets: they run on a few compute units for as long as the
+// prologue does on the others. The buckets then read the caller's indices, so
+// a repeated index of a row gets an entry per repeat: harmless where entries
+// only record z (the later ones have p = 0), but not for the separate
+// backward, whose entries patch their cells: it runs k_bucket after the
+// prologue. 512 tokens, K = 64: 20.2 us for both, now 13.1 us.
+constexpr int kPrepMaxK = 128;
+template <typename T>
+__global__ __launch_bounds__(kBucketThreads) void k_prep(PrologueArgs a, BucketArgs b, int nb) {
+  constexpr int kRowLds = prologue_lds(kPrepMaxK), NWV = kBucketThreads / 64;
+  __shared__ __attribute__((aligned(16))) char lds[NWV * kRowLds];
+  if ((int)blockIdx.x < nb) {
+    bucket_tile(b, blockIdx.x);
+    return;
+  }
+  const int wave = wave_id();
+  prologue_row<T>(a, ((int)blockIdx.x - nb) * NWV + wave, lds + wave * kRowLds);
+}
+template <typename T>
+__global__ __launch_bounds__(64) void k_prologue(PrologueArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char psm[];
+  prologue_row<T>(a, blockIdx.x, psm);
 }
 
 // --------------------------------------- logit recompute + dZ epilogue -----
@@ -1111,7 +1167,11 @@ __global__ void k_row_loss(const float* zhit, const float* p, int K, const float
   const int tok = (rowmap != nullptr && r < rows) ? rowmap[r] : 0;
   if (r < rows && tok >= 0) {
     float c = 0.f;
-    for (int k = lane; k < K; k += 64) c += p[(int64_t)r * K + k] * zhit[(int64_t)r * K + k];
+    for (int k = lane; k < K; k += 64) {
+      const float pk = p[(int64_t)r * K + k];
+      // (a repeated index has p = 0 and a z that need not be finite)
+      if (pk != 0.f) c += pk * zhit[(int64_t)r * K + k];
+    }
     c = wave_sum(c);
     const bool valid = rowmap != nullptr || ignore == nullptr || ignore[row0 + r] == 0;
     l = valid ? rowH[r] - c * inv_tau + rowM[r] * rowL2[r] * kLn2 : 0.f;
@@ -1231,7 +1291,7 @@ __global__ __launch_bounds__(256) void k_row_finish(
     for (int k = lane; k < K; k += 64) {
       const int64_t e = (int64_t)r * K + k;
       const float pk = p[e], z = zhit[e];
-      c += pk * z;
+      if (pk != 0.f) c += pk * z;
       const int v = tidx[e];
       if ((unsigned)v < (unsigned)V) {
         const float g = cm * fast_exp2(z * k2 - L2) - cf * pk;
@@ -1782,6 +1842,7 @@ __global__ void k_scale(ScaleArg a, ScaleArg b, int blocks0, const float* __rest
   const float s = g[0];
   const bool first = (int)blockIdx.x < blocks0;
   const ScaleArg c = first ? a : b;
+  if (s == 1.f && c.x == c.y) return;  // in place by 1: the values stay
   const int block = first ? blockIdx.x : blockIdx.x - blocks0;
   const int blocks = first ? blocks0 : gridDim.x - blocks0;
   if (c.bf16)
@@ -1806,11 +1867,11 @@ static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 // ------------------------------------------------- event instrumentation ----
 namespace {
 enum ProfKind {
-  P_PROLOGUE, P_BUCKET, P_LOGITS, P_MERGE, P_DZ, P_ROW_LOSS, P_DH, P_DW, P_TAIL, P_FILL,
+  P_PREP, P_LOGITS, P_MERGE, P_DZ, P_ROW_LOSS, P_DH, P_DW, P_TAIL, P_FILL,
   P_LOGITS_DZ, P_ROW_FINISH, P_DW_FIXUP, P_COMPACT, P_NKINDS
 };
 const char* const kProfNames[P_NKINDS] = {
-    "prologue", "bucket", "logits_lse", "lse_merge", "dz", "row_loss", "dh", "dw", "tail", "fill",
+    "prep", "logits_lse", "lse_merge", "dz", "row_loss", "dh", "dw", "tail", "fill",
     "logits_dz", "row_finish", "dw_fixup", "compact"};
 struct ProfRec {
   int kind;
@@ -1941,7 +2002,7 @@ static int launch_chunk_impl(const KdChunkArgs& a, hipStream_t s) {
   const bool fwd = a.mode != KD_MODE_BWD;
   if (a.stages & KD_STAGE_PREP) {
     {
-      ProfScope ps_(P_PROLOGUE, 0.0, s);
+      ProfScope ps_(P_PREP, 0.0, s);
       PrologueArgs p{};
       p.tidx = a.tidx_in;
       p.tidx_out = a.tidx;
@@ -1976,13 +2037,26 @@ static int launch_chunk_impl(const KdChunkArgs& a, hipStream_t s) {
       p.gh_row_bytes = a.D * (a.gh_f32 ? 4 : (int64_t)sizeof(T));
       p.lpt = a.lpt_full;
       p.logz_out = a.logz_out;
-      hipLaunchKernelGGL(k_prologue<T>, dim3(a.rows), dim3(64),
-                         (size_t)4 * prologue_hash_slots(a.K) + (size_t)8 * a.K, s, p);
-    }
-    {
-      ProfScope ps_(P_BUCKET, 0.0, s);
-      hipLaunchKernelGGL(k_bucket, dim3(nbt), dim3(kBucketThreads), 0, s, a.tidx, a.p, a.rows,
-                         a.K, (int)a.V, a.nVT, a.hits, fwd ? nullptr : a.hitp, a.hoff, a.zhit);
+      BucketArgs b{};
+      b.tidx = a.tidx;
+      b.p = a.p;
+      b.rows = a.rows;
+      b.K = a.K;
+      b.V = (int)a.V;
+      b.nVT = a.nVT;
+      b.hits = a.hits;
+      b.hitp = fwd ? nullptr : a.hitp;
+      b.hoff = a.hoff;
+      b.zhit = a.zhit;
+      if (fwd && a.K <= kPrepMaxK) {
+        b.tidx = a.rowmap != nullptr ? a.tidx_in : a.tidx_in + a.row0 * a.K;
+        b.rowmap = a.rowmap;
+        hipLaunchKernelGGL(k_prep<T>, dim3(nbt + cdiv(a.rows, kBucketThreads / 64)),
+                           dim3(kBucketThreads), 0, s, p, b, nbt);
+      } else {
+        hipLaunchKernelGGL(k_prologue<T>, dim3(a.rows), dim3(64), (size_t)prologue_lds(a.K), s, p);
+        hipLaunchKernelGGL(k_bucket, dim3(nbt), dim3(kBucketThreads), 0, s, b);
+      }
     }
   }
   if (!(a.stages & KD_STAGE_CHUNK)) return (int)hipGetLastError();
