@@ -187,8 +187,8 @@ __device__ void gemm_f32_plain(const OA& opa, const OB& opb, int ks_begin, int k
 // workgroup's split, writes and barriers is the second workgroup on the
 // compute unit (three do not fit the registers without spills: 40% slower).
 // LDS traffic per step and pair of workgroups is 288 KiB (2304 clocks at 128
-// B) against 3072 clocks of MFMA. Measured at 2048 x 1024 x 32000 (dH): 647 us,
-// 207 TFLOP/s, against 918 us with fp32 MFMAs in 256x256 tiles; counters: MFMA
+// B) against 3072 clocks of MFMA. Measured at 2048 x 1024 x 32000 (dH): 631 us,
+// 213 TFLOP/s, against 918 us with fp32 MFMAs in 256x256 tiles; counters: MFMA
 // pipes 63% busy at 1.89 GHz, no bank conflicts. Splitting the next step's
 // values between the current step's MFMAs was 3% slower; the wave priority
 // during the MFMAs gives 1-2%. Ends with a barrier.

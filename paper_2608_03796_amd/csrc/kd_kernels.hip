@@ -4,10 +4,12 @@
 //              compact_scan      -> the group's tokens that are not ignored (row map,
 //                                   count); the kernels below skip the rows past
 //                                   them. The first one also counts N_valid.
-// Per chunk:   prologue          -> p, M, H, g/tau                 (§3.2, Eq. 2 terms),
-//                                   the row's hidden row copied next to the others'
-//                                   (with a mask), the reference logit R
-//              bucket            -> teacher entries grouped by vocabulary tile
+// Per chunk:   prep              -> per row p, M, H, g/tau          (§3.2, Eq. 2 terms),
+//                                   its hidden row copied next to the others'
+//                                   (with a mask), the reference logit R; teacher
+//                                   entries grouped by vocabulary tile (in launches
+//                                   of their own, prologue and bucket, for K > 128
+//                                   and for the separate backward)
 //   loss and gradients together (one projection per chunk):
 //              logits_dz         -> (reference, sum-exp) partials per (token, vocab
 //                                   tile), z at the teacher entries, dZ'' = 2^(y - R)
@@ -25,7 +27,7 @@
 //
 // A kernel of a few microseconds of work occupies the stream for about 4.7 us,
 // so the small passes share launches where nothing orders them: a step of one
-// group is 7 launches (8 with a mask), which were 11 (14).
+// group is 6 launches (7 with a mask), which were 11 (14).
 #include "kd_device.h"
 #include "kd_f32.h"
 #include <type_traits>

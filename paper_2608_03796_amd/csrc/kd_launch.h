@@ -123,7 +123,9 @@ constexpr int kd_units(int64_t tile) { return tile == 256 ? 256 : 512; }
 // us. Evaluated on the device where the number of rows is only known there
 // (ignored tokens left out). At most max_parts partial tiles, and at most two
 // rounds of them (their traffic).
-constexpr float kSplitRound = 4.f;
+// The model is in integers (1024ths of a K step), so that host and device choose
+// alike.
+constexpr int kSplitRound = 4 * 1024;
 constexpr int kSplitMax = 64;
 struct KdRounds {
   int dp, rem, split;
@@ -131,19 +133,18 @@ struct KdRounds {
 #ifdef __HIP__
 __host__ __device__
 #endif
-inline KdRounds kd_split_rounds(int tiles, int ksteps, int units, float part_cost, int max_parts) {
+inline KdRounds kd_split_rounds(int tiles, int ksteps, int units, int part_cost, int max_parts) {
   KdRounds r;
   r.dp = tiles / units * units;
   r.rem = tiles - r.dp;
   r.split = 1;
   if (r.rem == 0) return r;
-  float best = (float)ksteps + kSplitRound;
+  int best = ksteps * 1024 + kSplitRound;
   for (int s = 2; s <= kSplitMax; ++s) {
     const int parts = r.rem * s;
     if (parts > max_parts || parts > 2 * units || ksteps < 4 * s) break;
-    const float t = (float)((parts + units - 1) / units) *
-                        ((float)((ksteps + s - 1) / s) + kSplitRound) +
-                    (float)parts * part_cost + kSplitRound;
+    const int t = (parts + units - 1) / units * ((ksteps + s - 1) / s * 1024 + kSplitRound) +
+                  parts * part_cost + kSplitRound;
     if (t < best) {
       best = t;
       r.split = s;
@@ -151,11 +152,9 @@ inline KdRounds kd_split_rounds(int tiles, int ksteps, int units, float part_cos
   }
   return r;
 }
-// K steps of a tile that one partial tile's write and read cost (a 256 KB
-// partial tile against 1.44 us, a 64 KB one against 2 us (fp32) or 0.65 us)
-constexpr float kd_part_cost(int tile, bool f32) {
-  return tile == 256 ? 0.08f : f32 ? 0.015f : 0.045f;
-}
+// 1024ths of a tile's K step that one partial tile's write and read cost (a 256
+// KB partial tile against 1.44 us, a 64 KB one against 2 us (fp32) or 0.65 us)
+constexpr int kd_part_cost(int tile, bool f32) { return tile == 256 ? 82 : f32 ? 15 : 46; }
 
 // the most parts of a split dW tile that k_dw_fixup has in flight at a time
 constexpr int kDwMaxSplit = 4;
