@@ -7,6 +7,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <numeric>
 
 #include "../../include/kdtopk.h"
 #include "kd_launch.h"
@@ -46,7 +47,8 @@ struct Plan {
   bool prep_per_group; // rows prepared once per group (chunks of whole 256-token tiles)
   int64_t ng;          // rows of the per-row arrays: the group's, or one chunk's (padded)
   int64_t ksteps;      // K steps of dH (the vocabulary)
-  int dh_max_parts, dw_max_parts;  // partial tiles of the split last rounds it holds
+  int64_t dh_rows[2];  // the row counts dH runs on: of the full and the last chunk or group
+  size_t dh_bytes, dw_bytes;  // partial tiles of their split last rounds it holds
   size_t off_misc, off_p, off_tidx, off_rows, off_pm, off_ps, off_hits, off_hitp, off_hoff, off_zhit,
       off_lossp, off_dz, off_fac, off_ht, off_rowmap, off_dhs, off_dwp, total;
 };
@@ -114,11 +116,14 @@ KdRounds dh_split(const Plan& pl, int64_t n, int max_parts = 1 << 20) {
 // The most partial tiles dH over 1..n rows of the tile of n rows needs (fewer
 // rows hold tokens when ignored ones are left out).
 int dh_parts(const Plan& pl, int64_t n) {
-  const int ts = dh_tile(pl, n);
+  const int ts = dh_tile(pl, n), units = kd_units(ts);
+  const int64_t tm_max = cdiv(n, ts), td = cdiv(pl.D, ts);
+  // the tiles left over for the last round repeat with this many tile rows
+  const int64_t period = units / std::gcd(td, (int64_t)units);
   int parts = 0;
-  for (int64_t tm = cdiv(n, ts); tm > 0; --tm) {
-    const KdRounds s = kd_split_rounds((int)(tm * cdiv(pl.D, ts)), (int)pl.ksteps, kd_units(ts),
-                                    kd_part_cost(ts, pl.eb == 4), 1 << 20);
+  for (int64_t tm = tm_max; tm > std::max<int64_t>(0, tm_max - period); --tm) {
+    const KdRounds s = kd_split_rounds((int)(tm * td), (int)pl.ksteps, units,
+                                       kd_part_cost(ts, pl.eb == 4), 1 << 20);
     if (s.split > 1) parts = std::max(parts, s.rem * s.split);
   }
   return parts;
@@ -132,9 +137,9 @@ int dw_parts(const Plan& pl, int64_t n) {
   return s.split > 1 ? s.rem * s.split : 0;
 }
 
-// g_max > 0 caps the chunks per dW group, parts_ok = false leaves the last rounds of dH
-// and dW unsplit (see plan_within).
-Plan make_plan(const kd_problem* p, int64_t g_max = 0, bool parts_ok = true) {
+// The plan without the partial tiles of split last rounds; g_max > 0 caps the
+// chunks per dW group (see plan_within).
+Plan base_plan(const kd_problem* p, int64_t g_max = 0) {
   Plan pl{};
   pl.N = p->N;
   pl.D = p->D;
@@ -194,18 +199,15 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0, bool parts_ok = true) {
   pl.prep_per_group = pl.G > 1 && pl.c % kTile == 0;
   pl.ng = pl.prep_per_group ? pl.G * pl.c : pl.cp;
   pl.dh_per_group = dh_split(pl, pl.c).split > 1;
-  int64_t dh_rows[2];  // the row counts dH runs on: full and last chunk or group
   if (pl.dh_per_group) {
-    dh_rows[0] = std::min<int64_t>(pl.G * pl.c, pl.N);
-    dh_rows[1] = pl.N - (pl.ngroups - 1) * pl.G * pl.c;
+    pl.dh_rows[0] = std::min<int64_t>(pl.G * pl.c, pl.N);
+    pl.dh_rows[1] = pl.N - (pl.ngroups - 1) * pl.G * pl.c;
   } else {
-    dh_rows[0] = pl.c;
-    dh_rows[1] = pl.N - (pl.nchunks - 1) * pl.c;
+    pl.dh_rows[0] = pl.c;
+    pl.dh_rows[1] = pl.N - (pl.nchunks - 1) * pl.c;
   }
-  // rows of the last chunk and group, whose tiles may differ from the others'
+  // rows of the last chunk, whose tiles may differ from the others'
   const int64_t c_last = pl.N - (std::max<int64_t>(pl.nchunks, 1) - 1) * pl.c;
-  const int64_t g_full = std::min<int64_t>(pl.G * pl.c, pl.N);
-  const int64_t g_last = pl.N - (std::max<int64_t>(pl.ngroups, 1) - 1) * pl.G * pl.c;
   const bool small = proj_large(pl, pl.c) < tiles256(pl.V, pl.c) ||
                      proj_large(pl, c_last) < tiles256(pl.V, c_last);
   pl.nP = small ? 2 * pl.nVT : pl.nVT;
@@ -234,28 +236,33 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0, bool parts_ok = true) {
   pl.off_ht = take((size_t)pl.D * rup(pl.G * pl.c, 64) * pl.eb);
   // the token of each of those rows
   pl.off_rowmap = take((size_t)pl.G * pl.c * 4);
-  if (parts_ok) {
-    size_t bytes = 0;
-    for (int64_t r : dh_rows) {
-      if (r <= 0) continue;
-      const int parts = dh_parts(pl, r), ts = dh_tile(pl, r);
-      pl.dh_max_parts = std::max(pl.dh_max_parts, parts);
-      bytes = std::max(bytes, (size_t)parts * ts * ts * 4);
-    }
-    pl.off_dhs = bytes > 0 ? take(bytes) : 0;
-  }
-  // partial tiles of dW's split last round
-  if (parts_ok) {
-    size_t bytes = 0;
-    for (int64_t r : {g_full, g_last}) {
-      if (r <= 0) continue;
-      const int parts = dw_parts(pl, r), ts = dw_tile(pl, r);
-      pl.dw_max_parts = std::max(pl.dw_max_parts, parts);
-      bytes = std::max(bytes, (size_t)parts * ts * ts * 4);
-    }
-    pl.off_dwp = bytes > 0 ? take(bytes) : 0;
-  }
   pl.total = align256(t);
+  return pl;
+}
+
+// Adds the partial tiles of dH's and dW's split last rounds.
+void add_parts(Plan* pl) {
+  for (int i = 0; i < 2; ++i) {
+    const int64_t r = pl->dh_rows[i];
+    if (r <= 0 || (i == 1 && r == pl->dh_rows[0])) continue;
+    const int ts = dh_tile(*pl, r);
+    pl->dh_bytes = std::max(pl->dh_bytes, (size_t)dh_parts(*pl, r) * ts * ts * 4);
+  }
+  const int64_t g_full = std::min<int64_t>(pl->G * pl->c, pl->N);
+  const int64_t g_last = pl->N - (std::max<int64_t>(pl->ngroups, 1) - 1) * pl->G * pl->c;
+  for (int64_t r : {g_full, g_last}) {
+    if (r <= 0) continue;
+    const int ts = dw_tile(*pl, r);
+    pl->dw_bytes = std::max(pl->dw_bytes, (size_t)dw_parts(*pl, r) * ts * ts * 4);
+  }
+  pl->off_dhs = pl->total;
+  pl->off_dwp = align256(pl->off_dhs + pl->dh_bytes);
+  pl->total = align256(pl->off_dwp + pl->dw_bytes);
+}
+
+Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
+  Plan pl = base_plan(p, g_max);
+  add_parts(&pl);
   return pl;
 }
 
@@ -264,13 +271,36 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0, bool parts_ok = true) {
 // tiles; false if the workspace of one chunk per group does not fit.
 // The partials of 128-column vocabulary tiles above those of 256-column ones
 // are not counted: kd_scratch_slack holds them.
+// The group is found by bisection, first of the plan without its partial tiles
+// (a microsecond a step), then of the whole plan (2 to 15): the size grows with
+// the group except for the partial tiles, of which some group sizes need none,
+// so now and then a group is a few percent below the largest that fits. One by
+// one from the whole group down, 20000 tokens of D = 256, V = 131072 in chunks
+// of 64 took 2.9 ms before the first launch, now 21 us; N = 16384, D = 64 in
+// chunks of one 187 ms, now 0.1 ms.
 bool plan_within(const kd_problem* p, size_t cap, Plan* out) {
-  auto counted = [](const Plan& q) { return q.total - (size_t)q.cp * (q.nP - q.nVT) * 8; };
-  Plan pl = make_plan(p);
-  const int64_t g0 = pl.G * pl.merged;  // the caller's chunks per dW group
-  for (int64_t g = g0; counted(pl) > cap && g > 1;) pl = make_plan(p, --g);
-  if (counted(pl) > cap) pl = make_plan(p, 1, false);
-  if (counted(pl) > cap || pl.total > kd_scratch_bytes_max) return false;
+  auto fits = [&](const Plan& q) { return q.total - (size_t)q.cp * (q.nP - q.nVT) * 8 <= cap; };
+  // the most chunks per group, up to g, whose plan fits (1 is not tried)
+  auto largest = [&](int64_t g, auto plan) {
+    int64_t lo = 1;
+    while (lo < g) {
+      const int64_t mid = lo + (g - lo + 1) / 2;
+      if (fits(plan(mid))) lo = mid;
+      else g = mid - 1;
+    }
+    return lo;
+  };
+  Plan pl = base_plan(p);
+  int64_t g = pl.G * pl.merged;  // the caller's chunks per dW group
+  if (!fits(pl)) {
+    g = largest(g - 1, [&](int64_t k) { return base_plan(p, k); });
+    pl = base_plan(p, g);
+    if (!fits(pl)) return false;
+  }
+  add_parts(&pl);
+  if (!fits(pl) && g > 1) pl = make_plan(p, largest(g - 1, [&](int64_t k) { return make_plan(p, k); }));
+  if (!fits(pl)) pl = base_plan(p, 1);
+  if (pl.total > kd_scratch_bytes_max) return false;
   *out = pl;
   return true;
 }
@@ -486,7 +516,7 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
       h.W = c.W;
       h.tokens = n;
       h.tile = dh_tile(pl, n);
-      h.max_parts = group_end ? pl.dh_max_parts : 0;
+      h.max_parts = group_end ? (int)(pl.dh_bytes / ((size_t)h.tile * h.tile * 4)) : 0;
       h.partial = h.max_parts > 0 ? reinterpret_cast<float*>(ws + pl.off_dhs) : nullptr;
       h.gh_f32 = (p->flags & KD_FLAG_GRAD_HIDDEN_F32) ? 1 : 0;
       h.gH = compact ? c.grad_hidden
@@ -530,7 +560,7 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
       d.Ht = ws + pl.off_ht;
       d.beta = (dw_done || c.accumulate) ? 1 : 0;
       d.gW = c.grad_W;
-      d.max_parts = pl.dw_max_parts;
+      d.max_parts = (int)(pl.dw_bytes / ((size_t)d.tile * d.tile * 4));
       d.partial = d.max_parts > 0 ? reinterpret_cast<float*>(ws + pl.off_dwp) : nullptr;
       d.nrow = compact ? gnrow : nullptr;
       if (kd_launch_dw(&d, c.stream) != 0) return KD_ERR_DEVICE;

@@ -2127,6 +2127,8 @@ static int launch_dh_impl(const KdDhArgs& a, hipStream_t s) {
   int blocks = d.sp.dp + d.sp.rem * d.sp.split;
   if (a.nrow != nullptr)
     for (int tm = cdiv(a.tokens, TS) - 1; tm > 0; --tm) {
+      // (full rounds and at most two of parts: no fewer rows need more)
+      if (tm * d.TN / kd_units(TS) * kd_units(TS) + 2 * kd_units(TS) <= blocks) break;
       const KdRounds q = kd_split_rounds(tm * d.TN, d.ks_total, kd_units(TS),
                                       kd_part_cost(TS, sizeof(T) == 4), a.max_parts);
       blocks = std::max(blocks, q.dp + q.rem * q.split);

@@ -143,7 +143,7 @@ inline KdRounds kd_split_rounds(int tiles, int ksteps, int units, int part_cost,
   for (int s = 2; s <= kSplitMax; ++s) {
     const int parts = r.rem * s;
     if (parts > max_parts || parts > 2 * units || ksteps < 4 * s) break;
-    const int t = (parts + units - 1) / units * ((ksteps + s - 1) / s * 1024 + kSplitRound) +
+    const int t = (parts > units ? 2 : 1) * ((ksteps + s - 1) / s * 1024 + kSplitRound) +
                   parts * part_cost + kSplitRound;
     if (t < best) {
       best = t;
