@@ -100,10 +100,10 @@ typedef struct kd_problem {
  * kd_topk_kl_bwd and kd_topk_kl_check_indices need for problem *p. Pure host
  * function: touches no device. The size is O(N/4 + G C_s (V + K + 1) + D G C_s),
  * with G C_s <= 16384 the tokens whose dZ rows one grad_W contraction
- * gathers (at most 4 GiB of them), plus at most 128 MiB each for the partial
- * tiles of grad_hidden's and grad_W's contractions when their tiles leave the
- * last round of the compute units partly filled: it grows with N only
- * through an array of loss partials (one per 4 tokens), never as N*V.
+ * gathers (at most 4 GiB of them), plus at most 128 MiB for the partial tiles
+ * of grad_hidden's and grad_W's contractions when their tiles leave the last
+ * round of the compute units partly filled: it grows with N only through an
+ * array of loss partials (one per 4 tokens), never as N*V.
  * Errors: KD_ERR_NULL_PTR if p or bytes is NULL; the shape/argument errors of
  * kd_topk_kl_fwd_bwd otherwise.
  */

@@ -50,7 +50,7 @@ struct Plan {
   int64_t dh_rows[2];  // the row counts dH runs on: of the full and the last chunk or group
   size_t dh_bytes, dw_bytes;  // partial tiles of their split last rounds it holds
   size_t off_misc, off_p, off_tidx, off_rows, off_pm, off_ps, off_hits, off_hitp, off_hoff, off_zhit,
-      off_lossp, off_dz, off_fac, off_ht, off_rowmap, off_dhs, off_dwp, total;
+      off_lossp, off_dz, off_fac, off_ht, off_rowmap, off_parts, total;
 };
 
 kd_status check_problem(const kd_problem* p) {
@@ -240,24 +240,29 @@ Plan base_plan(const kd_problem* p, int64_t g_max = 0) {
   return pl;
 }
 
-// Adds the partial tiles of dH's and dW's split last rounds.
-void add_parts(Plan* pl) {
+// Adds the partial tiles of dH's and dW's split last rounds, at most `room`
+// bytes of them: where these are fewer than the model would like, it splits into
+// fewer ranges (its max_parts). Both have the same place: a group's tail has
+// added up dH's parts before its dW starts.
+void add_parts(Plan* pl, size_t room = (size_t)1 << 40) {
+  size_t dh = 0, dw = 0;
   for (int i = 0; i < 2; ++i) {
     const int64_t r = pl->dh_rows[i];
     if (r <= 0 || (i == 1 && r == pl->dh_rows[0])) continue;
     const int ts = dh_tile(*pl, r);
-    pl->dh_bytes = std::max(pl->dh_bytes, (size_t)dh_parts(*pl, r) * ts * ts * 4);
+    dh = std::max(dh, (size_t)dh_parts(*pl, r) * ts * ts * 4);
   }
   const int64_t g_full = std::min<int64_t>(pl->G * pl->c, pl->N);
   const int64_t g_last = pl->N - (std::max<int64_t>(pl->ngroups, 1) - 1) * pl->G * pl->c;
   for (int64_t r : {g_full, g_last}) {
     if (r <= 0) continue;
     const int ts = dw_tile(*pl, r);
-    pl->dw_bytes = std::max(pl->dw_bytes, (size_t)dw_parts(*pl, r) * ts * ts * 4);
+    dw = std::max(dw, (size_t)dw_parts(*pl, r) * ts * ts * 4);
   }
-  pl->off_dhs = pl->total;
-  pl->off_dwp = align256(pl->off_dhs + pl->dh_bytes);
-  pl->total = align256(pl->off_dwp + pl->dw_bytes);
+  pl->dh_bytes = std::min(dh, room);
+  pl->dw_bytes = std::min(dw, room);
+  pl->off_parts = pl->total;
+  pl->total = align256(pl->off_parts + std::max(pl->dh_bytes, pl->dw_bytes));
 }
 
 Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
@@ -266,11 +271,13 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
   return pl;
 }
 
-// The plan of make_plan, with fewer chunks per dW group if its workspace
-// exceeds `cap` bytes (the same plan when it fits), and at last without partial
-// tiles; false if the workspace of one chunk per group does not fit.
-// The partials of 128-column vocabulary tiles above those of 256-column ones
-// are not counted: kd_scratch_slack holds them.
+// The plan of make_plan when it fits the static scratch; else with fewer chunks
+// per dW group; at last one chunk per group with the partial tiles that fit (a
+// dH without any leaves most of the chip idle: 1888 x 2048 x 24507 in fp32 has
+// 240 tiles for 512 workgroups). False if one chunk without partial tiles
+// exceeds `cap` bytes. The partials of 128-column vocabulary tiles above those
+// of 256-column ones are not counted against the cap: kd_scratch_slack holds
+// them, and where there are none, more partial tiles.
 // The group is found by bisection, first of the plan without its partial tiles
 // (a microsecond a step), then of the whole plan (2 to 15): the size grows with
 // the group except for the partial tiles, of which some group sizes need none,
@@ -279,28 +286,36 @@ Plan make_plan(const kd_problem* p, int64_t g_max = 0) {
 // of 64 took 2.9 ms before the first launch, now 21 us; N = 16384, D = 64 in
 // chunks of one 187 ms, now 0.1 ms.
 bool plan_within(const kd_problem* p, size_t cap, Plan* out) {
-  auto fits = [&](const Plan& q) { return q.total - (size_t)q.cp * (q.nP - q.nVT) * 8 <= cap; };
-  // the most chunks per group, up to g, whose plan fits (1 is not tried)
-  auto largest = [&](int64_t g, auto plan) {
+  // without its partial tiles; with them
+  auto base_fits = [&](const Plan& q) {
+    return q.total - (size_t)q.cp * (q.nP - q.nVT) * 8 <= cap;
+  };
+  auto fits = [](const Plan& q) { return q.total <= kd_scratch_bytes_max; };
+  // the most chunks per group, up to g, that pass (1 is not tried)
+  auto largest = [](int64_t g, auto ok) {
     int64_t lo = 1;
     while (lo < g) {
       const int64_t mid = lo + (g - lo + 1) / 2;
-      if (fits(plan(mid))) lo = mid;
+      if (ok(mid)) lo = mid;
       else g = mid - 1;
     }
     return lo;
   };
   Plan pl = base_plan(p);
   int64_t g = pl.G * pl.merged;  // the caller's chunks per dW group
-  if (!fits(pl)) {
-    g = largest(g - 1, [&](int64_t k) { return base_plan(p, k); });
+  if (!base_fits(pl)) {
+    g = largest(g - 1, [&](int64_t k) { return base_fits(base_plan(p, k)); });
     pl = base_plan(p, g);
-    if (!fits(pl)) return false;
+    if (!base_fits(pl)) return false;
   }
+  if (!fits(pl)) return false;
   add_parts(&pl);
-  if (!fits(pl) && g > 1) pl = make_plan(p, largest(g - 1, [&](int64_t k) { return make_plan(p, k); }));
-  if (!fits(pl)) pl = base_plan(p, 1);
-  if (pl.total > kd_scratch_bytes_max) return false;
+  if (!fits(pl) && g > 1)
+    pl = make_plan(p, largest(g - 1, [&](int64_t k) { return fits(make_plan(p, k)); }));
+  if (!fits(pl)) {
+    pl = base_plan(p, 1);
+    add_parts(&pl, kd_scratch_bytes_max - pl.total);
+  }
   *out = pl;
   return true;
 }
@@ -517,7 +532,7 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
       h.tokens = n;
       h.tile = dh_tile(pl, n);
       h.max_parts = group_end ? (int)(pl.dh_bytes / ((size_t)h.tile * h.tile * 4)) : 0;
-      h.partial = h.max_parts > 0 ? reinterpret_cast<float*>(ws + pl.off_dhs) : nullptr;
+      h.partial = h.max_parts > 0 ? reinterpret_cast<float*>(ws + pl.off_parts) : nullptr;
       h.gh_f32 = (p->flags & KD_FLAG_GRAD_HIDDEN_F32) ? 1 : 0;
       h.gH = compact ? c.grad_hidden
                      : static_cast<char*>(c.grad_hidden) + r0 * pl.D * (h.gh_f32 ? 4 : pl.eb);
@@ -561,7 +576,7 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
       d.beta = (dw_done || c.accumulate) ? 1 : 0;
       d.gW = c.grad_W;
       d.max_parts = (int)(pl.dw_bytes / ((size_t)d.tile * d.tile * 4));
-      d.partial = d.max_parts > 0 ? reinterpret_cast<float*>(ws + pl.off_dwp) : nullptr;
+      d.partial = d.max_parts > 0 ? reinterpret_cast<float*>(ws + pl.off_parts) : nullptr;
       d.nrow = compact ? gnrow : nullptr;
       if (kd_launch_dw(&d, c.stream) != 0) return KD_ERR_DEVICE;
       dw_done = true;

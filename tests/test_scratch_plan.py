@@ -61,3 +61,51 @@ def test_reduced_group_is_found_quickly(host, N, D, V, chunk, dtype, groups):
     print(f"[plan] N={N} D={D} V={V} chunk={chunk}: {best * 1e6:.0f} us")
     assert len(_launches(host, DW)) <= groups
     assert best < 0.4e-3
+
+
+@pytest.mark.parametrize("N,D,V,chunk,dtype,units", [
+    (16602, 512, 28368, 3423, kd.KD_BF16, 252),
+    (2169, 832, 65487, 1584, kd.KD_BF16, 224),
+    (21411, 2048, 24507, 1888, kd.KD_F32, 480),
+    (11048, 256, 48506, 2220, kd.KD_BF16, 126),
+    (18122, 320, 22562, 2289, kd.KD_F32, 378),
+])
+def test_split_keeps_the_parts_that_fit(host, N, D, V, chunk, dtype, units):
+    """One chunk nearly fills the scratch: dH still splits its tiles into what
+    is left (`units` workgroups at least, of 256 for 256-edge tiles and 512 for
+    128-edge ones), and no partial tile lies past the end of the array."""
+    scratch = (256 + 8) << 20
+    for masked in (False, True):
+        assert _call(host, N, D, V, chunk, dtype, masked=masked) == 0
+        dh, dw = _launches(host, DH), _launches(host, DW)
+        assert dh and dw
+        for r in dh + dw:
+            assert r["part_end"] <= scratch
+            assert r["rem"] * r["split"] <= max(r["max_parts"], r["rem"])
+        full = [r for r in dh if r["tokens"] == chunk]
+        assert full and all(r["rem"] * r["split"] >= units for r in full)
+
+
+def test_no_partial_tile_past_the_scratch(host):
+    """Problems of one chunk of 100 to 255 MiB of gradient rows: whatever row
+    count the device finds, the parts its model picks fit."""
+    import random
+    rng = random.Random(4)
+    host.rec_model_parts.restype = ctypes.c_int64
+    i64, seen = ctypes.c_int64, 0
+    while seen < 150:
+        dtype = rng.choice([kd.KD_BF16, kd.KD_F32])
+        eb = 2 if dtype == kd.KD_BF16 else 4
+        V, D = rng.randint(2000, 131072), 64 * rng.randint(1, 64)
+        chunk = max(1, int(rng.uniform(100, 255) * 2 ** 20 / (eb * V)))
+        N = chunk + rng.randint(0, 2 * chunk)
+        if _call(host, N, D, V, chunk, dtype, masked=True) != 0:
+            continue
+        seen += 1
+        for r in _launches(host, DH) + _launches(host, DW):
+            assert r["part_end"] <= (256 + 8) << 20
+        for r in _launches(host, DH):
+            cols = -(-D // r["tile"])
+            for rows in range(1, -(-r["tokens"] // r["tile"]) + 1):
+                assert host.rec_model_parts(i64(rows * cols), i64(r["ksteps"]), i64(r["tile"]),
+                                            int(eb == 4), int(r["max_parts"])) <= r["max_parts"]

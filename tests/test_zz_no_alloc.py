@@ -18,7 +18,8 @@ import pytest
 import torch
 
 import kd_inputs as ki
-from tests.helpers import TOL, rel_max, to64
+from oracle import kd_topk_kl
+from tests.helpers import TOL, oracle_by_row_blocks, rel_max, to64
 
 pytestmark = pytest.mark.gpu
 
@@ -117,6 +118,35 @@ def test_noalloc_call_in_a_graph(gpu_lib):
         for k in out:
             assert torch.equal(out[k], eager[k]), (rep, k)
         assert not torch.equal(other["grad_W"], eager["grad_W"])
+
+
+@pytest.mark.parametrize("N,D,V,chunk,dtype", [
+    (15769, 64, 3610, 15769, torch.float32),    # dH split into 2 of the 4 ranges it would take
+    (13581, 64, 8452, 13581, torch.bfloat16),   # 2 of 4
+    (18557, 64, 3095, 18557, torch.float32),    # no room for 2
+    (30757, 64, 3597, 30757, torch.bfloat16),
+])
+@pytest.mark.parametrize("ign", [0.0, 0.4])
+def test_noalloc_near_the_scratch_size(gpu_lib, N, D, V, chunk, dtype, ign):
+    """One chunk that leaves the scratch little room for the partial tiles of
+    dH's split last round: every output against the oracle and, up to the
+    order of fp32 sums, against the call with a workspace, which splits more."""
+    kd, K = gpu_lib, 8
+    tol = TOL["bf16" if dtype == torch.bfloat16 else "f32"]
+    print(f"[noalloc] N={N} D={D} V={V} {dtype} ignored={ign}", flush=True)
+    hidden, W, idx, logit, ignore = _inputs(N, D, V, K, dtype, ign, seed=120)
+    kw = dict(tau=1.0, ignore=ignore, chunk=chunk, loss_per_token=True)
+    ref = oracle_by_row_blocks(kd_topk_kl, to64(hidden), to64(W), to64(idx), to64(logit), 1.0,
+                               ignore=to64(ignore))
+    full = kd.fwd_bwd(hidden, W, idx, logit, **kw)
+    got = kd.fwd_bwd_noalloc(hidden, W, idx, logit, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(got["loss_per_token"], full["loss_per_token"])
+    for out in (got, full):
+        assert abs(float(out["loss"]) - ref["loss"]) <= tol["loss"] * abs(ref["loss"])
+        assert rel_max(to64(out["loss_per_token"]), ref["loss_per_token"]) <= tol["loss"]
+        assert rel_max(to64(out["grad_hidden"]), ref["grad_hidden"]) <= tol["grad"]
+        assert rel_max(to64(out["grad_W"]), ref["grad_W"]) <= tol["grad"]
 
 
 def test_noalloc_debug_index_check(gpu_lib, monkeypatch):
