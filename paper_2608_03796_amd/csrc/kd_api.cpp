@@ -26,6 +26,9 @@ constexpr int64_t kMaxChunk = (int64_t)1 << 20; // rows per chunk actually used
 // 20 bits by the bucket pass, and k is packed in 16
 constexpr int64_t kMaxK = 4096;
 
+// no limit to the partial tiles of dH (see kd_dh_rounds): two rounds of 256 x 256
+constexpr int kPartSpaceMax = 512 * 256 * 256 / 64;
+
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline int64_t rup(int64_t a, int64_t b) { return cdiv(a, b) * b; }
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -103,30 +106,31 @@ int dw_tile(const Plan& pl, int64_t n) {
   return pl.eb == 4 || t <= 128 || (n <= 128 && t <= 512) ? 128 : 256;
 }
 
-// Tiles of dH over n rows, and how they run (see kd_split_rounds).
+// Tiles of dH over n rows, and how they run with all the partial tiles they like.
 int dh_tiles(const Plan& pl, int64_t n) {
   const int ts = dh_tile(pl, n);
   return (int)(cdiv(n, ts) * cdiv(pl.D, ts));
 }
-KdRounds dh_split(const Plan& pl, int64_t n, int max_parts = 1 << 20) {
-  const int ts = dh_tile(pl, n);
-  return kd_split_rounds(dh_tiles(pl, n), (int)pl.ksteps, kd_units(ts), kd_part_cost(ts, pl.eb == 4),
-                     max_parts);
+KdRounds dh_split(const Plan& pl, int64_t n, int ts) {
+  return kd_dh_rounds((int)n, (int)pl.D, ts, (int)pl.ksteps, pl.eb == 4, kPartSpaceMax);
 }
-// The most partial tiles dH over 1..n rows of the tile of n rows needs (fewer
-// rows hold tokens when ignored ones are left out).
-int dh_parts(const Plan& pl, int64_t n) {
+KdRounds dh_split(const Plan& pl, int64_t n) { return dh_split(pl, n, dh_tile(pl, n)); }
+// The most bytes of partial tiles dH over 1..n rows in the tiles of n rows needs
+// (fewer rows hold tokens when ignored ones are left out).
+size_t dh_part_bytes(const Plan& pl, int64_t n) {
   const int ts = dh_tile(pl, n), units = kd_units(ts);
   const int64_t tm_max = cdiv(n, ts), td = cdiv(pl.D, ts);
-  // the tiles left over for the last round repeat with this many tile rows
+  // the tiles left over for the last round repeat with this many tile rows, and
+  // take the most space in the last repetition
   const int64_t period = units / std::gcd(td, (int64_t)units);
-  int parts = 0;
+  size_t bytes = 0;
   for (int64_t tm = tm_max; tm > std::max<int64_t>(0, tm_max - period); --tm) {
-    const KdRounds s = kd_split_rounds((int)(tm * td), (int)pl.ksteps, units,
-                                       kd_part_cost(ts, pl.eb == 4), 1 << 20);
-    if (s.split > 1) parts = std::max(parts, s.rem * s.split);
+    const int64_t rows = std::min(tm * ts, n);
+    const KdRounds s = dh_split(pl, rows, ts);
+    if (s.split > 1)
+      bytes = std::max(bytes, (size_t)4 * s.split * (s.dp == 0 ? rows * pl.D : (int64_t)s.rem * ts * ts));
   }
-  return parts;
+  return bytes;
 }
 // The partial tiles dW over n tokens needs.
 int dw_parts(const Plan& pl, int64_t n) {
@@ -249,8 +253,7 @@ void add_parts(Plan* pl, size_t room = (size_t)1 << 40) {
   for (int i = 0; i < 2; ++i) {
     const int64_t r = pl->dh_rows[i];
     if (r <= 0 || (i == 1 && r == pl->dh_rows[0])) continue;
-    const int ts = dh_tile(*pl, r);
-    dh = std::max(dh, (size_t)dh_parts(*pl, r) * ts * ts * 4);
+    dh = std::max(dh, dh_part_bytes(*pl, r));
   }
   const int64_t g_full = std::min<int64_t>(pl->G * pl->c, pl->N);
   const int64_t g_last = pl->N - (std::max<int64_t>(pl->ngroups, 1) - 1) * pl->G * pl->c;
@@ -531,8 +534,8 @@ kd_status enqueue(const kd_problem* p, const Plan& pl, const Call& c) {
       h.W = c.W;
       h.tokens = n;
       h.tile = dh_tile(pl, n);
-      h.max_parts = group_end ? (int)(pl.dh_bytes / ((size_t)h.tile * h.tile * 4)) : 0;
-      h.partial = h.max_parts > 0 ? reinterpret_cast<float*>(ws + pl.off_parts) : nullptr;
+      h.part_space = group_end ? (int)(pl.dh_bytes / 256) : 0;
+      h.partial = h.part_space > 0 ? reinterpret_cast<float*>(ws + pl.off_parts) : nullptr;
       h.gh_f32 = (p->flags & KD_FLAG_GRAD_HIDDEN_F32) ? 1 : 0;
       h.gH = compact ? c.grad_hidden
                      : static_cast<char*>(c.grad_hidden) + r0 * pl.D * (h.gh_f32 ? 4 : pl.eb);

@@ -1347,7 +1347,7 @@ struct DhArgs {
   void* gH;
   int gh_f32;
   float* partial;
-  int max_parts;
+  int part_space;
   const float* rowscale;
   const int* rowmap;
   const int* nrow;
@@ -1361,8 +1361,7 @@ __device__ __forceinline__ KdRounds dh_split(const DhArgs& a, int& n, int& TM) {
   n = max(n, 0);
   TM = (n + TS - 1) / TS;
   if (a.nrow == nullptr) return a.sp;
-  return kd_split_rounds(TM * a.TN, a.ks_total, kd_units(TS), kd_part_cost(TS, sizeof(T) == 4),
-                     a.max_parts);
+  return kd_dh_rounds(n, a.D, TS, a.ks_total, sizeof(T) == 4, a.part_space);
 }
 
 template <typename T, int TS>
@@ -1372,7 +1371,7 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dh(DhA
   int n, TM;
   const KdRounds sp = dh_split<T, TS>(a, n, TM);
   const int pid = blockIdx.x;
-  int L, slot = -1, kb = 0, ke = a.ks_total;
+  int L, part = -1, kb = 0, ke = a.ks_total;  // part: of a split tile
   if (pid < sp.dp) {
     L = tile_order_xcd(pid, sp.dp);
   } else {
@@ -1384,7 +1383,7 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dh(DhA
     const int s = q / sp.rem;
     L = sp.dp + q - s * sp.rem;
     if (sp.split > 1) {
-      slot = (L - sp.dp) * sp.split + s;
+      part = s;
       kb = (int)((int64_t)a.ks_total * s / sp.split);
       ke = (int)((int64_t)a.ks_total * (s + 1) / sp.split);
     }
@@ -1402,7 +1401,7 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dh(DhA
   // kept in LDS for the epilogue: a load there would wait for every store
   // issued before it (loads and stores complete in order)
   const int tid = threadIdx.x;
-  const float rsv = (a.rowscale != nullptr && slot < 0 && tid < TS && m0 + tid < rows)
+  const float rsv = (a.rowscale != nullptr && part < 0 && tid < TS && m0 + tid < rows)
                         ? a.rowscale[m0 + tid]
                         : 1.f;
   gemm<T, TS, true>(
@@ -1412,8 +1411,11 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dh(DhA
       kb, ke, lds, acc);
   const int lane = tid & 63, wave = wave_id();
   const int wm = G::wm(wave), wn = G::wn(wave);
-  if (slot >= 0) {
-    float* part = a.partial + (int64_t)slot * TS * TS;
+  if (part >= 0) {
+    const bool rows_d = sp.dp == 0;  // the range's [n, D] array, or a tile of its own
+    const int pitch = rows_d ? D : TS, cols = rows_d ? D - n0 : TS;
+    float* dst = a.partial + (rows_d ? ((int64_t)part * n + m0) * D + n0
+                                     : (int64_t)((L - sp.dp) * sp.split + part) * TS * TS);
 #pragma unroll
     for (int i = 0; i < G::NI; ++i)
 #pragma unroll
@@ -1421,7 +1423,10 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dh(DhA
         const int m = G::acc_m(wm, i, lane, r);
         if (m0 + m >= n) continue;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) part[m * TS + G::acc_n(wn, j, lane)] = acc.v[i][j][r];
+        for (int j = 0; j < 4; ++j) {
+          const int c = G::acc_n(wn, j, lane);
+          if (c < cols) dst[(int64_t)m * pitch + c] = acc.v[i][j][r];
+        }
       }
     return;
   }
@@ -1464,20 +1469,30 @@ __device__ __forceinline__ void dh_reduce(int block, int blocks, const DhArgs& a
   const KdRounds sp = dh_split<T, TS>(a, n, TM);
   if (sp.split < 2) return;
   constexpr int Q = TS * TS / 4;  // pieces per tile
-  const int total = sp.rem * Q;
+  const bool rows_d = sp.dp == 0;  // parts as [n, D] arrays
+  const int total = rows_d ? n * (a.D / 4) : sp.rem * Q;
+  const int64_t step = rows_d ? (int64_t)n * a.D : TS * TS;
   for (int i = block * 256 + (int)threadIdx.x; i < total; i += blocks * 256) {
-    const int q = i / Q, row = i % Q / (TS / 4), c = i % (TS / 4) * 4;
-    int mt, nt;
-    tile_at(sp.dp + q, TM, a.TN, Geo<TS>::GM, mt, nt);
-    const int t = mt * TS + row, d = nt * TS + c;
+    int t, d;
+    const float* part = a.partial;
+    if (rows_d) {
+      t = i / (a.D / 4);
+      d = i % (a.D / 4) * 4;
+      part += (int64_t)i * 4;
+    } else {
+      const int q = i / Q, row = i % Q / (TS / 4), c = i % (TS / 4) * 4;
+      int mt, nt;
+      tile_at(sp.dp + q, TM, a.TN, Geo<TS>::GM, mt, nt);
+      t = mt * TS + row;
+      d = nt * TS + c;
+      part += (int64_t)q * sp.split * (TS * TS) + row * TS + c;
+    }
     if (t >= n || d >= a.D) continue;
     const int64_t o = a.rowmap != nullptr ? a.rowmap[t] : t;  // the grad_hidden row
     if (o < 0) continue;
-    const float* part = a.partial + (int64_t)q * sp.split * (TS * TS) + row * TS + c;
     f32x4_t v = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 8
-    for (int k = 0; k < sp.split; ++k)
-      v += *reinterpret_cast<const f32x4_t*>(part + (int64_t)k * TS * TS);
+    for (int k = 0; k < sp.split; ++k) v += *reinterpret_cast<const f32x4_t*>(part + k * step);
     if (a.rowscale != nullptr) v *= a.rowscale[t];
     if (a.gh_f32 || sizeof(T) == 4) {
       *reinterpret_cast<f32x4_t*>(static_cast<float*>(a.gH) + o * a.D + d) = v;
@@ -2110,27 +2125,27 @@ static DhArgs dh_args(const KdDhArgs& a) {
   d.gH = a.gH;
   d.gh_f32 = a.gh_f32;
   d.partial = a.partial;
-  d.max_parts = a.max_parts;
+  d.part_space = a.part_space;
   d.rowscale = a.rowscale;
   d.rowmap = a.rowmap;
   d.nrow = a.nrow;
   d.nrow_base = a.nrow_base;
-  d.sp = kd_split_rounds(cdiv(a.tokens, TS) * d.TN, d.ks_total, kd_units(TS),
-                     kd_part_cost(TS, sizeof(T) == 4), a.max_parts);
+  d.sp = kd_dh_rounds((int)a.tokens, (int)a.D, TS, d.ks_total, sizeof(T) == 4, a.part_space);
   return d;
 }
 
 template <typename T, int TS>
 static int launch_dh_impl(const KdDhArgs& a, hipStream_t s) {
   const DhArgs d = dh_args<T, TS>(a);
-  // with a device-side row count: the most workgroups any count needs
+  // with a device-side row count: the most workgroups any count needs (the
+  // fewest rows of a tile row leave room for the most ranges)
   int blocks = d.sp.dp + d.sp.rem * d.sp.split;
   if (a.nrow != nullptr)
-    for (int tm = cdiv(a.tokens, TS) - 1; tm > 0; --tm) {
+    for (int tm = cdiv(a.tokens, TS); tm > 0; --tm) {
       // (full rounds and at most two of parts: no fewer rows need more)
       if (tm * d.TN / kd_units(TS) * kd_units(TS) + 2 * kd_units(TS) <= blocks) break;
-      const KdRounds q = kd_split_rounds(tm * d.TN, d.ks_total, kd_units(TS),
-                                      kd_part_cost(TS, sizeof(T) == 4), a.max_parts);
+      const KdRounds q = kd_dh_rounds((tm - 1) * TS + 1, (int)a.D, TS, d.ks_total, sizeof(T) == 4,
+                                      a.part_space);
       blocks = std::max(blocks, q.dp + q.rem * q.split);
     }
   {
@@ -2200,7 +2215,7 @@ static int launch_tail_impl(const KdTailArgs& a, hipStream_t s) {
     t.nt = t.ldt / 64 * (int)(a.D / 64);
   }
   t.D = (int)a.D;
-  if (a.dh != nullptr && a.dh->max_parts > 0) {
+  if (a.dh != nullptr && a.dh->part_space > 0) {
     t.dh = dh_args<T, DTS>(*a.dh);
     const int rem = a.dh->nrow != nullptr ? std::min(cdiv(a.dh->tokens, DTS) * t.dh.TN, kd_units(DTS))
                     : t.dh.sp.split > 1   ? t.dh.sp.rem

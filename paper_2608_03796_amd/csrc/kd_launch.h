@@ -95,7 +95,7 @@ struct KdDhArgs {
   const void* W;            // [V, D]
   int64_t tokens;           // tokens in the group
   float* partial;           // partial tiles of the split last round
-  int max_parts;            // their number (0: no split)
+  int part_space;           // their space in units of 256 bytes (0: no split)
   void* gH;                 // grad_hidden + the group's first row * D (full with a rowmap)
   int gh_f32;               // grad_hidden is fp32 (else the operands' dtype)
   const float* rowscale;    // [tokens] factor of each dZ row, or null (= 1)
@@ -155,6 +155,23 @@ inline KdRounds kd_split_rounds(int tiles, int ksteps, int units, int part_cost,
 // 1024ths of a tile's K step that one partial tile's write and read cost (a 256
 // KB partial tile against 1.44 us, a 64 KB one against 2 us (fp32) or 0.65 us)
 constexpr int kd_part_cost(int tile, bool f32) { return tile == 256 ? 82 : f32 ? 15 : 46; }
+
+// The split of dH over n token rows, D features, with its partial tiles in
+// `space` units of 256 bytes. Where all tiles are split (no full rounds), a
+// range's partial tiles are stored as one [n, D] array, without the padding of
+// the tiles; else each is TS x TS on its own.
+#ifdef __HIP__
+__host__ __device__
+#endif
+inline KdRounds kd_dh_rounds(int n, int D, int tile, int ksteps, bool f32, int space) {
+  const int tiles = (n + tile - 1) / tile * ((D + tile - 1) / tile), units = kd_units(tile);
+  int max_parts = space / (tile * tile / 64);
+  if (tiles < units) {
+    const int fit = n > 0 ? space / (n * (D / 64)) : 0;  // ranges
+    max_parts = tiles * (fit < kSplitMax ? fit : kSplitMax);
+  }
+  return kd_split_rounds(tiles, ksteps, units, kd_part_cost(tile, f32), max_parts);
+}
 
 // the most parts of a split dW tile that k_dw_fixup has in flight at a time
 constexpr int kDwMaxSplit = 4;

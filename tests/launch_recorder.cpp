@@ -7,24 +7,18 @@
 
 namespace {
 // one launch of dH (kind 1) or dW (kind 2): its token rows, tile edge, whole
-// tiles, tiles and parts of the split last round, K steps, the most partial
-// tiles it may use, and the scratch bytes up to the end of these
+// tiles, tiles and parts of the split last round, K steps, the bytes its partial
+// tiles may take, and the scratch bytes up to the end of these
 struct Rec {
-  int64_t kind, tokens, tile, dp, rem, split, ksteps, max_parts, part_end;
+  int64_t kind, tokens, tile, dp, rem, split, ksteps, part_bytes, part_end;
 };
 std::vector<Rec> recs;
 char* const kScratch = reinterpret_cast<char*>((uintptr_t)1 << 40);
 
-int64_t tiles(int64_t a, int64_t b, int64_t ts) { return (a + ts - 1) / ts * ((b + ts - 1) / ts); }
-void record(int64_t kind, int64_t tokens, int64_t tile, int64_t n_tiles, int64_t ksteps, bool f32,
-            int max_parts, const float* partial) {
-  const KdRounds r = kd_split_rounds((int)n_tiles, (int)ksteps, kd_units(tile),
-                                     kd_part_cost((int)tile, f32), max_parts);
-  const int64_t end =
-      max_parts > 0
-          ? (int64_t)(reinterpret_cast<const char*>(partial) - kScratch) + max_parts * tile * tile * 4
-          : 0;
-  recs.push_back({kind, tokens, tile, r.dp, r.rem, r.split, ksteps, max_parts, end});
+void record(int64_t kind, int64_t tokens, int64_t tile, const KdRounds& r, int64_t ksteps,
+            int64_t part_bytes, const float* partial) {
+  const int64_t at = part_bytes > 0 ? reinterpret_cast<const char*>(partial) - kScratch : 0;
+  recs.push_back({kind, tokens, tile, r.dp, r.rem, r.split, ksteps, part_bytes, at + part_bytes});
 }
 }  // namespace
 
@@ -33,15 +27,15 @@ int rec_count() { return (int)recs.size(); }
 void rec_clear() { recs.clear(); }
 void rec_get(int i, int64_t* out) {
   const Rec& r = recs[i];
-  const int64_t v[9] = {r.kind, r.tokens, r.tile, r.dp, r.rem, r.split, r.ksteps, r.max_parts,
+  const int64_t v[9] = {r.kind, r.tokens, r.tile, r.dp, r.rem, r.split, r.ksteps, r.part_bytes,
                         r.part_end};
   for (int k = 0; k < 9; ++k) out[k] = v[k];
 }
-// the most partial tiles the device may use for any count of token rows
-int64_t rec_model_parts(int64_t n_tiles, int64_t ksteps, int64_t tile, int f32, int max_parts) {
-  const KdRounds r = kd_split_rounds((int)n_tiles, (int)ksteps, kd_units(tile),
-                                     kd_part_cost((int)tile, f32 != 0), max_parts);
-  return r.split > 1 ? r.rem * r.split : 0;
+// the bytes of partial tiles that dH over n rows takes of the `part_bytes` it has
+int64_t rec_dh_bytes(int n, int D, int tile, int ksteps, int f32, int64_t part_bytes) {
+  const KdRounds r = kd_dh_rounds(n, D, tile, ksteps, f32 != 0, (int)(part_bytes / 256));
+  if (r.split < 2) return 0;
+  return 4 * (int64_t)r.split * (r.dp == 0 ? (int64_t)n * D : (int64_t)r.rem * tile * tile);
 }
 
 int kd_launch_fill(float*, int64_t, void*) { return 0; }
@@ -50,15 +44,19 @@ int kd_launch_compact(const KdCompactArgs*, void*) { return 0; }
 int kd_launch_tail(const KdTailArgs*, void*) { return 0; }
 int kd_launch_scale(const KdScaleArg*, const KdScaleArg*, const float*, void*) { return 0; }
 int kd_launch_dh(const KdDhArgs* a, void*) {
-  const int eb = a->dtype == 1 ? 2 : 4;
-  record(1, a->tokens, a->tile, tiles(a->tokens, a->D, a->tile), a->ldz * eb / 128, eb == 4,
-         a->max_parts, a->partial);
+  const int eb = a->dtype == 1 ? 2 : 4, ksteps = (int)(a->ldz * eb / 128);
+  record(1, a->tokens, a->tile,
+         kd_dh_rounds((int)a->tokens, (int)a->D, a->tile, ksteps, eb == 4, a->part_space), ksteps,
+         (int64_t)a->part_space * 256, a->partial);
   return 0;
 }
 int kd_launch_dw(const KdDwArgs* a, void*) {
-  const int eb = a->dtype == 1 ? 2 : 4;
-  record(2, a->tokens, a->tile, tiles(a->D, a->V, a->tile), (a->tokens + 63) / 64 * 64 * eb / 128,
-         eb == 4, a->max_parts, a->partial);
+  const int eb = a->dtype == 1 ? 2 : 4, ts = a->tile;
+  const int ksteps = (int)((a->tokens + 63) / 64 * 64 * eb / 128);
+  const int tiles = (int)((a->D + ts - 1) / ts * ((a->V + ts - 1) / ts));
+  record(2, a->tokens, ts,
+         kd_split_rounds(tiles, ksteps, kd_units(ts), kd_part_cost(ts, eb == 4), a->max_parts),
+         ksteps, (int64_t)a->max_parts * ts * ts * 4, a->partial);
   return 0;
 }
 int kd_scratch_get(void** ptr) {

@@ -14,7 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(os.path.dirname(HERE), "paper_2608_03796_amd", "csrc")
 FAKE = ctypes.c_void_p(0x10000)  # never dereferenced
 DH, DW = 1, 2
-FIELDS = ("kind", "tokens", "tile", "dp", "rem", "split", "ksteps", "max_parts", "part_end")
+FIELDS = ("kind", "tokens", "tile", "dp", "rem", "split", "ksteps", "part_bytes", "part_end")
 
 
 @pytest.fixture(scope="module")
@@ -81,7 +81,6 @@ def test_split_keeps_the_parts_that_fit(host, N, D, V, chunk, dtype, units):
         assert dh and dw
         for r in dh + dw:
             assert r["part_end"] <= scratch
-            assert r["rem"] * r["split"] <= max(r["max_parts"], r["rem"])
         full = [r for r in dh if r["tokens"] == chunk]
         assert full and all(r["rem"] * r["split"] >= units for r in full)
 
@@ -91,7 +90,7 @@ def test_no_partial_tile_past_the_scratch(host):
     count the device finds, the parts its model picks fit."""
     import random
     rng = random.Random(4)
-    host.rec_model_parts.restype = ctypes.c_int64
+    host.rec_dh_bytes.restype = ctypes.c_int64
     i64, seen = ctypes.c_int64, 0
     while seen < 150:
         dtype = rng.choice([kd.KD_BF16, kd.KD_F32])
@@ -105,7 +104,7 @@ def test_no_partial_tile_past_the_scratch(host):
         for r in _launches(host, DH) + _launches(host, DW):
             assert r["part_end"] <= (256 + 8) << 20
         for r in _launches(host, DH):
-            cols = -(-D // r["tile"])
-            for rows in range(1, -(-r["tokens"] // r["tile"]) + 1):
-                assert host.rec_model_parts(i64(rows * cols), i64(r["ksteps"]), i64(r["tile"]),
-                                            int(eb == 4), int(r["max_parts"])) <= r["max_parts"]
+            for n in {min(r["tokens"], t + d) for t in range(0, r["tokens"], r["tile"])
+                      for d in (1, r["tile"] // 2, r["tile"])}:
+                assert host.rec_dh_bytes(n, D, int(r["tile"]), int(r["ksteps"]), int(eb == 4),
+                                         i64(r["part_bytes"])) <= r["part_bytes"]

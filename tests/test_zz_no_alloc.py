@@ -121,10 +121,11 @@ def test_noalloc_call_in_a_graph(gpu_lib):
 
 
 @pytest.mark.parametrize("N,D,V,chunk,dtype", [
-    (15769, 64, 3610, 15769, torch.float32),    # dH split into 2 of the 4 ranges it would take
-    (13581, 64, 8452, 13581, torch.bfloat16),   # 2 of 4
-    (18557, 64, 3095, 18557, torch.float32),    # no room for 2
-    (30757, 64, 3597, 30757, torch.bfloat16),
+    (19100, 64, 3114, 19100, torch.float32),    # dH in 2 of the 3 ranges it would take
+    (20744, 64, 5975, 20744, torch.bfloat16),
+    (44021, 320, 3416, 33016, torch.bfloat16),  # the same behind a full round; two chunks
+    (19111, 64, 3086, 19111, torch.float32),    # no room for 2
+    (32156, 64, 3611, 32156, torch.bfloat16),
 ])
 @pytest.mark.parametrize("ign", [0.0, 0.4])
 def test_noalloc_near_the_scratch_size(gpu_lib, N, D, V, chunk, dtype, ign):
