@@ -1354,6 +1354,24 @@ struct DhArgs {
   int nrow_base;
   KdRounds sp;  // without nrow
 };
+// kd_split_rounds by a whole wave, a number of ranges per lane (all lanes active,
+// the arguments the same). One after the other, with a division each, they took
+// about 5 us of a masked dH and as much of its tail (77 x 768 x 32003 with a tenth
+// ignored 93 us, now 84; six chunks of 5504 x 320 x 14960 773 us, now 487).
+__device__ __forceinline__ KdRounds split_rounds(int tiles, int ksteps, int units, int part_cost,
+                                                 int max_parts) {
+  static_assert(kSplitMax == 64, "a number of ranges per lane");
+  KdRounds r;
+  r.dp = tiles / units * units;
+  r.rem = tiles - r.dp;
+  const int t = kd_split_time((int)(threadIdx.x & 63) + 1, r.rem, ksteps, units, part_cost, max_parts);
+  int best = t;
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) best = min(best, __shfl_xor(best, o));
+  // the fewest ranges of equals
+  r.split = r.rem == 0 ? 1 : __builtin_ctzll(__builtin_amdgcn_ballot_w64(t == best)) + 1;
+  return r;
+}
 // the tile rows that hold tokens and the launch's split
 template <typename T, int TS>
 __device__ __forceinline__ KdRounds dh_split(const DhArgs& a, int& n, int& TM) {
@@ -1361,7 +1379,8 @@ __device__ __forceinline__ KdRounds dh_split(const DhArgs& a, int& n, int& TM) {
   n = max(n, 0);
   TM = (n + TS - 1) / TS;
   if (a.nrow == nullptr) return a.sp;
-  return kd_dh_rounds(n, a.D, TS, a.ks_total, sizeof(T) == 4, a.part_space);
+  return split_rounds(TM * a.TN, a.ks_total, kd_units(TS), kd_part_cost(TS, sizeof(T) == 4),
+                      kd_dh_max_parts(TM * a.TN, n, a.D, TS, a.part_space));
 }
 
 template <typename T, int TS>

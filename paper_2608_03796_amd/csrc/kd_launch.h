@@ -125,26 +125,35 @@ constexpr int kd_units(int64_t tile) { return tile == 256 ? 256 : 512; }
 // rounds of them (their traffic).
 // The model is in integers (1024ths of a K step), so that host and device choose
 // alike.
+#ifdef __HIP__
+#define KD_HOST_DEVICE __host__ __device__
+#else
+#define KD_HOST_DEVICE
+#endif
 constexpr int kSplitRound = 4 * 1024;
 constexpr int kSplitMax = 64;
 struct KdRounds {
   int dp, rem, split;
 };
-#ifdef __HIP__
-__host__ __device__
-#endif
+// the model's time of `rem` tiles in s ranges each, INT_MAX if s is too many
+KD_HOST_DEVICE inline int kd_split_time(int s, int rem, int ksteps, int units, int part_cost,
+                                        int max_parts) {
+  if (s == 1) return ksteps * 1024 + kSplitRound;
+  const int parts = rem * s;
+  if (parts > max_parts || parts > 2 * units || ksteps < 4 * s) return 0x7fffffff;
+  return (parts > units ? 2 : 1) * ((ksteps + s - 1) / s * 1024 + kSplitRound) + parts * part_cost +
+         kSplitRound;
+}
 inline KdRounds kd_split_rounds(int tiles, int ksteps, int units, int part_cost, int max_parts) {
   KdRounds r;
   r.dp = tiles / units * units;
   r.rem = tiles - r.dp;
   r.split = 1;
   if (r.rem == 0) return r;
-  int best = ksteps * 1024 + kSplitRound;
+  int best = kd_split_time(1, r.rem, ksteps, units, part_cost, max_parts);
   for (int s = 2; s <= kSplitMax; ++s) {
-    const int parts = r.rem * s;
-    if (parts > max_parts || parts > 2 * units || ksteps < 4 * s) break;
-    const int t = (parts > units ? 2 : 1) * ((ksteps + s - 1) / s * 1024 + kSplitRound) +
-                  parts * part_cost + kSplitRound;
+    const int t = kd_split_time(s, r.rem, ksteps, units, part_cost, max_parts);
+    if (t == 0x7fffffff) break;  // and so for more ranges
     if (t < best) {
       best = t;
       r.split = s;
@@ -156,21 +165,19 @@ inline KdRounds kd_split_rounds(int tiles, int ksteps, int units, int part_cost,
 // KB partial tile against 1.44 us, a 64 KB one against 2 us (fp32) or 0.65 us)
 constexpr int kd_part_cost(int tile, bool f32) { return tile == 256 ? 82 : f32 ? 15 : 46; }
 
-// The split of dH over n token rows, D features, with its partial tiles in
-// `space` units of 256 bytes. Where all tiles are split (no full rounds), a
-// range's partial tiles are stored as one [n, D] array, without the padding of
-// the tiles; else each is TS x TS on its own.
-#ifdef __HIP__
-__host__ __device__
-#endif
+// The most partial tiles of dH over n token rows, D features, in `space` units of
+// 256 bytes. Where all tiles are split (no full rounds), a range's partial
+// tiles are stored as one [n, D] array, without the padding of the tiles; else
+// each is TS x TS on its own.
+KD_HOST_DEVICE inline int kd_dh_max_parts(int tiles, int n, int D, int tile, int space) {
+  if (tiles >= kd_units(tile)) return space / (tile * tile / 64);
+  const int fit = n > 0 ? space / (n * (D / 64)) : 0;  // ranges
+  return tiles * (fit < kSplitMax ? fit : kSplitMax);
+}
 inline KdRounds kd_dh_rounds(int n, int D, int tile, int ksteps, bool f32, int space) {
-  const int tiles = (n + tile - 1) / tile * ((D + tile - 1) / tile), units = kd_units(tile);
-  int max_parts = space / (tile * tile / 64);
-  if (tiles < units) {
-    const int fit = n > 0 ? space / (n * (D / 64)) : 0;  // ranges
-    max_parts = tiles * (fit < kSplitMax ? fit : kSplitMax);
-  }
-  return kd_split_rounds(tiles, ksteps, units, kd_part_cost(tile, f32), max_parts);
+  const int tiles = (n + tile - 1) / tile * ((D + tile - 1) / tile);
+  return kd_split_rounds(tiles, ksteps, kd_units(tile), kd_part_cost(tile, f32),
+                         kd_dh_max_parts(tiles, n, D, tile, space));
 }
 
 // the most parts of a split dW tile that k_dw_fixup has in flight at a time
