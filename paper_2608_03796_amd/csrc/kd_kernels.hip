@@ -1623,7 +1623,22 @@ __global__ __launch_bounds__(256) void k_tail(TailArgs a) {
 //
 // With nrow (ignored tokens left out), only the group's first *nrow dZ rows
 // hold tokens: the K range stops there, and the dZ rows past it read as
-// zeros.
+// zeros. The split is then the model's for that K range, at most the launch's:
+// parts of a few steps cost more in partial tiles than they fill the chip
+// (fwd and bwd of 11343 x 128 x 22099 with 12 tokens left: 124 us, now 114).
+template <typename T>
+__device__ __forceinline__ int dw_steps(int tokens, int ldt, const int* nrow) {
+  constexpr int KS = kRowB / (int)sizeof(T);
+  if (nrow != nullptr) tokens = min(tokens, __builtin_amdgcn_readfirstlane(*nrow));
+  return min(ldt / KS, (tokens + KS - 1) / KS);
+}
+template <typename T, int TS>
+__device__ __forceinline__ int dw_split(int split, int nks, int tiles, int nfull, const int* nrow) {
+  if (nrow == nullptr) return split;
+  return split_rounds(tiles, nks, kd_units(TS), kd_part_cost(TS, sizeof(T) == 4),
+                      (tiles - nfull) * split)
+      .split;
+}
 template <typename T, int TS, bool SPLIT>
 __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dw(const T* __restrict__ Ht, int ldt,
                                                     const T* __restrict__ dZ, int64_t ldz,
@@ -1634,9 +1649,8 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dw(con
   typedef Geo<TS> G;
   constexpr int NI = G::NI;
   __shared__ __attribute__((aligned(16))) char lds[gemm_lds<T, TS>];
-  constexpr int KS = kRowB / (int)sizeof(T);
+  const int nks = dw_steps<T>(tokens, ldt, nrow);
   if (nrow != nullptr) tokens = min(tokens, __builtin_amdgcn_readfirstlane(*nrow));
-  const int nks = min(ldt / KS, (tokens + KS - 1) / KS);
   const int pid = blockIdx.x;
   int L, ks0 = 0, ks1 = nks, slot = -1;
   if (!SPLIT) {
@@ -1645,12 +1659,16 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dw(con
     L = tile_order_xcd(pid, nfull);
   } else {
     const int rem = TM * TN - nfull;
+    split = dw_split<T, TS>(split, nks, TM * TN, nfull, nrow);
+    if (pid - nfull >= rem * split) return;
     const int o = tile_order_xcd(pid - nfull, rem * split);
     const int s = o / rem, q = o - s * rem;
     L = nfull + q;
-    slot = q * split + s;
-    ks0 = (int)((int64_t)nks * s / split);
-    ks1 = (int)((int64_t)nks * (s + 1) / split);
+    if (split > 1) {
+      slot = q * split + s;
+      ks0 = (int)((int64_t)nks * s / split);
+      ks1 = (int)((int64_t)nks * (s + 1) / split);
+    }
   }
   int mt, nt;
   tile_at(L, TM, TN, G::GM, mt, nt);
@@ -1731,10 +1749,13 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dw(con
 // The split tail tiles of k_dw: grad_W = (beta ? grad_W : 0) + (part 0 + part 1
 // + ...), the parts in this order. One thread per 4 features of a vocabulary row of a tail
 // tile (grid: tail tiles x blocks of rows).
-template <int TS>
+template <typename T, int TS>
 __global__ __launch_bounds__(256) void k_dw_fixup(const float* __restrict__ partial, int split,
                                                   int nfull, int TM, int TN, int V, int D,
-                                                  int beta, float* __restrict__ gW) {
+                                                  int beta, float* __restrict__ gW, int tokens,
+                                                  int ldt, const int* __restrict__ nrow) {
+  split = dw_split<T, TS>(split, dw_steps<T>(tokens, ldt, nrow), TM * TN, nfull, nrow);
+  if (split < 2) return;
   const int q = blockIdx.x;                      // tail tile
   constexpr int TPR = TS / 4;                    // threads per row
   const int row = blockIdx.y * (256 / TPR) + threadIdx.x / TPR;
@@ -2209,8 +2230,9 @@ static int launch_dw_impl(const KdDwArgs& a, hipStream_t s) {
   }
   if (nfull < tiles) {
     ProfScope ps_(P_DW_FIXUP, 0.0, s);
-    hipLaunchKernelGGL(k_dw_fixup<TS>, dim3(tiles - nfull, TS * TS / 1024), dim3(256), 0, s, a.partial,
-                       split, nfull, TM, TN, (int)a.V, (int)a.D, a.beta, a.gW);
+    hipLaunchKernelGGL((k_dw_fixup<T, TS>), dim3(tiles - nfull, TS * TS / 1024), dim3(256), 0, s,
+                       a.partial, split, nfull, TM, TN, (int)a.V, (int)a.D, a.beta, a.gW,
+                       (int)a.tokens, ldt, a.nrow);
   }
   return (int)hipGetLastError();
 }

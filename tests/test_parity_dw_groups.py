@@ -173,3 +173,45 @@ def test_chunk_plans(gpu_lib, N, D, V, chunk, masked):
     assert rel_max(to64(out["loss_per_token"]), ref["loss_per_token"]) <= tol["loss"]
     assert rel_max(to64(out["grad_hidden"]), ref["grad_hidden"]) <= tol["grad"]
     assert rel_max(to64(out["grad_W"]), ref["grad_W"]) <= tol["grad"]
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("N,D,V", [
+    (4000, 128, 4096),     # few tiles, many token ranges
+    (3000, 64, 76800),     # bf16: a full round and a split rest; fp32: 512 and 88 of 128
+])
+@pytest.mark.parametrize("ign", [0.5, 0.97, 0.9995, 1.0])
+def test_grad_W_split_by_the_tokens_left(gpu_lib, N, D, V, ign, dtype):
+    """With a mask the tokens left decide on the device into how many ranges
+    dW's last round is split, down to none, and the fixup pass follows: grad_W
+    overwritten (every element, into a NaN-filled tensor) and accumulated."""
+    kd, K, dev = gpu_lib, 8, "cuda"
+    tol = TOL["bf16" if dtype == torch.bfloat16 else "f32"]["grad"]
+    hidden = ki.make_hidden(N, D, dtype, dev, seed=ki.SEED_HIDDEN + 31)
+    W = ki.make_weight(V, D, dtype, dev, seed=ki.SEED_W + 31)
+    idx, logit = ki.make_teacher(N, K, V, dev, seed=ki.SEED_TEACHER + 31)
+    g = torch.Generator(device="cpu")
+    g.manual_seed(ki.SEED_MASK + 31)
+    ignore = (torch.rand(N, generator=g) < ign).to(torch.uint8).to(dev)
+    left = int((ignore == 0).sum())
+    print(f"[dw-left] N={N} D={D} V={V} {dtype}: {left} tokens left", flush=True)
+    code = kd.KD_BF16 if dtype == torch.bfloat16 else kd.KD_F32
+    ws = torch.full((kd.workspace_size(N, D, V, K, 4096, 1.0, code),), 0xff, dtype=torch.uint8,
+                    device=dev)
+    gw = torch.full((V, D), float("nan"), device=dev)
+    out = kd.fwd_bwd(hidden, W, idx, logit, ignore=ignore, workspace=ws, grad_W_out=gw)
+    ref = gw.clone()
+    acc = torch.ones_like(gw)
+    kd.fwd_bwd(hidden, W, idx, logit, ignore=ignore, workspace=ws, grad_hidden=False,
+               grad_W_out=acc, accumulate_grad_W=True)
+    torch.cuda.synchronize()
+    keep = (ignore == 0).nonzero().squeeze(1)
+    if left == 0:
+        assert bool((gw == 0).all()) and bool((acc == 1).all())
+        assert bool((out["grad_hidden"] == 0).all()) and float(out["loss"]) == 0.0
+        return
+    o = oracle_by_row_blocks(kd_topk_kl, to64(hidden[keep]), to64(W), to64(idx[keep]),
+                             to64(logit[keep]), 1.0, block=256)
+    assert rel_max(to64(gw), o["grad_W"]) <= tol
+    # 1 + x rounds to 2^-24 of a sum below 2
+    assert float((acc.double() - 1 - ref.double()).abs().max()) <= 2.0 ** -23
