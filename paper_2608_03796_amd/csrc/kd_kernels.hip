@@ -651,11 +651,13 @@ __global__ void k_lse_merge(const float* part_m, const float* part_s, int rows, 
 // contributes nothing to C or dZ).
 //
 // Latency-bound (one workgroup per 256 tokens). Up to kBucketRegs entries per
-// thread (K <= 128) stay in registers: all of a thread's loads are in flight
-// together, and the atomic that counts an entry also returns its place among
-// the entries of its vocabulary tile, so each entry is read once and takes one
-// atomic (512 tokens, K = 64, V = 32000: 22.5 us, now 12.2 us). More entries are
-// read twice, counted and then placed.
+// thread (K <= 128, or fewer tokens) stay in registers: all of a thread's loads
+// are in flight together, and the atomic that counts an entry also returns its
+// place among the entries of its vocabulary tile, so each entry is read once and
+// takes one atomic (512 tokens, K = 64, V = 32000: 22.5 us, now 12.2 us). More
+// entries are read twice, counted and then placed: a kernel of its own, in which
+// the registers of the first form would cost it a quarter (574 tokens, K = 2932,
+// both passes of a split call: 860 us alone, 1080 beside it).
 constexpr int kBucketThreads = 1024;
 constexpr int kBucketRegs = 32;
 constexpr int kBucketBatch = 8;  // entries per thread whose loads are in flight together
@@ -672,59 +674,72 @@ struct BucketArgs {
   float* zhit;
 };
 
-__device__ __forceinline__ void bucket_tile(const BucketArgs& a, int block) {
+struct BucketLds {
+  int cnt[kMaxVT], cur[kMaxVT], wsum[kBucketThreads / 64];
+};
+
+// ONE: at most kBucketRegs entries per thread. PREP: rowmap may be set, no hitp
+template <bool ONE, bool PREP>
+__device__ __forceinline__ void bucket_tile(const BucketArgs& a, int block, BucketLds& l) {
   const int rows = a.rows, K = a.K, V = a.V, nVT = a.nVT;
-  uint32_t* hits = a.hits;
-  float* hitp = a.hitp;
-  __shared__ int cnt[kMaxVT];
-  __shared__ int cur[kMaxVT];
-  __shared__ int wsum[kBucketThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
   const int t0 = block * kTile;
   const int total = min(kTile, rows - t0) * K;
   const int64_t seg = (int64_t)block * kTile * K;
+  uint32_t* hits = a.hits + seg;
+  float* hitp = PREP || a.hitp == nullptr ? nullptr : a.hitp + seg;
   // entry e of the tile is element t0 K + e of the row-major [rows, K] arrays
-  const float* pt = a.p + (int64_t)t0 * K;
+  const int32_t* __restrict__ ti = a.tidx + (PREP && a.rowmap != nullptr ? 0 : (int64_t)t0 * K);
+  const float* __restrict__ pt = a.p + (int64_t)t0 * K;
   float* zt = a.zhit + (int64_t)t0 * K;
   const float invK = 1.0f / (float)K;
   // token = e / K (exact: e < 2^20, and (e + 0.5) / K stays >= 1/(2K)
   // away from an integer while the float product errs by < 2^-12)
   auto token = [&](int e) { return (int)(((float)e + 0.5f) * invK); };
   auto index = [&](int e) -> int {
-    if (a.rowmap == nullptr) return a.tidx[(int64_t)t0 * K + e];
+    if (!PREP || a.rowmap == nullptr) return ti[(uint32_t)e];
     const int tl = token(e), tok = a.rowmap[t0 + tl];
-    return tok < 0 ? -1 : a.tidx[(int64_t)tok * K + (e - tl * K)];
+    return tok < 0 ? -1 : ti[(int64_t)tok * K + (e - tl * K)];
   };
   auto put = [&](int e, int v, int pos, float pk) {
     const int tl = token(e);
     const int k = e - tl * K;
-    hits[seg + pos] = (uint32_t)tl | ((uint32_t)(v & 255) << 8) | ((uint32_t)k << 16);
-    if (hitp != nullptr) hitp[seg + pos] = pk;
+    hits[(uint32_t)pos] = (uint32_t)tl | ((uint32_t)(v & 255) << 8) | ((uint32_t)k << 16);
+    if (hitp != nullptr) hitp[(uint32_t)pos] = pk;
   };
-  const bool in_regs = total <= kBucketThreads * kBucketRegs;
-  int v[kBucketRegs], rank[kBucketRegs];
-  float pv[kBucketRegs];
-  if (in_regs) {
+  constexpr int NR = ONE ? kBucketRegs : 1;
+  int v[NR], rank[NR];
+  // p a batch ahead of its use (all of it in registers would spill)
+  float pv[2][kBucketBatch];
+  auto load_p = [&](int u0) {
+    if (hitp == nullptr || u0 >= kBucketRegs) return;
+#pragma unroll
+    for (int u = 0; u < kBucketBatch; ++u) {
+      const int e = (u0 + u) * kBucketThreads + tid;
+      pv[u0 / kBucketBatch & 1][u] = e < total ? pt[(uint32_t)e] : 0.f;
+    }
+  };
+  if constexpr (ONE) {
 #pragma unroll
     for (int u = 0; u < kBucketRegs; ++u) {
       const int e = u * kBucketThreads + tid;
       v[u] = e < total ? index(e) : -1;
-      pv[u] = hitp != nullptr && e < total ? pt[e] : 0.f;
     }
   }
-  for (int b = tid; b < nVT; b += kBucketThreads) cnt[b] = 0;
+  for (int b = tid; b < nVT; b += kBucketThreads) l.cnt[b] = 0;
   __syncthreads();
-  if (in_regs) {
+  if constexpr (ONE) {
 #pragma unroll
     for (int u = 0; u < kBucketRegs; ++u) {
       const int e = u * kBucketThreads + tid;
       if (u * kBucketThreads >= total) break;
       rank[u] = 0;
       if ((unsigned)v[u] < (unsigned)V)
-        rank[u] = atomicAdd(&cnt[v[u] >> 8], 1);
+        rank[u] = atomicAdd(&l.cnt[v[u] >> 8], 1);
       else if (e < total)
-        zt[e] = 0.f;
+        zt[(uint32_t)e] = 0.f;
     }
+    load_p(0);
   } else {
     for (int base = 0; base < total; base += kBucketThreads * kBucketBatch) {
       int w[kBucketBatch];
@@ -738,9 +753,9 @@ __device__ __forceinline__ void bucket_tile(const BucketArgs& a, int block) {
         const int e = base + u * kBucketThreads + tid;
         if (e >= total) continue;
         if ((unsigned)w[u] < (unsigned)V)
-          atomicAdd(&cnt[w[u] >> 8], 1);
+          atomicAdd(&l.cnt[w[u] >> 8], 1);
         else
-          zt[e] = 0.f;
+          zt[(uint32_t)e] = 0.f;
       }
     }
   }
@@ -750,35 +765,39 @@ __device__ __forceinline__ void bucket_tile(const BucketArgs& a, int block) {
   int run = 0;
   for (int q = 0; q < R; ++q) {
     const int b = tid * R + q;
-    if (b < nVT) run += cnt[b];
+    if (b < nVT) run += l.cnt[b];
   }
   const int incl = wave_incl_scan(run);
-  if (lane == 63) wsum[wave] = incl;
+  if (lane == 63) l.wsum[wave] = incl;
   __syncthreads();
   if (wave == 0) {
-    const int x = lane < kBucketThreads / 64 ? wsum[lane] : 0;
+    const int x = lane < kBucketThreads / 64 ? l.wsum[lane] : 0;
     const int y = wave_incl_scan(x);
-    if (lane < kBucketThreads / 64) wsum[lane] = y - x;
+    if (lane < kBucketThreads / 64) l.wsum[lane] = y - x;
   }
   __syncthreads();
-  int off = wsum[wave] + incl - run;
+  int off = l.wsum[wave] + incl - run;
   int* ho = a.hoff + (int64_t)block * (nVT + 1);
   for (int q = 0; q < R; ++q) {
     const int b = tid * R + q;
     if (b < nVT) {
-      cur[b] = off;
+      l.cur[b] = off;
       ho[b] = off;
-      off += cnt[b];
+      off += l.cnt[b];
     }
   }
   if (tid == kBucketThreads - 1) ho[nVT] = off;
   __syncthreads();
-  if (in_regs) {
+  if constexpr (ONE) {
 #pragma unroll
-    for (int u = 0; u < kBucketRegs; ++u) {
-      if (u * kBucketThreads >= total) break;
-      if ((unsigned)v[u] < (unsigned)V)
-        put(u * kBucketThreads + tid, v[u], cur[v[u] >> 8] + rank[u], pv[u]);
+    for (int u0 = 0; u0 < kBucketRegs; u0 += kBucketBatch) {
+      if (u0 * kBucketThreads >= total) break;
+      load_p(u0 + kBucketBatch);
+#pragma unroll
+      for (int u = u0; u < u0 + kBucketBatch; ++u)
+        if ((unsigned)v[u] < (unsigned)V)
+          put(u * kBucketThreads + tid, v[u], l.cur[v[u] >> 8] + rank[u],
+              pv[u / kBucketBatch & 1][u % kBucketBatch]);
     }
     return;
   }
@@ -789,19 +808,22 @@ __device__ __forceinline__ void bucket_tile(const BucketArgs& a, int block) {
     for (int u = 0; u < kBucketBatch; ++u) {
       const int e = base + u * kBucketThreads + tid;
       w[u] = e < total ? index(e) : -1;
-      pw[u] = hitp != nullptr && e < total ? pt[e] : 0.f;
+      pw[u] = hitp != nullptr && e < total ? pt[(uint32_t)e] : 0.f;
     }
 #pragma unroll
     for (int u = 0; u < kBucketBatch; ++u) {
       const int e = base + u * kBucketThreads + tid;
       if (e >= total || (unsigned)w[u] >= (unsigned)V) continue;
-      put(e, w[u], atomicAdd(&cur[w[u] >> 8], 1), pw[u]);
+      put(e, w[u], atomicAdd(&l.cur[w[u] >> 8], 1), pw[u]);
     }
   }
 }
 
+// after the prologue, from its copy of the indices (no rowmap); ONE as above
+template <bool ONE>
 __global__ __launch_bounds__(kBucketThreads) void k_bucket(BucketArgs a) {
-  bucket_tile(a, blockIdx.x);
+  __shared__ BucketLds l;
+  bucket_tile<ONE, false>(a, blockIdx.x, l);
 }
 
 // The prologue of a row per wave and, in the first `nb` workgroups (K <=
@@ -816,8 +838,10 @@ template <typename T>
 __global__ __launch_bounds__(kBucketThreads) void k_prep(PrologueArgs a, BucketArgs b, int nb) {
   constexpr int kRowLds = prologue_lds(kPrepMaxK), NWV = kBucketThreads / 64;
   __shared__ __attribute__((aligned(16))) char lds[NWV * kRowLds];
+  __shared__ BucketLds l;
+  static_assert(kPrepMaxK * kTile <= kBucketThreads * kBucketRegs, "entries in registers");
   if ((int)blockIdx.x < nb) {
-    bucket_tile(b, blockIdx.x);
+    bucket_tile<true, true>(b, blockIdx.x, l);
     return;
   }
   const int wave = wave_id();
@@ -2135,7 +2159,9 @@ static int launch_chunk_impl(const KdChunkArgs& a, hipStream_t s) {
                            dim3(kBucketThreads), 0, s, p, b, nbt);
       } else {
         hipLaunchKernelGGL(k_prologue<T>, dim3(a.rows), dim3(64), (size_t)prologue_lds(a.K), s, p);
-        hipLaunchKernelGGL(k_bucket, dim3(nbt), dim3(kBucketThreads), 0, s, b);
+        const bool one = std::min(a.rows, kTile) * a.K <= kBucketThreads * kBucketRegs;
+        hipLaunchKernelGGL(one ? k_bucket<true> : k_bucket<false>, dim3(nbt), dim3(kBucketThreads),
+                           0, s, b);
       }
     }
   }

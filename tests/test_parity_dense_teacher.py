@@ -47,3 +47,13 @@ def _check(kd, N, D, V, K, dtype, masked):
 ])
 def test_crowded_tiles(gpu_lib, N, D, V, K, masked, dtype):
     _check(gpu_lib, N, D, V, K, dtype, masked)
+
+
+@pytest.mark.parametrize("N,K,masked", [
+    (256, 128, 0.0), (256, 129, 0.0),     # entries of a tile kept in registers, read twice
+    (300, 129, 0.3), (254, 129, 0.0),
+    (64, 512, 0.0), (64, 513, 0.0), (64, 512, 0.5),
+    (1, 4096, 0.0), (9, 4096, 0.0),
+])
+def test_entries_per_tile(gpu_lib, N, K, masked):
+    _check(gpu_lib, N, 64, 5000, K, "bf16", masked)
