@@ -96,8 +96,8 @@ typedef struct kd_problem {
 #define KD_FLAG_GRAD_HIDDEN_F32 2
 
 /*
- * Bytes of device workspace kd_topk_kl_fwd_bwd, kd_topk_kl_fwd,
- * kd_topk_kl_bwd and kd_topk_kl_check_indices need for problem *p. Pure host
+ * Bytes of device workspace kd_topk_kl_fwd_bwd, kd_topk_kl_fwd and
+ * kd_topk_kl_bwd need for problem *p. Pure host
  * function: touches no device. The size is O(N/4 + G C_s (V + K + 1) + D G C_s),
  * with G C_s <= 16384 the tokens whose dZ rows one grad_W contraction
  * gathers (at most 4 GiB of them), plus at most 128 MiB for the partial tiles
@@ -259,7 +259,8 @@ kd_status kd_topk_kl_bwd(const kd_problem* p,
  * them, but a top-K cache never repeats an index, so a repeat points at a
  * broken cache). Synchronises `hip_stream`.
  * Returns KD_OK, KD_ERR_BAD_INDEX, or an argument/device error. Uses the
- * first bytes of `workspace` (same size rule as kd_topk_kl_fwd_bwd).
+ * first 256 bytes of `workspace` (KD_ERR_WORKSPACE_TOO_SMALL if it has fewer),
+ * whatever the problem's D, chunk and dtype.
  *
  * Debug mode: with the environment variable KD_DEBUG_CHECK set to 1 when a
  * call is made, kd_topk_kl_fwd_bwd, kd_topk_kl_fwd and kd_topk_kl_bwd run

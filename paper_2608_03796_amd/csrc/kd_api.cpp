@@ -26,6 +26,8 @@ constexpr int64_t kMaxChunk = (int64_t)1 << 20; // rows per chunk actually used
 // 20 bits by the bucket pass, and k is packed in 16
 constexpr int64_t kMaxK = 4096;
 
+// the first bytes of every workspace: scalars, among them the index check's flag
+constexpr size_t kMiscBytes = 256;
 // no limit to the partial tiles of dH (see kd_dh_rounds): two rounds of 256 x 256
 constexpr int kPartSpaceMax = 512 * 256 * 256 / 64;
 
@@ -221,7 +223,7 @@ Plan base_plan(const kd_problem* p, int64_t g_max = 0) {
     t = o + bytes;
     return o;
   };
-  pl.off_misc = take(256);
+  pl.off_misc = take(kMiscBytes);
   pl.off_p = take((size_t)pl.ng * pl.K * 4);
   pl.off_tidx = take((size_t)pl.ng * pl.K * 4);
   pl.off_rows = take((size_t)7 * pl.ng * 4);
@@ -669,9 +671,8 @@ kd_status kd_topk_kl_check_indices(const kd_problem* p, const int32_t* teacher_i
   if (st != KD_OK) return st;
   if (workspace == nullptr || (p->N > 0 && teacher_idx == nullptr)) return KD_ERR_NULL_PTR;
   if (!aligned16(workspace)) return KD_ERR_UNSUPPORTED;
-  const Plan pl = make_plan(p);
-  if (workspace_bytes < pl.total) return KD_ERR_WORKSPACE_TOO_SMALL;
-  int* flag = reinterpret_cast<int*>(static_cast<char*>(workspace) + pl.off_misc + 8);
+  if (workspace_bytes < kMiscBytes) return KD_ERR_WORKSPACE_TOO_SMALL;
+  int* flag = reinterpret_cast<int*>(static_cast<char*>(workspace) + 8);
   int host_flag = 0;
   if (kd_launch_check_indices(teacher_idx, p->N, p->K, p->V, flag, &host_flag, hip_stream) != 0)
     return KD_ERR_DEVICE;

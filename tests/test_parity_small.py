@@ -272,6 +272,18 @@ def test_check_indices(gpu_lib):
     assert not gpu_lib.check_indices(dup, V=1000)
 
 
+def test_check_indices_in_the_loss_workspace(gpu_lib):
+    """The check with a workspace sized for the loss, where the problem that
+    check_indices describes by default (D = 64) has a larger one."""
+    N, D, V, K, chunk = 583, 320, 419, 10, 20
+    idx, _ = ki.make_teacher(N, K, V, "cuda", seed=15)
+    ws = gpu_lib.alloc_workspace(N, D, V, K, chunk, 1.0, gpu_lib.KD_BF16, idx.device)
+    assert ws.numel() < gpu_lib.workspace_size(N, 64, V, K, chunk)
+    assert gpu_lib.check_indices(idx, V=V, chunk=chunk, workspace=ws)
+    idx[N - 1, K - 1] = V
+    assert not gpu_lib.check_indices(idx, V=V, chunk=chunk, workspace=ws)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("logprobs", [False, True])
 def test_repeated_teacher_indices(gpu_lib, dtype, logprobs):

@@ -108,3 +108,13 @@ def test_no_partial_tile_past_the_scratch(host):
                       for d in (1, r["tile"] // 2, r["tile"])}:
                 assert host.rec_dh_bytes(n, D, int(r["tile"]), int(r["ksteps"]), int(eb == 4),
                                          i64(r["part_bytes"])) <= r["part_bytes"]
+
+
+def test_index_check_needs_only_its_own_bytes(host):
+    """256 bytes, not the workspace of the problem: a check that describes
+    another D or chunk than the workspace was sized for is not refused."""
+    for N, D, V, chunk in ((14163, 64, 42568, 349), (583, 64, 419, 20)):
+        pr = kd.problem(N, D, V, 10, chunk, 1.0, kd.KD_BF16)
+        for size, rc in ((255, 5), (256, 0), (1 << 20, 0)):
+            assert host.kd_topk_kl_check_indices(ctypes.byref(pr), FAKE, FAKE,
+                                                 ctypes.c_size_t(size), None) == rc
