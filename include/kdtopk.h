@@ -332,7 +332,8 @@ kd_status kd_topk_kl_fwd_bwd_noalloc(const kd_problem* p,
  *
  * Each output is rounded once to its dtype (KD_F32 or KD_BF16). An fp32
  * output may be its input itself (in place); otherwise output and input must
- * not overlap. A NULL pair (or a zero count) skips that gradient.
+ * not overlap. A NULL pair (or a zero count) skips that gradient. grad_hidden
+ * comes first where one pair's buffers overlap what the other writes.
  * Asynchronous on hip_stream. Errors, all detected before any launch:
  * KD_ERR_NULL_PTR (grad_loss NULL, or one of a pair NULL), KD_ERR_BAD_SHAPE
  * (a negative count), KD_ERR_UNSUPPORTED (an output dtype other than KD_F32

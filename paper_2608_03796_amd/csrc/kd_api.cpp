@@ -679,18 +679,20 @@ kd_status kd_topk_kl_check_indices(const kd_problem* p, const int32_t* teacher_i
   return host_flag ? KD_ERR_BAD_INDEX : KD_OK;
 }
 
+static bool overlap(const void* a, int64_t an, const void* b, int64_t bn) {
+  return (uintptr_t)a < (uintptr_t)b + (uintptr_t)bn && (uintptr_t)b < (uintptr_t)a + (uintptr_t)an;
+}
+
 // Checks one gradient of kd_scale_grads: in [n] fp32 -> out [n] dtype.
-static kd_status scale_one(const float* g, const float* in, int32_t dtype, void* out, int64_t n,
-                    void* stream) {
+static kd_status check_scale(const float* in, int32_t dtype, const void* out, int64_t n) {
   if ((in == nullptr) != (out == nullptr)) return KD_ERR_NULL_PTR;
   if (n < 0) return KD_ERR_BAD_SHAPE;
   if (in == nullptr || n == 0) return KD_OK;
   if (dtype != KD_F32 && dtype != KD_BF16) return KD_ERR_UNSUPPORTED;
   if (!aligned16(in) || !aligned16(out)) return KD_ERR_UNSUPPORTED;
   // fp32 output: in place or disjoint; bf16 output: disjoint from the input
-  const uintptr_t a0 = (uintptr_t)in, a1 = a0 + (uintptr_t)n * 4;
-  const uintptr_t b0 = (uintptr_t)out, b1 = b0 + (uintptr_t)n * (dtype == KD_F32 ? 4 : 2);
-  if (a0 < b1 && b0 < a1 && !(dtype == KD_F32 && a0 == b0)) return KD_ERR_BAD_ARG;
+  if (overlap(in, n * 4, out, n * (dtype == KD_F32 ? 4 : 2)) && !(dtype == KD_F32 && in == out))
+    return KD_ERR_BAD_ARG;
   return KD_OK;
 }
 
@@ -699,15 +701,23 @@ kd_status kd_scale_grads(const float* grad_loss, const float* grad_hidden_f32,
                          const float* grad_W_f32, int32_t w_dtype, void* grad_W_out, int64_t n_W,
                          void* hip_stream) {
   if (grad_loss == nullptr) return KD_ERR_NULL_PTR;
-  kd_status st = scale_one(grad_loss, grad_hidden_f32, hidden_dtype, grad_hidden_out, n_hidden,
-                           hip_stream);
+  kd_status st = check_scale(grad_hidden_f32, hidden_dtype, grad_hidden_out, n_hidden);
   if (st != KD_OK) return st;
-  st = scale_one(grad_loss, grad_W_f32, w_dtype, grad_W_out, n_W, hip_stream);
+  st = check_scale(grad_W_f32, w_dtype, grad_W_out, n_W);
   if (st != KD_OK) return st;
+  const KdScaleArg none{nullptr, nullptr, 0, 0};
   const KdScaleArg h{grad_hidden_f32, grad_hidden_out, grad_hidden_f32 != nullptr ? n_hidden : 0,
                      hidden_dtype == KD_BF16};
   const KdScaleArg w{grad_W_f32, grad_W_out, grad_W_f32 != nullptr ? n_W : 0, w_dtype == KD_BF16};
-  if (kd_launch_scale(&h, &w, grad_loss, hip_stream) != 0) return KD_ERR_DEVICE;
+  // one launch, or one after the other where a gradient reads or writes what the
+  // other one writes
+  const int64_t hb = h.n * (h.out_bf16 ? 2 : 4), wb = w.n * (w.out_bf16 ? 2 : 4);
+  const bool ordered = h.n > 0 && w.n > 0 &&
+                       (overlap(h.y, hb, w.x, w.n * 4) || overlap(h.y, hb, w.y, wb) ||
+                        overlap(h.x, h.n * 4, w.y, wb));
+  if (kd_launch_scale(&h, ordered ? &none : &w, grad_loss, hip_stream) != 0 ||
+      (ordered && kd_launch_scale(&w, &none, grad_loss, hip_stream) != 0))
+    return KD_ERR_DEVICE;
   return KD_OK;
 }
 

@@ -6,6 +6,7 @@
 #include "../paper_2608_03796_amd/csrc/kd_launch.h"
 
 namespace {
+// kind 3: a launch of kd_scale_grads, its two element counts
 // one launch of dH (kind 1) or dW (kind 2): its token rows, tile edge, whole
 // tiles, tiles and parts of the split last round, K steps, the bytes its partial
 // tiles may take, and the scratch bytes up to the end of these
@@ -42,7 +43,10 @@ int kd_launch_fill(float*, int64_t, void*) { return 0; }
 int kd_launch_chunk(const KdChunkArgs*, void*) { return 0; }
 int kd_launch_compact(const KdCompactArgs*, void*) { return 0; }
 int kd_launch_tail(const KdTailArgs*, void*) { return 0; }
-int kd_launch_scale(const KdScaleArg*, const KdScaleArg*, const float*, void*) { return 0; }
+int kd_launch_scale(const KdScaleArg* a, const KdScaleArg* b, const float*, void*) {
+  recs.push_back({3, a->n, b->n, 0, 0, 0, 0, 0, 0});
+  return 0;
+}
 int kd_launch_dh(const KdDhArgs* a, void*) {
   const int eb = a->dtype == 1 ? 2 : 4, ksteps = (int)(a->ldz * eb / 128);
   record(1, a->tokens, a->tile,

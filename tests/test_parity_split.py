@@ -304,6 +304,17 @@ def test_scale_grads(gpu_lib, n):
     assert torch.equal(out_bf2.cpu(), ref2.to(torch.bfloat16))
 
 
+def test_scale_grads_through_a_shared_buffer(gpu_lib):
+    """The second gradient's input is the first one's output: scaled twice."""
+    n = 3000000
+    x = torch.arange(n, dtype=torch.float32, device="cuda") % 1000
+    mid, out = torch.empty_like(x), torch.empty_like(x)
+    g = torch.tensor([3.0], dtype=torch.float32, device="cuda")
+    gpu_lib.scale_grads(g, grad_hidden=x, grad_hidden_out=mid, grad_W=mid, grad_W_out=out)
+    torch.cuda.synchronize()
+    assert torch.equal(mid, 3 * x) and torch.equal(out, 9 * x)
+
+
 @pytest.mark.parametrize("chunk", [100, 300])
 def test_grad_hidden_f32_flag(gpu_lib, chunk):
     """KD_FLAG_GRAD_HIDDEN_F32 (fused call and split backward): grad_hidden in

@@ -118,3 +118,25 @@ def test_index_check_needs_only_its_own_bytes(host):
         for size, rc in ((255, 5), (256, 0), (1 << 20, 0)):
             assert host.kd_topk_kl_check_indices(ctypes.byref(pr), FAKE, FAKE,
                                                  ctypes.c_size_t(size), None) == rc
+
+
+def test_scaled_gradients_that_share_buffers_keep_their_order(host):
+    """Both gradients in one launch, unless one writes what the other reads or
+    writes: then grad_hidden first, as two launches."""
+    def launches(hin, hdt, hout, nh, win, wdt, wout, nw):
+        host.rec_clear()
+        v = ctypes.c_void_p
+        i64 = ctypes.c_int64
+        assert host.kd_scale_grads(FAKE, v(hin), hdt, v(hout), i64(nh), v(win), wdt, v(wout),
+                                   i64(nw), None) == 0
+        return [(r["tokens"], r["tile"]) for r in _launches(host, 3)]
+    A, B, C, D = (0x10000 * (i + 1) for i in range(4))
+    n = 4096  # 0x4000 bytes of fp32
+    f32, bf16 = kd.KD_F32, kd.KD_BF16
+    assert launches(A, bf16, B, n, C, f32, C, n) == [(n, n)]
+    assert launches(A, bf16, B, n, A, f32, D, n) == [(n, n)]          # the same input
+    assert launches(A, f32, B, n, B, bf16, C, n) == [(n, 0), (n, 0)]  # reads what the first writes
+    assert launches(A, bf16, B, n, C, f32, A, n) == [(n, 0), (n, 0)]  # writes what the first reads
+    assert launches(A, bf16, B, n, C, bf16, B + 0x1000, n) == [(n, 0), (n, 0)]
+    assert launches(A, bf16, B, n, C, bf16, B + 0x2000, n) == [(n, n)]
+    assert launches(A, f32, B, n, None, f32, None, n) == [(n, 0)]
