@@ -1217,9 +1217,10 @@ __global__ void k_row_loss(const float* zhit, const float* p, int K, const float
   if (r < rows && tok >= 0) {
     float c = 0.f;
     for (int k = lane; k < K; k += 64) {
-      const float pk = p[(int64_t)r * K + k];
-      // (a repeated index has p = 0 and a z that need not be finite)
-      if (pk != 0.f) c += pk * zhit[(int64_t)r * K + k];
+      // (both loads at once; a repeated index has p = 0 and a z that need not be
+      // finite)
+      const float pk = p[(int64_t)r * K + k], z = zhit[(int64_t)r * K + k];
+      c += pk != 0.f ? pk * z : 0.f;
     }
     c = wave_sum(c);
     const bool valid = rowmap != nullptr || ignore == nullptr || ignore[row0 + r] == 0;
