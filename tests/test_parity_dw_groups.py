@@ -215,3 +215,43 @@ def test_grad_W_split_by_the_tokens_left(gpu_lib, N, D, V, ign, dtype):
     assert rel_max(to64(gw), o["grad_W"]) <= tol
     # 1 + x rounds to 2^-24 of a sum below 2
     assert float((acc.double() - 1 - ref.double()).abs().max()) <= 2.0 ** -23
+
+
+@pytest.mark.parametrize("dtype,V", [(torch.bfloat16, 5000), (torch.float32, 2000)])
+@pytest.mark.parametrize("ign", [0.0, 0.05, 0.3])
+def test_dh_per_chunk_with_a_split_last_chunk(gpu_lib, dtype, V, ign):
+    """Three chunks in one dW group whose dH runs chunk by chunk: the first two in
+    whole rounds, the last one's 252 rows split along the vocabulary, its parts
+    added up by the tail at the rows' place in the group (the row factors, the row
+    map and the device's count are the group's). With 5% ignored part of the last
+    chunk is left, with 30% none of it and half of the second."""
+    N, D, K, chunk, kd, dev = 2300, 16384, 8, 1024, gpu_lib, "cuda"
+    tol = TOL["bf16" if dtype == torch.bfloat16 else "f32"]
+    hidden = ki.make_hidden(N, D, dtype, dev, seed=ki.SEED_HIDDEN + 41, std=0.5)
+    W = ki.make_weight(V, D, dtype, dev, seed=ki.SEED_W + 41)
+    idx, logit = ki.make_teacher(N, K, V, dev, seed=ki.SEED_TEACHER + 41)
+    ignore = None
+    if ign:
+        g = torch.Generator(device="cpu")
+        g.manual_seed(ki.SEED_MASK + 41)
+        ignore = (torch.rand(N, generator=g) < ign).to(torch.uint8).to(dev)
+    print(f"[dh-last] V={V} {dtype} ignored={ign}", flush=True)
+    code = kd.KD_BF16 if dtype == torch.bfloat16 else kd.KD_F32
+    ws = torch.full((kd.workspace_size(N, D, V, K, chunk, 1.0, code),), 0xff, dtype=torch.uint8,
+                    device=dev)
+    kw = dict(ignore=ignore, chunk=chunk, workspace=ws)
+    gh = torch.full((N, D), float("nan"), dtype=dtype, device=dev)
+    out = kd.fwd_bwd(hidden, W, idx, logit, loss_per_token=True, out={"grad_hidden": gh}, **kw)
+    f = kd.fwd(hidden, W, idx, logit, **kw)
+    b = kd.bwd(hidden, W, idx, logit, f["saved_logz"], **kw)
+    torch.cuda.synchronize()
+    ref = oracle_by_row_blocks(kd_topk_kl, to64(hidden), to64(W), to64(idx), to64(logit), 1.0,
+                               ignore=to64(ignore), block=256)
+    assert rel_max(to64(out["loss_per_token"]), ref["loss_per_token"]) <= tol["loss"]
+    for r in (out, b):
+        assert rel_max(to64(r["grad_hidden"]), ref["grad_hidden"]) <= tol["grad"]
+        assert rel_max(to64(r["grad_W"]), ref["grad_W"]) <= tol["grad"]
+    # the rows of the split last chunk by themselves
+    last = slice(1024 * (N // 1024), N)
+    if np.abs(ref["grad_hidden"][last]).max() > 0:
+        assert rel_max(to64(out["grad_hidden"])[last], ref["grad_hidden"][last]) <= tol["grad"]
