@@ -14,8 +14,6 @@
 namespace kd {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
-typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4_t;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4_t;
 typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2_t;
@@ -59,9 +57,6 @@ __device__ __forceinline__ void tile_at(int L, int TM, int TN, int gm, int& mt, 
   const int rem = L - g * per_group;
   mt = first_m + rem % gs;
   nt = rem / gs;
-}
-__device__ __forceinline__ void tile_coords(int pid, int TM, int TN, int gm, int& mt, int& nt) {
-  tile_at(tile_order_xcd(pid, TM * TN), TM, TN, gm, mt, nt);
 }
 
 template <typename T>
@@ -199,13 +194,6 @@ __device__ __forceinline__ void dma_b128(i32x4_t r, uint32_t lds_addr, uint32_t 
                : "s"(lds_addr), "v"(voff), "s"(r)
                : "memory");
 }
-// 4-byte-per-lane LDS-DMA load: lane i's dword at voffset lands at lds_addr + 4 i.
-__device__ __forceinline__ void dma_b32(i32x4_t r, uint32_t lds_addr, uint32_t voff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
-               :
-               : "s"(lds_addr), "v"(voff), "s"(r)
-               : "memory");
-}
 __device__ __forceinline__ uint32_t lds_addr(const char* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p;
 }
@@ -223,11 +211,11 @@ struct DmaStep {
 
 // An operand's stage (TS rows of 128 bytes) is TS/8 instructions of 1 KiB; wave
 // w issues instructions w*NPW .. w*NPW + NPW - 1.
-template <typename T, typename Op, int NPW, int TS>
+template <typename Op, int NPW, int TS>
 struct OpDma;
 
-template <typename T, int NPW, int TS>
-struct OpDma<T, KcOp, NPW, TS> {
+template <int NPW, int TS>
+struct OpDma<KcOp, NPW, TS> {
   uint32_t voff[NPW];
   i32x4_t r;
   __device__ __forceinline__ void init(const KcOp& op, int wave, int lane) {
@@ -251,9 +239,9 @@ struct OpDma<T, KcOp, NPW, TS> {
   }
 };
 
-template <typename T, int NPW, int TS>
-struct OpDma<T, KmOp, NPW, TS> {
-  static constexpr int KS = kRowB / (int)sizeof(T);  // K rows per step
+template <int NPW, int TS>
+struct OpDma<KmOp, NPW, TS> {
+  static constexpr int KS = kRowB / 2;  // K rows per step
   uint32_t voff[NPW];
   __device__ __forceinline__ void init(const KmOp& op, int wave, int lane) {
 #pragma unroll
@@ -283,11 +271,11 @@ struct OpDma<T, KmOp, NPW, TS> {
 // Sub-step s of a K step covers K elements [s*KS/2, (s+1)*KS/2) of the step;
 // lane (g = lane/16, j = lane%16) holds row base + 16b + j with K elements
 // s*KS/2 + 8g + 0..7, in both layouts.
-template <typename T, typename Op, int NB, int TS>
+template <typename Op, int NB, int TS>
 struct OpFrag;
 
-template <typename T, int NB, int TS>
-struct OpFrag<T, KcOp, NB, TS> {
+template <int NB, int TS>
+struct OpFrag<KcOp, NB, TS> {
   static constexpr int kReads = NB;
   int rd[NB], fx[NB];
   __device__ __forceinline__ void init(int base, int lane) {
@@ -304,7 +292,7 @@ struct OpFrag<T, KcOp, NB, TS> {
 };
 
 template <int NB, int TS>
-struct OpFrag<__bf16, KmOp, NB, TS> {
+struct OpFrag<KmOp, NB, TS> {
   static constexpr int kReads = 2 * NB;
   static constexpr int kRow = TS * 2;     // bytes of a K row in LDS
   int off[NB];                            // byte offset at sub-step 0, h = 0
@@ -331,7 +319,7 @@ struct OpFrag<__bf16, KmOp, NB, TS> {
 // SPREAD selects the fragment-read placement: false puts one read per MFMA
 // pair in order, true spreads them evenly, fragment f with pair f * NP / 12.
 // Which one is faster depends on the operand layouts (measured per kernel).
-template <typename T, typename OA, typename OB, bool SPREAD>
+template <typename OA, typename OB, bool SPREAD>
 __device__ __forceinline__ void gemm_tile(const OA& opa, const OB& opb, int ks_begin, int ks_end,
                                           char* lds, AccTile<256>& acc) {
   typedef Geo<256> G;
@@ -356,12 +344,12 @@ __device__ __forceinline__ void gemm_tile(const OA& opa, const OB& opb, int ks_b
     return;
   }
 
-  OpDma<T, OA, NPW, 256> da;
-  OpDma<T, OB, NPW, 256> db;
+  OpDma<OA, NPW, 256> da;
+  OpDma<OB, NPW, 256> db;
   da.init(opa, wave, lane);
   db.init(opb, wave, lane);
-  OpFrag<T, OA, 8, 256> fra;
-  OpFrag<T, OB, NJ, 256> frb;
+  OpFrag<OA, 8, 256> fra;
+  OpFrag<OB, NJ, 256> frb;
   fra.init(wm * 128, lane);
   frb.init(wn * 64, lane);
 
@@ -372,8 +360,8 @@ __device__ __forceinline__ void gemm_tile(const OA& opa, const OB& opb, int ks_b
   auto mfma2 = [&](int q, const u32x4_t (&fa)[8], const u32x4_t (&fb)[NJ]) {
     const int i = q / (NJ / 2), jj = 2 * (q % (NJ / 2));
     const int j0 = (i & 1) ? NJ - 1 - jj : jj, j1 = (i & 1) ? NJ - 2 - jj : jj + 1;
-    acc.v[i][j0] = mfma_slot(fa[i], fb[j0], acc.v[i][j0], (T*)nullptr);
-    acc.v[i][j1] = mfma_slot(fa[i], fb[j1], acc.v[i][j1], (T*)nullptr);
+    acc.v[i][j0] = mfma_slot(fa[i], fb[j0], acc.v[i][j0], (__bf16*)nullptr);
+    acc.v[i][j1] = mfma_slot(fa[i], fb[j1], acc.v[i][j1], (__bf16*)nullptr);
   };
 
   {
@@ -489,12 +477,12 @@ __device__ __forceinline__ void gemm_small(const OA& opa, const OB& opb, int ks_
     __syncthreads();
     return;
   }
-  OpDma<__bf16, OA, NPW, 128> da;
-  OpDma<__bf16, OB, NPW, 128> db;
+  OpDma<OA, NPW, 128> da;
+  OpDma<OB, NPW, 128> db;
   da.init(opa, wave, lane);
   db.init(opb, wave, lane);
-  OpFrag<__bf16, OA, 4, 128> fra;
-  OpFrag<__bf16, OB, 4, 128> frb;
+  OpFrag<OA, 4, 128> fra;
+  OpFrag<OB, 4, 128> frb;
   fra.init(wm * 64, lane);
   frb.init(wn * 64, lane);
   auto fill = [&](int stage, int ks) {

@@ -311,7 +311,7 @@ __device__ __forceinline__ void prologue_row(const PrologueArgs& a, int r, char*
 template <typename T, int TS, bool SPREAD, typename OA, typename OB>
 __device__ __forceinline__ void gemm(const OA& a, const OB& b, int kb, int ke, char* lds,
                                      AccTile<TS>& acc) {
-  if constexpr (TS == 256) gemm_tile<T, OA, OB, SPREAD>(a, b, kb, ke, lds, acc);
+  if constexpr (TS == 256) gemm_tile<OA, OB, SPREAD>(a, b, kb, ke, lds, acc);
   else if constexpr (sizeof(T) == 2) gemm_small<OA, OB>(a, b, kb, ke, lds, acc);
   else gemm_f32<OA, OB>(a, b, kb, ke, lds, acc);
 }
@@ -859,11 +859,11 @@ __global__ __launch_bounds__(64) void k_prologue(PrologueArgs a) {
 // (one per thread) are loaded into registers, so the epilogue issues no
 // global loads (a load waited for after a store would also wait for that
 // store); after the loop the scalars go to LDS beside the staging area.
-// The fp32 tile is staged 128 tokens at a time as [token][vocab] with a
+// The fp32 tile is staged half its tokens at a time as [token][vocab] with a
 // 16-byte-slot swizzle; each teacher entry of the half is patched in place to
-// its final value (g/tau)(M q - p), its z is recorded for C, and a bitmap marks
-// it; then one wave per token row forms G = (g/tau) M 2^(y - L2) elsewhere and
-// stores the row of dZ[rows, Vp] (columns V..Vp as zeros).
+// its final value (g/tau)(M q - p), and a bitmap marks it; then one wave per token
+// row forms G = (g/tau) M 2^(y - L2) elsewhere and stores the row of dZ[rows, Vp]
+// (columns V..Vp: finite values of z = 0).
 // epilogue LDS (the main loop's stages are free by then), after the staging area
 template <int TS>
 constexpr int kDzBits = stage_bytes<TS>;                // TS/2 x TS-bit hit map of one half
@@ -878,7 +878,7 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dz(
     float k2, const float* __restrict__ rowL2, const float* __restrict__ rowCoef,
     const float* __restrict__ rowCoefM, const uint32_t* __restrict__ hits,
     const float* __restrict__ hitp, const int* __restrict__ hoff, int K, int nVT, T* dZ,
-    int64_t ldz, float* zhit, const int* __restrict__ nrow, int nrow_base) {
+    int64_t ldz, const int* __restrict__ nrow, int nrow_base) {
   typedef Geo<TS> G;
   constexpr int kThreads = G::kThreads, HT = TS / 2;  // HT: tokens staged at a time
   __shared__ __attribute__((aligned(16))) char lds[gemm_lds<T, TS>];
@@ -949,9 +949,8 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dz(
     for (int q = tid; q < HT * TS / 32; q += kThreads) hbits[q] = 0u;
     __syncthreads();
 
-    // Teacher entries of this half: dZ = (g/tau) M q - (g/tau) p in place,
-    // z kept for C = sum_k p z (Eq. 2). Thread tid has entry tid of the
-    // bucket in registers; a skewed teacher with more entries in one tile
+    // Teacher entries of this half: dZ = (g/tau) M q - (g/tau) p in place.
+    // Thread tid has entry tid of the bucket in registers; a skewed teacher with more entries in one tile
     // than threads reads the rest from memory.
     auto fold = [&](uint32_t e, float pk) {
       int tl, v;
@@ -959,7 +958,6 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dz(
       const int n = tl & (HT - 1);
       float* cell = stage_cell<TS>(st, n, v);
       const float z = *cell;
-      if (zhit != nullptr) zhit[(int64_t)(n0 + tl) * K + (e >> 16)] = z;
       *cell = rs_cm[tl] * fast_exp2(z * k2 - rs_l2[tl]) - rs_cf[tl] * pk;
       atomicOr(&hbits[n * (TS / 32) + (v >> 5)], 1u << (v & 31));
     };
@@ -2096,7 +2094,7 @@ static void launch_projection(const KdChunkArgs& a, int first, int count, hipStr
     ProfScope ps_(P_DZ, flops, s);
     hipLaunchKernelGGL((k_dz<T, TS>), grid, block, 0, s, W, Hc, (int)a.D, (int)a.V, a.rows, t, k2,
                        a.rowL2, a.rowCoef, a.rowCoefM, a.hits, a.hitp, a.hoff, a.K, a.nVT,
-                       static_cast<T*>(a.dZ), a.ldz, (float*)nullptr, a.nrow, a.nrow_base);
+                       static_cast<T*>(a.dZ), a.ldz, a.nrow, a.nrow_base);
   }
 }
 
