@@ -1477,22 +1477,25 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dh(DhA
   const int lane = tid & 63, wave = wave_id();
   const int wm = G::wm(wave), wn = G::wn(wave);
   if (part >= 0) {
-    const bool rows_d = sp.dp == 0;  // the range's [n, D] array, or a tile of its own
-    const int pitch = rows_d ? D : TS, cols = rows_d ? D - n0 : TS;
+    // into the range's [n, D] array or a tile of its own, rows past n out of the
+    // resource's range; the wave's 64 columns all exist or none
+    const bool rows_d = sp.dp == 0;
+    const int pitch = rows_d ? D : TS;
     float* dst = a.partial + (rows_d ? ((int64_t)part * n + m0) * D + n0
                                      : (int64_t)((L - sp.dp) * sp.split + part) * TS * TS);
+    const __amdgpu_buffer_rsrc_t ro = make_rsrc(
+        dst, 4u * (uint32_t)__builtin_amdgcn_readfirstlane(rows_d ? (n - m0) * D - n0
+                                                                  : min(TS, n - m0) * TS));
+    if (rows_d && n0 + wn * 64 >= D) return;
+    const uint32_t o0 = 4u * (uint32_t)(G::acc_m(wm, 0, lane, 0) * pitch + G::acc_n(wn, 0, lane));
 #pragma unroll
     for (int i = 0; i < G::NI; ++i)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = G::acc_m(wm, i, lane, r);
-        if (m0 + m >= n) continue;
+      for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int c = G::acc_n(wn, j, lane);
-          if (c < cols) dst[(int64_t)m * pitch + c] = acc.v[i][j][r];
-        }
-      }
+        for (int j = 0; j < 4; ++j)
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, acc.v[i][j][r]), ro,
+                                                o0 + 64u * j, 4 * (16 * i + r) * pitch, 0);
     return;
   }
   float* rsl = reinterpret_cast<float*>(lds);
