@@ -389,16 +389,18 @@ __device__ __forceinline__ bool entry_cell(uint32_t e, int m0, int n0, int& tl, 
   return TS == 256 || ((unsigned)tl < (unsigned)TS && (unsigned)v < (unsigned)TS);
 }
 
-// f(entry, p) for entries q0, q0 + threads, ... of a tile's bucket (p null: 0).
-// Each is a load and what depends on it, one latency after the other: a small
-// tile, whose bucket is that of four tiles, loads eight at a time. Where
-// the entries crowd few vocabulary tiles (190 x 128 x 351, K = 351) the projection
-// took 94 us one by one, now 44.
+// f(entry, p) for the entries of a tile's bucket past the first one of each thread
+// (p null: 0). Each is a load and what depends on it, one latency after the
+// other: a small tile, whose bucket is that of four tiles, loads four at a time.
+// Where the entries crowd few vocabulary tiles (190 x 128 x 351, K = 351) the
+// projection took 94 us one by one, now 54 (eight at a time 43, but their code cost
+// every other small launch 0.5 to 1 us).
 template <int TS, typename F>
-__device__ __forceinline__ void for_entries(int q0, int cnt, const uint32_t* __restrict__ hits,
-                                            const float* __restrict__ hitp, F f) {
-  constexpr int U = TS == 128 ? 8 : 1, TH = Geo<TS>::kThreads;
-  for (int q = q0; q < cnt; q += U * TH) {
+__device__ __forceinline__ void rest_entries(int tid, int cnt, const uint32_t* __restrict__ hits,
+                                             const float* __restrict__ hitp, F f) {
+  constexpr int U = TS == 128 ? 4 : 1, TH = Geo<TS>::kThreads;
+  if (__builtin_expect(cnt <= TH, 1)) return;
+  for (int q = TH + tid; q < cnt; q += U * TH) {
     uint32_t e[U];
     float p[U];
 #pragma unroll
@@ -479,11 +481,13 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_logits
     for (int h = 0; h < 2; ++h) {
       stage_half<TS>(st, acc, h, wm, wn, lane);
       __syncthreads();
-      for_entries<TS>(tid, cnt, hl, nullptr, [&](uint32_t e, float) {
+      auto rec = [&](uint32_t e, float) {
         int tl, v;
         if (entry_cell<TS>(e, m0, n0, tl, v) && tl / (TS / 2) == h)
           zhit[(int64_t)(n0 + tl) * K + (e >> 16)] = *stage_cell<TS>(st, tl & (TS / 2 - 1), v);
-      });
+      };
+      if (tid < cnt) rec(hl[tid], 0.f);
+      rest_entries<TS>(tid, cnt, hl, nullptr, rec);
       __syncthreads();
     }
   } else {
@@ -963,7 +967,7 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dz(
     };
     if (tid < cnt) fold(fe, fpk);
     // a bucket with more entries than threads: the rest from memory
-    for_entries<TS>(kThreads + tid, cnt, hits + seg + hb, hitp + seg + hb, fold);
+    rest_entries<TS>(tid, cnt, hits + seg + hb, hitp + seg + hb, fold);
     __syncthreads();
 
     if (dZ != nullptr) {
@@ -1109,7 +1113,7 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_logits
       zhit[(int64_t)(n0 + tl) * K + (e >> 16)] = *stage_cell<TS>(st, tl & (HT - 1), v);
     };
     if (tid < cnt) rec(fe, 0.f);
-    for_entries<TS>(kThreads + tid, cnt, hits + seg + hb, nullptr, rec);
+    rest_entries<TS>(tid, cnt, hits + seg + hb, nullptr, rec);
 
     // 16 lanes per token row, lane lam holding columns 4 lam + 64 k + (0..3), k < NK.
     // The row's run of dZ'' is 2^(y - R) against the token's reference R; the
