@@ -1497,9 +1497,11 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dh(DhA
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, acc.v[i][j][r]), ro,
-                                                o0 + 64u * j, 4 * (16 * i + r) * pitch, 0);
+        for (int j = 0; j < 4; ++j) {
+          const float v = acc.v[i][j][r];  // (a bit cast of the element itself takes element 0)
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), ro, o0 + 64u * j,
+                                                4 * (16 * i + r) * pitch, 0);
+        }
     return;
   }
   float* rsl = reinterpret_cast<float*>(lds);
