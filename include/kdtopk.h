@@ -278,16 +278,18 @@ kd_status kd_topk_kl_check_indices(const kd_problem* p,
  * kd_topk_kl_fwd_bwd for callers that cannot allocate device memory (code
  * being captured into a HIP graph, tight serving loops, harnesses that forbid
  * allocation): the same arguments without the workspace. The workspace is a
- * static per-device array of KD_SCRATCH_BYTES inside the library, which each
- * device the library runs on holds from the first use of the library on that
+ * static per-device array inside the library, KD_SCRATCH_BYTES and 8 MiB for
+ * partial sums that do not count against it, which each device the library runs
+ * on holds from the first use of the library on that
  * device until the process ends; the call itself allocates nothing (no
  * hipMalloc, no events, no allocating library routine) and only enqueues
  * kernels on hip_stream. The caller still provides every output.
  *
  * The plan is kd_topk_kl_fwd_bwd's when its workspace fits the array: results
  * are then bitwise identical to kd_topk_kl_fwd_bwd's. Otherwise fewer chunks'
- * dZ rows are gathered per grad_W contraction (grad_W differs only in the fp32
- * summation order); if one chunk's workspace does not fit (about
+ * dZ rows are gathered per grad_W contraction, and the contractions may be split
+ * into fewer ranges (every output may then differ in the order of its fp32
+ * sums); if one chunk's workspace does not fit (about
  * chunk * V * (element size) bytes plus small terms), the call returns
  * KD_ERR_WORKSPACE_TOO_SMALL before touching the device: use a smaller chunk.
  *

@@ -83,7 +83,10 @@ kd_status check_problem(const kd_problem* p) {
 //  * dW, t <= 128: 2000 x 512 x 4096 (32) 110, 90; 1000 x 512 x 16000 (126) 104,
 //    97; 2000 x 4096 x 4096 (256) 226, 238. Also up to two K steps (128 tokens)
 //    in up to two rounds, where a tile is all epilogue: 77 x 768 x 32003
-//    (t = 375) 109, 86; 128 x 1024 x 100003 (1564) 265, 285.
+//    (t = 375) 109, 86. Past two rounds 90 calls of 16 to 128 tokens, D = 64 to
+//    4096, took 0.90 to 1.04 of the time in 128x128 tiles up to t = 1400 (0.95 in the
+//    middle) and 0.98 to 1.13 from 1530 on (128 x 1024 x 100003, t = 1564: 265, 285):
+//    the line could lie at about 1400.
 int64_t tiles256(int64_t m, int64_t n) { return cdiv(m, 256) * cdiv(n, 256); }
 int proj_tile(const Plan& pl, int64_t n) {
   return pl.eb == 4 || tiles256(pl.V, n) <= 128 ? 128 : 256;
@@ -177,6 +180,10 @@ Plan base_plan(const kd_problem* p, int64_t g_max = 0) {
   //    10.80 and 9.55 ms; 512, 8192 tokens 19.26 and 18.59 ms; 1024, 16384
   //    tokens 37.99 and 37.88 ms; 2048, 16384 tokens 37.61 and 37.84 ms. fp32,
   //    256 tokens in chunks of 64 (fp32 MFMAs in 256x256 tiles): 488 and 250 us.
+  //    Other heads of whole rounds (D = 512 to 8192, V = 32768 to 131072, 8192 and
+  //    16384 tokens), merged over unmerged: chunk 256 0.87 to 0.91, 512 0.95 to
+  //    0.99, 1024 0.96 to 1.03 (above 1 at D = 512, V = 65536 only), 2048 0.97 to
+  //    1.02, 4096 0.97 to 1.02: no clear winner from 2048 on.
   //  * A chunk whose tiles fill the chip is merged only when padding its last
   //    256-token tile costs more than merging (above 5% of its rows): each
   //    chunk's dH right after its own projection is faster than one dH over

@@ -4,10 +4,10 @@
 //
 // x = hi + mid + lo with hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid:
 // both subtractions are exact and 24 bits of mantissa fit in 3 x 8, so the
-// three terms are x (each at most 2^-8 of the one before). Of the nine
+// three terms are x (mid at most 2^-8 and lo 2^-17 of it). Of the nine
 // products the six largest are accumulated in fp32; the three left out (mid
-// lo, lo mid, lo lo) are at most 2^-25 of the product together, below the
-// rounding of one fp32 accumulation. Why: the bf16 MFMA does 16 times the
+// lo, lo mid, lo lo) are at most 2^-24 of the product together (x = 1.0038986
+// squared), as much as the rounding of one fp32 accumulation. Why: the bf16 MFMA does 16 times the
 // multiply-adds per cycle of the fp32 one (about 2.5 PFLOP/s against 157
 // TFLOP/s dense), so six of them take 3/8 of its time. The relative error of
 // the gradients against 64 bits is below the fp32 MFMA's (256 x 256 x 4096:

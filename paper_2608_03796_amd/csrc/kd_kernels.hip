@@ -27,7 +27,9 @@
 //
 // A kernel of a few microseconds of work occupies the stream for about 4.7 us,
 // so the small passes share launches where nothing orders them: a step of one
-// group is 6 launches (7 with a mask), which were 11 (14).
+// group is 6 launches, which were 11, and one more each with a mask, for K > 128
+// (prologue and buckets apart), where the projection's last tiles run as small ones
+// and where dW's last round is split (fixup).
 #include "kd_device.h"
 #include "kd_f32.h"
 #include <type_traits>

@@ -8,10 +8,10 @@
 enum { KD_MODE_FWD_BWD = 0, KD_MODE_FWD = 1, KD_MODE_BWD = 2 };
 
 // bytes of the allocation-free entry point's static per-device scratch: the
-// 256 MiB a plan may count, and a slack for the projection's partials of
-// 128-column vocabulary tiles above those of 256-column ones: 8 bytes per row
-// (padded to 256) and 256 columns, at most 8 MiB (256 rows at V = 2^20; more
-// rows only with fewer columns)
+// 256 MiB a plan without its partial tiles may count, and a slack for the
+// projection's partials of 128-column vocabulary tiles above those of 256-column
+// ones: 8 bytes per row (padded to 256) and 256 columns, at most 8 MiB (256 rows
+// at V = 2^20; more rows only with fewer columns). Partial tiles take what is left.
 constexpr size_t kd_scratch_slack = (size_t)8 << 20;
 constexpr size_t kd_scratch_bytes_max = ((size_t)256 << 20) + kd_scratch_slack;
 
