@@ -2236,17 +2236,9 @@ static DhArgs dh_args(const KdDhArgs& a) {
 template <typename T, int TS>
 static int launch_dh_impl(const KdDhArgs& a, hipStream_t s) {
   const DhArgs d = dh_args<T, TS>(a);
-  // with a device-side row count: the most workgroups any count needs (the
-  // fewest rows of a tile row leave room for the most ranges)
-  int blocks = d.sp.dp + d.sp.rem * d.sp.split;
-  if (a.nrow != nullptr)
-    for (int tm = cdiv(a.tokens, TS); tm > 0; --tm) {
-      // (full rounds and at most two of parts: no fewer rows need more)
-      if (tm * d.TN / kd_units(TS) * kd_units(TS) + 2 * kd_units(TS) <= blocks) break;
-      const KdRounds q = kd_dh_rounds((tm - 1) * TS + 1, (int)a.D, TS, d.ks_total, sizeof(T) == 4,
-                                      a.part_space);
-      blocks = std::max(blocks, q.dp + q.rem * q.split);
-    }
+  const int blocks = a.nrow == nullptr ? d.sp.dp + d.sp.rem * d.sp.split
+                                       : kd_dh_blocks((int)a.tokens, (int)a.D, TS, d.ks_total,
+                                                      sizeof(T) == 4, a.part_space);
   {
     ProfScope ps_(P_DH, 2.0 * (double)a.tokens * (double)a.D * (double)a.V, s);
     hipLaunchKernelGGL((k_dh<T, TS>), dim3(blocks), dim3(Geo<TS>::kThreads), 0, s, d);

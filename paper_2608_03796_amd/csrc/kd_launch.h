@@ -180,6 +180,21 @@ inline KdRounds kd_dh_rounds(int n, int D, int tile, int ksteps, bool f32, int s
                          kd_dh_max_parts(tiles, n, D, tile, space));
 }
 
+// Workgroups of a dH launch over `tokens` rows of which the device may find any
+// number to hold tokens: the most any count needs (the fewest rows of a tile row
+// leave room for the most ranges).
+inline int kd_dh_blocks(int tokens, int D, int tile, int ksteps, bool f32, int space) {
+  const int units = kd_units(tile), td = (D + tile - 1) / tile;
+  int blocks = 0;
+  for (int tm = (tokens + tile - 1) / tile; tm > 0; --tm) {
+    // (full rounds and at most two of parts: no fewer rows need more)
+    if (tm * td / units * units + 2 * units <= blocks) break;
+    const KdRounds r = kd_dh_rounds((tm - 1) * tile + 1, D, tile, ksteps, f32, space);
+    if (r.dp + r.rem * r.split > blocks) blocks = r.dp + r.rem * r.split;
+  }
+  return blocks;
+}
+
 // the most parts of a split dW tile that k_dw_fixup has in flight at a time
 constexpr int kDwMaxSplit = 4;
 

@@ -39,6 +39,29 @@ int64_t rec_dh_bytes(int n, int D, int tile, int ksteps, int f32, int64_t part_b
   return 4 * (int64_t)r.split * (r.dp == 0 ? (int64_t)n * D : (int64_t)r.rem * tile * tile);
 }
 
+// dH over 0..tokens rows: 0 if every count's workgroups and partial tiles stay
+// within the launch's and the model's choice is the least of all numbers of
+// ranges (as a wave takes it on the device), else a count for which one fails, + 1
+int rec_dh_counts(int tokens, int D, int tile, int ksteps, int f32, int space) {
+  const int blocks = kd_dh_blocks(tokens, D, tile, ksteps, f32 != 0, space);
+  const int units = kd_units(tile), cost = kd_part_cost(tile, f32 != 0);
+  for (int n = 0; n <= tokens; ++n) {
+    const KdRounds r = kd_dh_rounds(n, D, tile, ksteps, f32 != 0, space);
+    if (r.dp + r.rem * r.split > blocks) return n + 1;
+    const int64_t bytes =
+        4 * (int64_t)r.split * (r.dp == 0 ? (int64_t)n * D : (int64_t)r.rem * tile * tile);
+    if (r.split > 1 && bytes > (int64_t)space * 256) return n + 1;
+    const int tiles = r.dp + r.rem, parts = kd_dh_max_parts(tiles, n, D, tile, space);
+    int best = 1;
+    for (int s = 2; s <= kSplitMax; ++s)
+      if (kd_split_time(s, r.rem, ksteps, units, cost, parts) <
+          kd_split_time(best, r.rem, ksteps, units, cost, parts))
+        best = s;
+    if (r.rem > 0 && best != r.split) return n + 1;
+  }
+  return 0;
+}
+
 int kd_launch_fill(float*, int64_t, void*) { return 0; }
 int kd_launch_chunk(const KdChunkArgs*, void*) { return 0; }
 int kd_launch_compact(const KdCompactArgs*, void*) { return 0; }

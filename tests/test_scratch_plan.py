@@ -1,6 +1,7 @@
-"""The plan of the allocation-free entry point when the call's own plan does not
-fit the static scratch, on the CPU: the host schedule (kd_api.cpp) compiled with
-launchers that only record what they are given (launch_recorder.cpp)."""
+"""What the host schedule launches, on the CPU: kd_api.cpp compiled with launchers
+that only record what they are given (launch_recorder.cpp). Above all the plan of
+the allocation-free entry point when the call's own plan does not fit the static
+scratch, and the split of dH for the row counts a device may find."""
 import ctypes
 import os
 import subprocess
@@ -140,3 +141,18 @@ def test_scaled_gradients_that_share_buffers_keep_their_order(host):
     assert launches(A, bf16, B, n, C, bf16, B + 0x1000, n) == [(n, 0), (n, 0)]
     assert launches(A, bf16, B, n, C, bf16, B + 0x2000, n) == [(n, n)]
     assert launches(A, f32, B, n, None, f32, None, n) == [(n, 0)]
+
+
+def test_every_row_count_stays_within_the_launch(host):
+    """With a mask the device finds the rows of dH and splits for them: whatever
+    their number, the workgroups it uses were launched, its partial tiles fit
+    their space, and the numbers of ranges tried one after the other and all at
+    once give the same choice."""
+    import random
+    rng = random.Random(6)
+    for _ in range(400):
+        tile, f32 = rng.choice([(256, 0), (128, 0), (128, 1)])
+        D = 64 * rng.choice([rng.randint(1, 24), rng.randint(1, 200)])
+        space = rng.choice([512 * 256 * 256 // 64, rng.randint(1, 1 << 19), rng.randint(1, 4096)])
+        args = (rng.randint(1, rng.choice([600, 9000])), D, tile, rng.randint(1, 2048), f32, space)
+        assert host.rec_dh_counts(*args) == 0, args
