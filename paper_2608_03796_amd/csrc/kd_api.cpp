@@ -132,8 +132,8 @@ size_t dh_part_bytes(const Plan& pl, int64_t n) {
   for (int64_t tm = tm_max; tm > std::max<int64_t>(0, tm_max - period); --tm) {
     const int64_t rows = std::min(tm * ts, n);
     const KdRounds s = dh_split(pl, rows, ts);
-    if (s.split > 1)
-      bytes = std::max(bytes, (size_t)4 * s.split * (s.dp == 0 ? rows * pl.D : (int64_t)s.rem * ts * ts));
+    const int64_t part = s.dp == 0 ? rows * pl.D : (int64_t)s.rem * ts * ts;  // of a range
+    if (s.split > 1) bytes = std::max(bytes, (size_t)4 * s.split * part);
   }
   return bytes;
 }

@@ -956,8 +956,8 @@ __global__ __launch_bounds__(Geo<TS>::kThreads, TS == 256 ? 1 : 2) void k_dz(
     __syncthreads();
 
     // Teacher entries of this half: dZ = (g/tau) M q - (g/tau) p in place.
-    // Thread tid has entry tid of the bucket in registers; a skewed teacher with more entries in one tile
-    // than threads reads the rest from memory.
+    // Thread tid has entry tid of the bucket in registers; a skewed teacher with
+    // more entries in one tile than threads reads the rest from memory.
     auto fold = [&](uint32_t e, float pk) {
       int tl, v;
       if (!entry_cell<TS>(e, m0, n0, tl, v) || tl / HT != h) return;
@@ -1416,7 +1416,8 @@ __device__ __forceinline__ KdRounds split_rounds(int tiles, int ksteps, int unit
   KdRounds r;
   r.dp = tiles / units * units;
   r.rem = tiles - r.dp;
-  const int t = kd_split_time((int)(threadIdx.x & 63) + 1, r.rem, ksteps, units, part_cost, max_parts);
+  const int ranges = (int)(threadIdx.x & 63) + 1;
+  const int t = kd_split_time(ranges, r.rem, ksteps, units, part_cost, max_parts);
   int best = t;
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) best = min(best, __shfl_xor(best, o));
